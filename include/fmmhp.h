@@ -107,10 +107,12 @@ typedef struct {
  * and the deep-level M2L on streams of their own beside the rest: a profiling aid (each kernel's
  * duration is then its own, not shared with concurrent kernels); slower. */
 #define FMMHP_FLAG_SERIAL 16u
-/* Form of the FP64 M2L of upper sources (eq. (truncatedM2Lcoef) and the log-kernel M2L): the vector
- * ALUs (one lane per target box, operators in scalar registers; the default) or the FP64 matrix cores
- * (v_mfma_f64_16x16x4f64, complex numbers as 2 x 2 real blocks); at most one of the two flags.  The
- * same sums in another order (agreement to rounding).  Ignored with FMMHP_FLAG_M2L_FP32. */
+/* Form of the FP64 M2L of upper sources (eq. (truncatedM2Lcoef) and the log-kernel M2L).  The default
+ * translates plane waves: the same sums through a quadrature whose error stays below the expansion's
+ * own at every p (under 1% of it up to p = 25, 12% at p = 30, of the order of rounding above).  The
+ * flags select the Hankel rows themselves, on the vector ALUs (one lane per target box, operators in
+ * scalar registers) or on the FP64 matrix cores (v_mfma_f64_16x16x4f64, complex numbers as 2 x 2 real
+ * blocks); at most one of the two.  Ignored with FMMHP_FLAG_M2L_FP32. */
 #define FMMHP_FLAG_M2L_VECTOR 32u
 #define FMMHP_FLAG_M2L_MFMA 64u
 
@@ -436,8 +438,8 @@ fmmhp_status fmmhp_reaction_integrals(int64_t m, const double *x, const double *
  *   best         [host] receives the chosen options (p, leaf_size, and the launch shape
  *                near_walk, near_groups timed on the chosen plan, six shapes (walks 1, 2 and 4 on
  *                two to eight workgroups per CU) in turn over three rounds; a shape other than the
- *                default needs to be more than 2% faster; then the FP64 M2L form: the other of
- *                FMMHP_FLAG_M2L_VECTOR and FMMHP_FLAG_M2L_MFMA when more than 2% faster; then
+ *                default needs to be more than 2% faster; then the FP64 M2L form:
+ *                FMMHP_FLAG_M2L_MFMA instead of the default when more than 2% faster; then
  *                flags gets FMMHP_FLAG_M2L_FP32 when the FP32 matrix-core M2L on that plan and
  *                shape still meets tol against the direct sum and is more than 2% faster;
  *                max_level 0)

@@ -30,8 +30,8 @@ FLAG_M2L_FP32 = 2  # fmmhp_opts.flags: upper-source M2L on the FP32 matrix cores
 FLAG_DIRICHLET = 4  # fmmhp_opts.flags: Dirichlet half-plane kernel (eq. (ddd1.2), image term +)
 FLAG_NEUMANN = 8    # fmmhp_opts.flags: Neumann half-plane kernel (eq. (ddd1.2), image term -)
 FLAG_SERIAL = 16    # fmmhp_opts.flags: every kernel on the eval stream (profiling aid)
-FLAG_M2L_VECTOR = 32  # fmmhp_opts.flags: FP64 M2L on the vector ALUs (the default form)
-FLAG_M2L_MFMA = 64    # fmmhp_opts.flags: FP64 M2L on the matrix cores
+FLAG_M2L_VECTOR = 32  # fmmhp_opts.flags: FP64 M2L by Hankel rows on the vector ALUs
+FLAG_M2L_MFMA = 64    # fmmhp_opts.flags: FP64 M2L by Hankel rows on the matrix cores
 
 
 def _m2l_flag(form):
@@ -399,8 +399,8 @@ class HalfPlaneFMM:
     bc          "robin" (the impedance condition), "dirichlet" or "neumann" (eq. (ddd1.2); the
                 impedance is then ignored)
     serial      every kernel on the eval stream, one after another (profiling aid; slower)
-    m2l_form    FP64 M2L form: None (the default: vector ALUs), "vector" or "mfma" (the same sums
-                in another order)
+    m2l_form    FP64 M2L form: None (the default: plane waves), "vector" or "mfma" (the Hankel rows
+                on the vector ALUs or the matrix cores)
     """
 
     def __init__(self, x, y, impedance, p=20, leaf_size=40, max_level=0, pass_images=False,

@@ -47,6 +47,7 @@
 
 #include "internal.hpp"
 #include "special.hpp"
+#include "m2l_pw.hpp"
 
 namespace fmmhp {
 
@@ -412,7 +413,8 @@ __global__ __launch_bounds__(256) void k_m2m_sub(int nlev, const int2 *__restric
 }
 
 // ---------------------------------------------------------------------------------------------
-// M2L over tiles of same-level, same-class target boxes; one wave per (tile, chunk of CH output
+// M2L by Hankel rows (FMMHP_FLAG_M2L_VECTOR; the default is the plane-wave form of m2l_pw.hpp) over
+// tiles of same-level, same-class target boxes; one wave per (tile, chunk of CH output
 // coefficients).  Lanes are target boxes; the operator of an offset slot is the same for every
 // lane, so its coefficients are read with scalar loads.  Operator rows are zero-padded to
 // m2l_row(PB) entries so that every chunk runs the same branch-free inner loop.
@@ -2654,6 +2656,143 @@ static fmmhp_status to_host(std::vector<T> &dst, const T *src, size_t n, hipStre
     return FMMHP_OK;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Tiles and tables of the plane-wave M2L
+// ---------------------------------------------------------------------------------------------
+// Box ids of each tile's source and target children by quadrant, from its parents (par, src: parent
+// boxes, -1 padding).
+__global__ void k_pw_boxes(int ntiles, const int32_t *__restrict__ src_par, const int32_t *__restrict__ tgt_par,
+                           const int32_t *__restrict__ child_first, const int32_t *__restrict__ nchild,
+                           const int32_t *__restrict__ bx, const int32_t *__restrict__ by, int32_t *__restrict__ src,
+                           int32_t *__restrict__ tgt) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int per = 64 + kPwPar;
+    if (i >= ntiles * per) return;
+    const int t = i / per, k = i - t * per;
+    const bool is_src = k < 64;
+    const int p = is_src ? src_par[t * 64 + k] : tgt_par[t * kPwPar + k - 64];
+    int ch[4] = {-1, -1, -1, -1};
+    if (p >= 0)
+        for (int c = child_first[p]; c < child_first[p] + nchild[p]; ++c) {
+            const int q = (bx[c] & 1) | ((by[c] & 1) << 1);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ch[j] = q == j ? c : ch[j];
+        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (is_src) src[((int64_t)t * 4 + q) * 64 + k] = ch[q];
+        else tgt[((int64_t)t * 4 + q) * kPwPar + k - 64] = ch[q];
+    }
+}
+
+// Tiles: consecutive non-leaf boxes of one level (the parents), at most kPwPar of them and kPwCells
+// distinct non-leaf upper colleagues.  Seven parents always fit (8 colleagues each).
+static fmmhp_status build_pw_tiles(Arena &A, const Tree &T, Sched &S, const std::vector<int32_t> &level,
+                                   const std::vector<int32_t> &leaf, hipStream_t s) {
+    std::vector<int32_t> par;
+    for (int b = 0; b < T.nbox; ++b)
+        if (!leaf[b]) par.push_back(b);
+    const int np = (int)par.size();
+    std::vector<int32_t> nbr;
+    FMMHP_CHECK(parent_colleagues(T, par, nbr, s));
+    std::vector<int32_t> src, tgt, uniq, stamp(T.nbox, -1);
+    std::vector<uint64_t> cells;
+    S.tile_lev.assign(T.depth + 2, 0);
+    int nt = 0, lev = 0;
+    for (int i = 0; i < np;) {
+        const int l = level[par[i]] + 1;  // level of the targets
+        while (lev < l) S.tile_lev[++lev] = nt;
+        uniq.clear();
+        int k = 0;
+        tgt.resize((size_t)(nt + 1) * kPwPar, -1);
+        cells.resize((size_t)(nt + 1) * kPwPar, 0x0101010101010101ull * kPwCells);
+        for (; i < np && k < kPwPar && level[par[i]] + 1 == l; ++i, ++k) {
+            const size_t had = uniq.size();
+            uint64_t c = 0;
+            for (int j = 0; j < 8; ++j) {
+                const int32_t q = nbr[(size_t)i * 8 + j];
+                int at = kPwCells;
+                if (q >= 0) {
+                    if (stamp[q] < 0) {
+                        stamp[q] = (int32_t)uniq.size();
+                        uniq.push_back(q);
+                    }
+                    at = stamp[q];
+                }
+                c |= (uint64_t)at << (8 * j);
+            }
+            if ((int)uniq.size() > kPwCells) {  // this parent opens the next tile
+                for (size_t u = had; u < uniq.size(); ++u) stamp[uniq[u]] = -1;
+                uniq.resize(had);
+                break;
+            }
+            tgt[(size_t)nt * kPwPar + k] = par[i];
+            cells[(size_t)nt * kPwPar + k] = c;
+        }
+        src.resize((size_t)(nt + 1) * 64, -1);
+        for (size_t u = 0; u < uniq.size(); ++u) {
+            src[(size_t)nt * 64 + u] = uniq[u];
+            stamp[uniq[u]] = -1;
+        }
+        ++nt;
+    }
+    while (lev < T.depth + 1) S.tile_lev[++lev] = nt;
+    S.ntiles = nt;
+    int32_t *d_src = nullptr, *d_tgt = nullptr;
+    FMMHP_CHECK(to_dev(A, &d_src, src, "M2L tile source parents", s));
+    FMMHP_CHECK(to_dev(A, &d_tgt, tgt, "M2L tile target parents", s));
+    FMMHP_CHECK(to_dev(A, &S.pw_cells, cells, "M2L tile cells", s));
+    FMMHP_CHECK(A.alloc_n(&S.pw_src, (size_t)nt * 4 * 64, "M2L tile sources"));
+    FMMHP_CHECK(A.alloc_n(&S.pw_tgt, (size_t)nt * 4 * kPwPar, "M2L tile targets"));
+    if (nt > 0) {
+        hipLaunchKernelGGL(k_pw_boxes, dim3(nblk((int64_t)nt * (64 + kPwPar), 256)), dim3(256), 0, s, nt, d_src, d_tgt,
+                           T.child_first, T.nchild, T.bx, T.by, S.pw_src, S.pw_tgt);
+        FMMHP_HIP(hipGetLastError());
+    }
+    FMMHP_HIP(hipStreamSynchronize(s));  // the uploads read host vectors
+    return FMMHP_OK;
+}
+
+// Node tables: source rows mu^m; target rows {f, cos and sin of mu, 3 mu, 5 mu, 2 mu} and g mu^n with
+// f = e^(-2 mu), g = omega e^(-4 mu) / (4 pi mu); Lp = L minus the quadrature's own n = m = 0 term.
+static fmmhp_status build_pw_tables(Arena &A, Sched &S, const std::vector<cplx> &Lfree, hipStream_t s) {
+    using ld = long double;
+    const int PB = S.PB, K = pw_nodes(PB), K2 = 2 * pw_steps(PB), TS = pw_src_row(PB), TT = pw_tgt_row(PB);
+    std::vector<double> ts((size_t)K2 * TS, 0.0), tt((size_t)K2 * TT, 0.0);
+    std::vector<cplx> Lp(Lfree);
+    std::vector<std::complex<ld>> Q(kNumSlots, 0);
+    const ld pi = 3.14159265358979323846264338327950288L;
+    for (int k = 0; k < K; ++k) {
+        const ld mu = pw_mu(PB)[k], f = std::exp(-2 * mu), g = pw_omega(PB)[k] * f * f / (4 * pi * mu);
+        double *a = ts.data() + (size_t)k * TS, *b = tt.data() + (size_t)k * TT;
+        ld pw = 1;
+        for (int n = 0; n <= PB; ++n, pw *= mu) {
+            a[n] = (double)pw;
+            b[kPwConst + n] = (double)(g * pw);
+        }
+        const ld c[kPwConst] = {f, std::cos(mu), std::sin(mu), std::cos(3 * mu), std::sin(3 * mu),
+                                std::cos(5 * mu), std::sin(5 * mu), std::cos(2 * mu), std::sin(2 * mu)};
+        for (int j = 0; j < kPwConst; ++j) b[j] = (double)c[j];
+        for (int dy = -3; dy <= 3; ++dy)
+            for (int dx = -3; dx <= 3; ++dx) {
+                if (std::abs(dx) <= 1 && std::abs(dy) <= 1) continue;
+                const bool ns = std::abs(dy) >= 2;  // N and S take the rows two and three away, E and W the rest
+                const int far = ns ? std::abs(dy) : std::abs(dx);
+                // e^(-mu eta), eta the offset turned so that its main part is real and positive
+                const ld ph = ns ? (dy > 0 ? 2 * mu * dx : -2 * mu * dx) : (dx > 0 ? -2 * mu * dy : 2 * mu * dy);
+                const ld r = g * std::exp(-2 * mu * (far - 2));
+                Q[slot_of(dx, dy)] += std::complex<ld>(r * std::cos(ph), r * std::sin(ph));
+            }
+    }
+    for (int o = 0; o < kNumSlots; ++o)
+        Lp[o] = mk((double)(Lfree[o].re - Q[o].real()), (double)(Lfree[o].im - Q[o].imag()));
+    FMMHP_CHECK(to_dev(A, &S.pw_ts, ts, "M2L source node table", s));
+    FMMHP_CHECK(to_dev(A, &S.pw_tt, tt, "M2L target node table", s));
+    FMMHP_CHECK(to_dev(A, &S.pw_L, Lp, "M2L log table", s));
+    FMMHP_HIP(hipStreamSynchronize(s));  // the uploads read local vectors
+    return FMMHP_OK;
+}
+
 static fmmhp_status ensure_vec_ws(Arena &A, const Tree &T, Sched &S, int nv);
 
 fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cplx *Zs, hipStream_t s) {
@@ -2700,16 +2839,19 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         fn(0);
         for (auto &th : pool) th.join();
     };
+    // The slot table and the tiles of the Hankel forms are built only for the plans that ask for one
+    // (the plane-wave form has tiles of its own, below).
+    const bool hankel = S.m2l_fp32 || S.m2l_form != 0;
     // M2L slots: vslot[b * kNumSlots + o] = upper V source of box b at offset slot o, or -1; image
     // V entries (source << 5 | slot) per box.  Threads take contiguous box ranges.
-    std::unique_ptr<int32_t[]> vslot(new int32_t[(size_t)kNumSlots * std::max(1, nbox)]);
+    std::unique_ptr<int32_t[]> vslot(new int32_t[hankel ? (size_t)kNumSlots * std::max(1, nbox) : 1]);
     std::vector<int32_t> vimg_off(nbox + 1, 0), vimg_ent;
     {
         std::vector<std::vector<int32_t>> img_t(nthr);
         std::atomic<int> bad{0};  // 1: V entry outside the 7 x 7 block, 2: image entry above its target
         run_threads([&](int t) {
             const int b0 = (int)((int64_t)nbox * t / nthr), b1 = (int)((int64_t)nbox * (t + 1) / nthr);
-            std::fill(vslot.get() + (size_t)b0 * kNumSlots, vslot.get() + (size_t)b1 * kNumSlots, -1);
+            if (hankel) std::fill(vslot.get() + (size_t)b0 * kNumSlots, vslot.get() + (size_t)b1 * kNumSlots, -1);
             std::vector<int32_t> &out = img_t[t];
             for (int b = b0; b < b1; ++b) {
                 const int l = level[b];
@@ -2723,7 +2865,7 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
                         continue;
                     }
                     if (!img) {
-                        vslot[(size_t)b * kNumSlots + slot_of(dx, dy)] = c;
+                        if (hankel) vslot[(size_t)b * kNumSlots + slot_of(dx, dy)] = c;
                     } else {
                         if (dy > -1) bad = 2;
                         out.push_back((c << 5) | slot_of(dx, dy));
@@ -2771,7 +2913,8 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
     std::vector<int32_t> tiles, tlev, tsoff(1, 0), tsrc;
     std::vector<int16_t> tslot;
     std::vector<uint64_t> tmask;
-    {
+    S.tile_lev.assign(T.depth + 2, 0);
+    if (hankel) {
         struct TileOut {
             std::vector<int32_t> boxes, src, nsrc, lev;  // kTile boxes (-1 padded) and sources per tile
             std::vector<int16_t> slot;                    // kNumSlots x kTile per tile
@@ -2872,11 +3015,10 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
                 for (size_t k = 0; k < o.nsrc.size(); ++k) tsoff[at[i] + k + 1] = (off += o.nsrc[k]);
             }
         });
-        S.tile_lev.assign(T.depth + 2, 0);
         for (int l = 2; l <= T.depth + 1; ++l) S.tile_lev[l] = (int)at[init_lev[l]];
-        S.tile_lev[0] = S.tile_lev[1] = 0;
     }
     S.ntiles = (int)tlev.size();
+    if (!hankel) FMMHP_CHECK(build_pw_tiles(A, T, S, level, leaf, s));
     FMMHP_CHECK(to_dev(A, &S.tiles, tiles, "tiles", s));
     FMMHP_CHECK(to_dev(A, &S.tile_level, tlev, "tile levels", s));
     FMMHP_CHECK(to_dev(A, &S.tile_src_off, tsoff, "tile source offsets", s));
@@ -3153,6 +3295,7 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         FMMHP_CHECK(to_dev(A, &S.Bf32, B, "FP32 M2L operators", s));
     }
     FMMHP_CHECK(to_dev(A, &S.Lfree, Lfree, "Lfree", s));
+    if (!hankel) FMMHP_CHECK(build_pw_tables(A, S, Lfree, s));
     {
         std::vector<double> ls(nbox);
         // log(2 rho) per (instance, level), the same value for every box there
@@ -3592,7 +3735,11 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
                 M2LArgs ma{nbox,    t0,      S.tiles,   S.tile_level, S.tile_src_off, S.tile_src, S.tile_slot,
                            S.tile_mask, S.Tfree, S.Lfree, S.logside,  ws.W,            ws.Lam,      S.nloc};
                 FMMHP_CHECK(mk_.km_mark(which, 0, st));
-                if (S.m2l_form != 2)
+                if (S.m2l_form == 0) {
+                    PwArgs pa{nbox,    t0,      S.nloc, S.pw_src,  S.pw_tgt, S.pw_cells,
+                              S.pw_ts, S.pw_tt, S.pw_L, S.logside, ws.W,     ws.Lam};
+                    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2l_pw<PB>), dim3(t1 - t0, NV), dim3(512), 0, st, pa);
+                } else if (S.m2l_form == 1)
                     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2l<PB, CH>), dim3(t1 - t0, NV), dim3(64 * m2l_waves(PB)),
                                        0, st, ma);
                 else

@@ -106,6 +106,11 @@ fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, 
                         const double *img_x, const double *img_y, int64_t src_end, int leaf_size, int max_level,
                         hipStream_t stream);
 
+// The eight colleagues of each box of par (all non-leaf) that are upper non-leaf boxes, else -1, in
+// the order (-1,-1) (0,-1) (1,-1) (-1,0) (1,0) (-1,1) (0,1) (1,1): nbr[8 * par.size()] on the host.
+fmmhp_status parent_colleagues(const Tree &T, const std::vector<int32_t> &par, std::vector<int32_t> &nbr,
+                               hipStream_t stream);
+
 // Root square and impedance of one instance of a plan.
 struct InstInfo {
     double x_lo, S;
@@ -164,6 +169,12 @@ struct Sched {
     int32_t *tile_src = nullptr;
     int16_t *tile_slot = nullptr;   // [ntiles][kNumSlots][kTile] index into the tile's sources, -1
     uint64_t *tile_mask = nullptr;  // [ntiles] slots used by any lane of the tile
+    // plane-wave M2L (the default form): per tile the source and target boxes by quadrant, the cells of
+    // each parent's colleagues, the quadrature's node tables
+    int32_t *pw_src = nullptr, *pw_tgt = nullptr;
+    uint64_t *pw_cells = nullptr;
+    double *pw_ts = nullptr, *pw_tt = nullptr;
+    cplx *pw_L = nullptr;           // [kNumSlots]
     // X list targets
     int nxbox = 0;
     int32_t *xbox = nullptr;
@@ -216,8 +227,8 @@ struct Sched {
     // tables
     cplx *Tfree = nullptr;          // [kNumSlots][m2l_row(PB)]
     bool m2l_fp32 = false;          // FMMHP_FLAG_M2L_FP32: upper-source M2L on the FP32 matrix cores
-    int m2l_form = 0;               // FP64 M2L of upper sources: 0 default (vector ALUs), 1 vector ALUs
-                                    // (k_m2l), 2 matrix cores (k_m2l_mf)
+    int m2l_form = 0;               // FP64 M2L of upper sources: 0 default (plane waves, k_m2l_pw), 1 Hankel
+                                    // rows on the vector ALUs (k_m2l), 2 on the matrix cores (k_m2l_mf)
     float *Bf32 = nullptr;          // [kNumSlots][KP][NP] embedded scaled operators (FP32 M2L)
     cplx *Lfree = nullptr;          // [kNumSlots]   (offset part of the log term)
     cplx *TimgH = nullptr;          // [blocks][kNumImgSlots][m2l_row(PB)]

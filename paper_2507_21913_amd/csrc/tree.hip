@@ -687,6 +687,36 @@ __global__ void k_lists(TreeView t, int nbox, int32_t *__restrict__ cnt /* [4][n
     }
 }
 
+// Upper non-leaf colleagues of the boxes par (parent_colleagues).
+__global__ void k_colleagues(TreeView t, int np, const int32_t *__restrict__ par, int32_t *__restrict__ nbr) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 8 * np) return;
+    const int b = par[i >> 3], j = i & 7, k = j + (j >= 4 ? 1 : 0);  // k: 3 x 3 without its centre
+    const int r = find_box(t, t.inst[b], t.level[b], t.bx[b] + k % 3 - 1, t.by[b] + k / 3 - 1);
+    nbr[i] = (r >= 0 && !(r & 1) && !t.leaf[r >> 1]) ? r >> 1 : -1;
+}
+
+fmmhp_status parent_colleagues(const Tree &T, const std::vector<int32_t> &par, std::vector<int32_t> &nbr,
+                               hipStream_t s) {
+    const int np = (int)par.size();
+    nbr.resize((size_t)8 * np);
+    if (np == 0) return FMMHP_OK;
+    Scratch sc(s);
+    int32_t *d_par = nullptr, *d_nbr = nullptr, *dlev = nullptr;
+    FMMHP_CHECK(sc.get(&d_par, np, "parents"));
+    FMMHP_CHECK(sc.get(&d_nbr, (size_t)8 * np, "colleagues"));
+    FMMHP_CHECK(sc.get(&dlev, 33, "level starts"));
+    FMMHP_HIP(hipMemcpyAsync(dlev, T.lev_start.data(), 33 * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    FMMHP_HIP(hipMemcpyAsync(d_par, par.data(), (size_t)np * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    TreeView tv{T.level, T.bx, T.by, T.parent, T.leaf, T.child_first, T.nchild, T.inst, T.prefix, dlev, T.depth,
+                T.lbits};
+    hipLaunchKernelGGL(k_colleagues, dim3(nblocks((int64_t)8 * np, 256)), dim3(256), 0, s, tv, np, d_par, d_nbr);
+    FMMHP_HIP(hipGetLastError());
+    FMMHP_HIP(hipMemcpyAsync(nbr.data(), d_nbr, (size_t)8 * np * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    FMMHP_HIP(hipStreamSynchronize(s));
+    return FMMHP_OK;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Driver
 // ---------------------------------------------------------------------------------------------

@@ -204,8 +204,8 @@ extern "C" fmmhp_status fmmhp_tune(int64_t n, const double *x, const double *y, 
             (void)fmmhp_plan_destroy(plan);
         }
     }
-    // FP64 M2L form: the other of the vector-ALU and matrix-core forms on the chosen plan and launch
-    // shape (the same sums in another order), kept when it is more than 2% faster
+    // FP64 M2L form: the matrix-core Hankel rows instead of the default plane waves on the chosen plan
+    // and launch shape, kept when more than 2% faster
     if (st == FMMHP_OK && best_ms < INFINITY) {
         fmmhp_opts of = bo;
         fmmhp_plan_t plan = nullptr;
