@@ -71,8 +71,8 @@ typedef struct {
     /* Launch shape of the near field (the U-list sums), which runs beside the far-field kernels on
      * a bounded grid.  Neither changes what is computed beyond rounding; fmmhp_tune picks both by
      * timing.  0 selects the default for the plan's p. */
-    int near_walk;   /* 0: default; 1: source points loaded one step ahead of their use (hides
-                        memory latency, more instructions per pair); 2: plain walk; 3: symmetric
+    int near_walk;   /* 0: default; 1, 2: a wave per leaf, its targets in registers against the stream
+                        of its sources (2: the default grid is twice as large); 3: symmetric
                         leaf pairs (potential evaluations: each pair of leaves once, its column
                         sums gathered by a second kernel; other passes use walk 1); 4: symmetric
                         leaf pairs with the pairs blocked in registers (each lane holds up to 8

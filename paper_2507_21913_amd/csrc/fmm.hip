@@ -44,6 +44,7 @@
 #include <cmath>
 #include <complex>
 #include <thread>
+#include <type_traits>
 
 #include "internal.hpp"
 #include "special.hpp"
@@ -94,6 +95,11 @@ __device__ __forceinline__ cplx reaction_I0_near(double x, double y, cplx Z) {
     return kInv2Pi * (e * mk(-ei.re, kPi - ei.im));
 }
 
+__global__ void k_zero_i32(int32_t *__restrict__ p, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0;
+}
+
 __global__ void k_pack_xy(const double *__restrict__ xs, const double *__restrict__ ys, int64_t n,
                           double2 *__restrict__ xy) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -103,15 +109,6 @@ __global__ void k_pack_xy(const double *__restrict__ xs, const double *__restric
 // ---------------------------------------------------------------------------------------------
 // Charges into sorted order
 // ---------------------------------------------------------------------------------------------
-// U entry (box << 1 | image) -> (first point, count | image << 31) of the box
-__global__ void k_u2(int64_t m, const int32_t *__restrict__ uent, const int32_t *__restrict__ first,
-                     const int32_t *__restrict__ count, int2 *__restrict__ u2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const int code = uent[i], c = code >> 1;
-    u2[i] = make_int2(first[c], (int)((unsigned)count[c] | ((unsigned)(code & 1) << 31)));
-}
-
 // ---------------------------------------------------------------------------------------------
 // nv charge vectors [nv][n] (caller order) -> qs[i * nv + v] (sorted, vectors interleaved)
 __global__ void k_gather_q(const double *__restrict__ q, const int32_t *__restrict__ perm, int64_t n, int nv,
@@ -1594,7 +1591,6 @@ struct LeafArgs {
     double *qc;              // [n] sum of the charges coincident with each sorted target, or null
     double *phi;             // [nv][n][2] potential, caller order (potential modes)
     cplx *gx, *gy;           // [n] gradient, caller order (gradient modes)
-    const int2 *u2;          // per U entry: (first point, point count | image << 31) of its source box
     double isg;              // sign of the image log term: +1 (Robin, Dirichlet), -1 (Neumann)
     const double2 *nrm;      // [n] source normals (sorted order), kDip only
     int sorted_out;          // phi, gx, gy in sorted order instead (outputs an internal pass reads)
@@ -1620,112 +1616,241 @@ __device__ __forceinline__ XcdChunks xcd_chunks(int64_t nch) {
     return r;
 }
 
-// Near field, log terms of the U list: one thread per target (sorted order; workgroups take chunks
-// of blockDim targets by xcd_chunks).  NV charge vectors share each pair's kernel value.  The
-// thread loads each source point (and the next U entry's range) one step ahead of its use, so that
-// the memory latency overlaps the arithmetic; free-space and image terms go into one signed sum,
-// (1/4 pi) sum_j q_j (log r_img^2 - log r^2).
+// Near field, log terms of the U list.  A wave takes a record: up to 64 targets of one leaf and the
+// leaf's source stream (the sorted indices of all its U points: the leaf's own, the other free ones,
+// the images).  IA = 1, 2, .. 16 lane groups hold up to kNearTargets targets each in registers, and
+// the JG = 64 / IA lanes of a group take every JG-th source of the stream, so that a source is loaded
+// once for all targets of a lane and the lanes have no list to walk; the stream index runs two steps
+// ahead and the point and charges one step ahead of their use.  The JG partial sums of a target meet
+// by exchanging halves of the lane's targets.  NV charge vectors share each pair's kernel value; the
+// lanes and the order of the sums are the same for every NV, so a vector's result does not depend on
+// the pass.  Only the leaf's own points can coincide with a target, so the potential passes mask
+// r^2 = 0 in the steps that hold them alone.
+//
+// What bounds it: FP64 issue (19 VALU instructions per evaluated pair, ~77% of them on real pairs:
+// partly filled lanes at the end of a stream and of a leaf) and, at two waves per SIMD, the latency of
+// the loads.  It replaced a thread per target walking the U list entry by entry (38 instructions per
+// pair, lanes of a wave waiting for the longest leaf).  Alone on the GPU at 1M uniform points, leaf 32:
+// one vector 272 -> 190 us; eight vectors on a 2M forest 1,155 -> 1,005 us; potential and gradient of
+// three vectors at 1M 468 -> 360 us; the 4M curve in walk 2's grid 1,980 -> 1,130 us.  Four targets per
+// lane measured better than eight (72 -> 60 M instructions at 1M): the smaller step leaves fewer lanes
+// idle at a stream's end.
+constexpr int kNearTargets = 4;  // targets per lane at most
+constexpr int kNearPad = 192;    // stream entries read (and not used) past a segment's end: 3 JG at most
+struct NearRec {
+    int32_t ft, nt;      // first target, targets (at most 64)
+    int32_t nself, nfree, nimg, pad;  // points of the leaf, free ones in all, image ones
+    int64_t off;         // first entry of the stream
+};
+
+struct NearArgs {
+    int64_t n;
+    int nrec;
+    const NearRec *rec;
+    const int32_t *stream;
+    const double2 *xy, *nrm, *logtab;
+    const double *qs;
+    double isg;
+    double2 *near;
+    cplx *near_gx, *near_gy;
+    double *qc;
+};
+
+// Sum over the lanes that share the low bits of off0 (off0 = IA): lane bits off0, 2 off0, ... 32.  The
+// first steps halve the lane's targets: a lane ends with the sum of one target, given by its bits, in
+// R[0].
+template <int T2>
+__device__ __forceinline__ void near_reduce(double (&R)[T2], int lane, int off0) {
+    int off = off0;
+#pragma unroll
+    for (int h = T2 / 2; h >= 1; h >>= 1) {
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int k = 0; k < h; ++k) {
+            const double give = up ? R[k] : R[k + h], keep = up ? R[k + h] : R[k];
+            R[k] = keep + __shfl_xor(give, off);
+        }
+        off <<= 1;
+    }
+    for (; off < 64; off <<= 1) R[0] += __shfl_xor(R[0], off);
+}
+
+// A lane's targets and their sums.
+template <int MODE, int NV, int TI>
+struct NearSums {
+    static constexpr int T2 = TI <= 1 ? 1 : TI <= 2 ? 2 : 4;
+    double tx[TI], ty[TI];
+    double acc[has_phi(MODE) ? NV : 1][T2], gx[has_grad(MODE) ? NV : 1][T2], gy[has_grad(MODE) ? NV : 1][T2], qc[T2];
+};
+
+// One segment of a stream: len sources of one sign, of which the first nmask may coincide with a target.
+template <int MODE, int NV, int TI, bool IMG>
+__device__ __forceinline__ void near_segment(NearSums<MODE, NV, TI> &S, const NearArgs &a,
+                                             const double2 *__restrict__ tab, const int32_t *__restrict__ st, int JG,
+                                             int jg, int nmask, int len) {
+    constexpr bool PHI = has_phi(MODE), GRAD = has_grad(MODE), DIP = is_dip(MODE);
+    const double2 *__restrict__ xy = a.xy;
+    const double *__restrict__ qs = a.qs;
+    st += jg;
+    uint32_t j = st[0], jn = st[JG];
+    double2 P = xy[j], N = DIP ? a.nrm[j] : make_double2(0.0, 0.0);
+    double q[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) q[v] = qs[(int64_t)j * NV + v];
+    st += 2 * JG;
+    // one source per lane; checked: the step holds sources that may coincide or lanes past the end
+    auto step = [&](int p0, auto checked) {
+        constexpr bool CHK = decltype(checked)::value;
+        constexpr bool MASK = CHK || GRAD || DIP;
+        const double sx = P.x, sy = IMG ? -P.y : P.y, nx = N.x, ny = IMG ? -N.y : N.y;
+        // image terms enter with isg = +-1, free ones with -1 (the negated multiply-adds below)
+        const bool in = !CHK || p0 + jg < len;
+        double w[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) w[v] = in ? (IMG ? -a.isg * q[v] : q[v]) : 0.0;
+        const double q0 = GRAD && in ? q[0] : 0.0;
+        j = jn;
+        jn = *st;
+        st += JG;
+        P = xy[j];
+        if (DIP) N = a.nrm[j];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) q[v] = qs[(int64_t)j * NV + v];
+#pragma unroll
+        for (int k = 0; k < TI; ++k) {
+            const double dx = S.tx[k] - sx, dy = S.ty[k] - sy;
+            const double r2 = fma(dx, dx, dy * dy);
+            // r2 = 0 only for a coincident free pair, skipped (eq. (1.2)), or between two target-only
+            // points on y = 0 (no charge); image distances to sources are positive
+            const bool nz = !MASK || r2 > 0.0;
+            const double ir = (GRAD || DIP) ? rcp_pos(nz ? r2 : 1.0) : 0.0;
+            if (DIP) {
+                const double kv = nz ? ir * fma(nx, dx, ny * dy) : 0.0;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) S.acc[v][k] = fma(w[v], kv, S.acc[v][k]);
+            } else if (PHI) {
+                const double lg = log_tab(r2, tab);  // finite for r2 = 0, masked
+                const double kv = nz ? lg : 0.0;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) S.acc[v][k] = fma(-w[v], kv, S.acc[v][k]);
+            }
+            if (GRAD) {
+                const double irx = nz ? ir * dx : 0.0, iry = nz ? ir * dy : 0.0;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    S.gx[v][k] = fma(-w[v], irx, S.gx[v][k]);
+                    S.gy[v][k] = fma(-w[v], iry, S.gy[v][k]);
+                }
+                if (!IMG) S.qc[k] += nz ? 0.0 : q0;
+            }
+        }
+    };
+    int p0 = 0;
+    for (; p0 < nmask; p0 += JG) step(p0, std::true_type{});
+    for (; p0 + JG <= len; p0 += JG) step(p0, std::false_type{});
+    if (p0 < len) step(p0, std::true_type{});
+}
+
+// A record with TI targets per lane (compile-time, so that a step's evaluations are straight-line
+// code whose table loads issue together).
+template <int MODE, int NV, int TI>
+__device__ __forceinline__ void near_record(const NearArgs &a, const double2 *__restrict__ tab, int lane,
+                                            const NearRec &rc, int IA) {
+    constexpr int T2 = NearSums<MODE, NV, TI>::T2;
+    constexpr bool PHI = has_phi(MODE), GRAD = has_grad(MODE), DIP = is_dip(MODE);
+    const int32_t *__restrict__ st = a.stream + rc.off;
+    const int JG = 64 / IA, ig = lane & (IA - 1), jg = lane / IA;
+    NearSums<MODE, NV, TI> S;
+#pragma unroll
+    for (int k = 0; k < TI; ++k) {
+        const int i = ig + IA * k;
+        const double2 P = a.xy[rc.ft + (i < rc.nt ? i : 0)];
+        S.tx[k] = P.x;
+        S.ty[k] = P.y;
+    }
+#pragma unroll
+    for (int k = 0; k < T2; ++k) {
+        S.qc[k] = 0.0;
+        for (int v = 0; v < NV; ++v) {
+            if (PHI) S.acc[v][k] = 0.0;
+            if (GRAD) S.gx[v][k] = S.gy[v][k] = 0.0;
+        }
+    }
+    near_segment<MODE, NV, TI, false>(S, a, tab, st, JG, jg, rc.nself, rc.nfree);
+    if (rc.nimg > 0) near_segment<MODE, NV, TI, true>(S, a, tab, st + rc.nfree, JG, jg, 0, rc.nimg);
+    // the lane's target after the reduction, and the one lane of its group that writes it
+    int k = 0, off = IA;
+#pragma unroll
+    for (int h = T2 / 2; h >= 1; h >>= 1, off <<= 1) k += (lane & off) ? h : 0;
+    const int i = ig + IA * k;
+    const bool wr = (lane & ~(off - 1)) == 0 && k < TI && i < rc.nt;
+    const int64_t o = rc.ft + i;
+    if (PHI) {
+        constexpr double kc = DIP ? kInv2Pi : kInv4Pi;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            near_reduce<T2>(S.acc[v], lane, IA);
+            if (wr) a.near[(int64_t)v * a.n + o] = make_double2(kc * S.acc[v][0], 0.0);
+        }
+    }
+    if (GRAD) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            near_reduce<T2>(S.gx[v], lane, IA);
+            near_reduce<T2>(S.gy[v], lane, IA);
+            if (wr) {
+                a.near_gx[(int64_t)v * a.n + o] = mk(kInv2Pi * S.gx[v][0], 0.0);
+                a.near_gy[(int64_t)v * a.n + o] = mk(kInv2Pi * S.gy[v][0], 0.0);
+            }
+        }
+        if (a.qc) {
+            near_reduce<T2>(S.qc, lane, IA);
+            if (wr) a.qc[o] = S.qc[0];
+        }
+    }
+}
+
 template <int MODE, int NV>
-__global__ __launch_bounds__(256) void k_near(LeafArgs a) {
+__global__ __launch_bounds__(256) void k_near(NearArgs a) {
     __shared__ double2 s_logtab[kLogTable];
-    if (has_phi(MODE)) {
+    if (has_phi(MODE) && !is_dip(MODE)) {
         for (int k = threadIdx.x; k < kLogTable; k += blockDim.x) s_logtab[k] = a.logtab[k];
         __syncthreads();
     }
-    const double2 *__restrict__ xy = a.xy;
-    const double2 *__restrict__ tab = s_logtab;
-    const double *__restrict__ qs = a.qs;
-    const int2 *__restrict__ u2 = a.u2;
-    const XcdChunks ch = xcd_chunks((a.n + blockDim.x - 1) / blockDim.x);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const XcdChunks ch = xcd_chunks((a.nrec + 3) / 4);  // four records (one per wave) per chunk
     for (int64_t c = ch.c0; c < ch.c1; c += ch.step) {
-        const int64_t i = c * blockDim.x + threadIdx.x;
-        if (i >= a.n) break;
-        const int b = a.leaf_of[i];
-        const double2 pi = a.xy[i];
-        const double x = pi.x, y = pi.y;
-        double acc[NV], gxa[NV], gya[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] = gxa[v] = gya[v] = 0.0;
-        double qc = 0.0;  // coincident charge of vector 0
-        // a leaf's U list holds at least the leaf itself, and every listed box holds a point
-        int e = a.uoff[b];
-        const int e1 = a.uoff[b + 1];
-        int2 fc = u2[e];
-        int2 fn = e + 1 < e1 ? u2[e + 1] : fc;  // range of entry e + 1
-        double2 pj = xy[fc.x];
-        double2 nj = is_dip(MODE) ? a.nrm[fc.x] : make_double2(0.0, 0.0);
-        double qj[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) qj[v] = qs[(int64_t)fc.x * NV + v];
-        while (true) {
-            const int j0 = fc.x, jend = fc.x + (fc.y & 0x7fffffff);
-            const double ysg = fc.y < 0 ? 1.0 : -1.0;   // image: y + y', free: y - y'
-            const double sg = fc.y < 0 ? a.isg : -1.0;  // image: +-log|r - r_img|, free: - log|r - r'|
-            const bool last = e + 1 >= e1;
-            const int jnext = last ? jend - 1 : fn.x;  // the point loaded after this entry's last
-            double ea[NV];  // this entry's sum, its sign applied once after the loop
-#pragma unroll
-            for (int v = 0; v < NV; ++v) ea[v] = 0.0;
-#pragma unroll 2
-            for (int j = j0; j < jend; ++j) {
-                const int jp = j + 1 < jend ? j + 1 : jnext;
-                const double2 pn = xy[jp];
-                const double2 nn = is_dip(MODE) ? a.nrm[jp] : make_double2(0.0, 0.0);
-                double qn[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) qn[v] = qs[(int64_t)jp * NV + v];
-                const double dx = x - pj.x, dy = fma(ysg, pj.y, y);  // y - y' or y + y'
-                const double r2 = fma(dx, dx, dy * dy);
-                // r2 = 0 only for a coincident free pair, skipped (eq. (1.2)), or between two
-                // target-only points on y = 0 (no charge); image distances to sources are positive
-                const bool nz = r2 > 0.0;
-                if (is_dip(MODE)) {
-                    const double kv = nz ? rcp_pos(nz ? r2 : 1.0) * fma(ysg * nj.y, dy, -nj.x * dx) : 0.0;
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) ea[v] = fma(qj[v], kv, ea[v]);
-                } else if (has_phi(MODE)) {
-                    const double lg = log_tab(r2, tab);  // finite for r2 = 0, masked below
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) ea[v] = fma(qj[v], nz ? lg : 0.0, ea[v]);
-                }
-                if (has_grad(MODE)) {
-                    const double sr = sg * rcp_pos(nz ? r2 : 1.0);
-                    const double irx = nz ? sr * dx : 0.0, iry = nz ? sr * dy : 0.0;
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        gxa[v] = fma(qj[v], irx, gxa[v]);
-                        gya[v] = fma(qj[v], iry, gya[v]);
-                    }
-                    qc += nz ? 0.0 : qj[0];
-                }
-                pj = pn;
-                nj = nn;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) qj[v] = qn[v];
-            }
-            if (has_phi(MODE)) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) acc[v] = fma(sg, ea[v], acc[v]);
-            }
-            if (last) break;
-            ++e;
-            fc = fn;
-            if (e + 1 < e1) fn = u2[e + 1];
-        }
-        if (has_phi(MODE)) {
-            constexpr double kc = is_dip(MODE) ? kInv2Pi : kInv4Pi;
-#pragma unroll
-            for (int v = 0; v < NV; ++v) a.near[(int64_t)v * a.n + i] = make_double2(kc * acc[v], 0.0);
-        }
-        if (has_grad(MODE)) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                a.near_gx[(int64_t)v * a.n + i] = mk(kInv2Pi * gxa[v], 0.0);
-                a.near_gy[(int64_t)v * a.n + i] = mk(kInv2Pi * gya[v], 0.0);
-            }
-            if (a.qc) a.qc[i] = qc;
+        const int ri = (int)(c * 4 + wave);
+        if (ri >= a.nrec) break;
+        const NearRec rc = a.rec[ri];
+        const int IA = rc.nt <= 4 ? 1 : rc.nt <= 8 ? 2 : rc.nt <= 16 ? 4 : rc.nt <= 32 ? 8 : 16;
+        switch ((rc.nt + IA - 1) / IA) {  // targets of lane group 0 (the others hold as many or one fewer)
+        case 1: near_record<MODE, NV, 1>(a, s_logtab, lane, rc, IA); break;
+        case 2: near_record<MODE, NV, 2>(a, s_logtab, lane, rc, IA); break;
+        case 3: near_record<MODE, NV, 3>(a, s_logtab, lane, rc, IA); break;
+        default: near_record<MODE, NV, 4>(a, s_logtab, lane, rc, IA); break;
         }
     }
+}
+
+// The source streams of the leaves, a wave per leaf: its own points, the other free U entries' in list
+// order, the image ones'.
+__global__ __launch_bounds__(64) void k_near_stream(const int32_t *__restrict__ leaves, const int64_t *__restrict__ off,
+                                                    const int32_t *__restrict__ uoff, const int32_t *__restrict__ uent,
+                                                    const int32_t *__restrict__ first,
+                                                    const int32_t *__restrict__ count, int32_t *__restrict__ stream) {
+    const int b = leaves[blockIdx.x];
+    int32_t *out = stream + off[blockIdx.x];
+    for (int t = threadIdx.x; t < count[b]; t += 64) out[t] = first[b] + t;
+    out += count[b];
+    for (int img = 0; img < 2; ++img)
+        for (int e = uoff[b]; e < uoff[b + 1]; ++e) {
+            const int code = uent[e], c = code >> 1, m = count[c], f = first[c];
+            if ((code & 1) != img || code == 2 * b) continue;
+            for (int t = threadIdx.x; t < m; t += 64) out[t] = f + t;
+            out += m;
+        }
 }
 
 // Near field, log terms, symmetric leaf-pair walk (near_walk 3; potential only).  The log kernel of
@@ -2043,109 +2168,6 @@ __global__ __launch_bounds__(256) void k_near_gather(int64_t n, const int32_t *_
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) near[(int64_t)v * n + i].x += kInv4Pi * sv[v];
-}
-
-// The same sums with a plain walk: the U list entry by entry, a source point loaded where it is
-// used (fewer instructions per pair; the memory latency is hidden by other waves only), free-space
-// and image terms in separate sums.
-template <int MODE, int NV>
-__global__ __launch_bounds__(256) void k_near_plain(LeafArgs a) {
-    __shared__ double2 s_logtab[kLogTable];
-    if (has_phi(MODE)) {
-        for (int k = threadIdx.x; k < kLogTable; k += blockDim.x) s_logtab[k] = a.logtab[k];
-        __syncthreads();
-    }
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int b = a.leaf_of[i];
-        const double2 pi = a.xy[i];
-        const double x = pi.x, y = pi.y;
-        double lfree[NV], limg[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) lfree[v] = limg[v] = 0.0;
-        double fx[NV], fy[NV], mx[NV], my[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) fx[v] = fy[v] = mx[v] = my[v] = 0.0;
-        double qc = 0.0;  // coincident charge of vector 0
-        const double2 *__restrict__ xy = a.xy;
-        const double2 *__restrict__ tab = s_logtab;
-        const double *__restrict__ qs = a.qs;
-        for (int e = a.uoff[b]; e < a.uoff[b + 1]; ++e) {
-            const int code = a.uent[e];
-            const int c = code >> 1;
-            const int j0 = a.first[c], j1 = j0 + a.count[c];
-            if (!(code & 1)) {
-                for (int j = j0; j < j1; ++j) {
-                    const double2 pj = xy[j];
-                    const double dx = x - pj.x, dy = y - pj.y;
-                    const double r2 = fma(dx, dx, dy * dy);
-                    const bool nz = r2 > 0.0;  // skip the self pair (eq. (1.2))
-                    if (is_dip(MODE)) {
-                        const double2 nj = a.nrm[j];
-                        const double kv = nz ? -rcp_pos(nz ? r2 : 1.0) * fma(nj.x, dx, nj.y * dy) : 0.0;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) lfree[v] = fma(qs[(int64_t)j * NV + v], kv, lfree[v]);
-                    } else if (has_phi(MODE)) {
-                        const double lg = nz ? log_tab(nz ? r2 : 1.0, tab) : 0.0;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) lfree[v] = fma(qs[(int64_t)j * NV + v], lg, lfree[v]);
-                    }
-                    if (has_grad(MODE)) {
-                        const double ir = nz ? rcp_pos(nz ? r2 : 1.0) : 0.0;
-                        const double irx = ir * dx, iry = ir * dy;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            const double qj = qs[(int64_t)j * NV + v];
-                            fx[v] = fma(qj, irx, fx[v]);
-                            fy[v] = fma(qj, iry, fy[v]);
-                        }
-                        qc += nz ? 0.0 : qs[(int64_t)j * NV];
-                    }
-                }
-            } else {
-                for (int j = j0; j < j1; ++j) {
-                    const double2 pj = xy[j];
-                    const double dx = x - pj.x, dy = y + pj.y;
-                    const double r2 = fma(dx, dx, dy * dy);
-                    // r2 = 0 only between two target-only points on y = 0 (no charge): skipped
-                    const bool nz = r2 > 0.0;
-                    if (is_dip(MODE)) {
-                        const double2 nj = a.nrm[j];
-                        const double kv = nz ? rcp_pos(nz ? r2 : 1.0) * fma(nj.y, dy, -nj.x * dx) : 0.0;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) limg[v] = fma(qs[(int64_t)j * NV + v], kv, limg[v]);
-                    } else if (has_phi(MODE)) {
-                        const double lg = nz ? log_tab(nz ? r2 : 1.0, tab) : 0.0;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) limg[v] = fma(qs[(int64_t)j * NV + v], lg, limg[v]);
-                    }
-                    if (has_grad(MODE)) {
-                        const double ir = nz ? rcp_pos(nz ? r2 : 1.0) : 0.0;
-                        const double irx = ir * dx, iry = ir * dy;
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            const double qj = qs[(int64_t)j * NV + v];
-                            mx[v] = fma(qj, irx, mx[v]);
-                            my[v] = fma(qj, iry, my[v]);
-                        }
-                    }
-                }
-            }
-        }
-        if (has_phi(MODE)) {
-            constexpr double kc = is_dip(MODE) ? kInv2Pi : kInv4Pi;
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                a.near[(int64_t)v * a.n + i] = make_double2(kc * (a.isg * limg[v] - lfree[v]), 0.0);
-        }
-        if (has_grad(MODE)) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                a.near_gx[(int64_t)v * a.n + i] = mk(kInv2Pi * (a.isg * mx[v] - fx[v]), 0.0);
-                a.near_gy[(int64_t)v * a.n + i] = mk(kInv2Pi * (a.isg * my[v] - fy[v]), 0.0);
-            }
-            if (a.qc) a.qc[i] = qc;
-        }
-    }
 }
 
 // L2P of the local(s), plus the near-field sums and the surface term; writes caller order (sorted
@@ -3445,12 +3467,35 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         FMMHP_CHECK(to_dev(A, &S.logtab, lt, "log table", s));
     }
     FMMHP_CHECK(to_dev(A, &S.E_l2l, El, "E_l2l", s));
-    // point range of every U entry's source box, for the near-field walk
-    if (T.len[0] > 0) {
-        FMMHP_CHECK(A.alloc_n(&S.u2, (size_t)T.len[0], "U entry ranges"));
-        hipLaunchKernelGGL(k_u2, dim3(nblk(T.len[0], 256)), dim3(256), 0, s, (int64_t)T.len[0], T.ent[0], T.first,
-                           T.count, S.u2);
+    // near-field records and source streams
+    {
+        std::vector<NearRec> rec;
+        std::vector<int64_t> soff;
+        std::vector<int32_t> first;
+        FMMHP_CHECK(to_host(first, T.first, (size_t)nbox, s));
+        FMMHP_HIP(hipStreamSynchronize(s));
+        int64_t tot = 0;
+        for (int b : lv) {
+            int64_t len[2] = {0, 0};
+            for (int e = uoff[b]; e < uoff[b + 1]; ++e) len[uent[e] & 1] += cnt[uent[e] >> 1];
+            for (int t0 = 0; t0 < cnt[b]; t0 += 64)
+                rec.push_back(NearRec{first[b] + t0, std::min(64, cnt[b] - t0), cnt[b], (int32_t)len[0],
+                                      (int32_t)len[1], 0, tot});
+            soff.push_back(tot);
+            tot += len[0] + len[1];
+        }
+        S.near_nrec = (int)rec.size();
+        NearRec *d_rec = nullptr;
+        int64_t *d_off = nullptr;
+        FMMHP_CHECK(to_dev(A, &d_rec, rec, "near-field records", s));
+        S.near_rec = d_rec;
+        FMMHP_CHECK(to_dev(A, &d_off, soff, "near-field stream offsets", s));
+        FMMHP_CHECK(A.alloc_n(&S.near_stream, (size_t)tot + kNearPad, "near-field source streams"));
+        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(kNearPad), 0, s, S.near_stream + tot, (int64_t)kNearPad);
+        hipLaunchKernelGGL(k_near_stream, dim3((unsigned)T.nleaf), dim3(64), 0, s, S.leaves, d_off, T.off[0], T.ent[0],
+                           T.first, T.count, S.near_stream);
         FMMHP_HIP(hipGetLastError());
+        FMMHP_HIP(hipStreamSynchronize(s));  // the uploads read local vectors
     }
 
     // surface-term chunks: at most kSurfChunk points, within one instance
@@ -3562,10 +3607,9 @@ static fmmhp_status build_sym_walk(Arena &A, const Tree &T, Sched &S, hipStream_
     return FMMHP_OK;
 }
 
-// Launch shape of the near field.  walk: 1 = sources loaded one step ahead, 2 = plain walk;
-// groups: workgroups per CU of its bounded grid.  0 selects the default: the prefetching walk on
-// two workgroups per CU, or for p >= 30 (far-field kernels heavy enough that the near field's
-// instruction count matters more than its latency) the plain walk on four.
+// Launch shape of the near field.  walk: 1, 2 = records (k_near), 3, 4 = symmetric leaf pairs; groups:
+// workgroups per CU of its bounded grid.  0 selects the default: two, or for p >= 30 (a heavier far
+// field, whose kernels leave more waves free) four.
 fmmhp_status apply_launch_shape(Arena &A, const Tree &T, Sched &S, int walk, int groups, hipStream_t s) {
     if (walk == 0) walk = S.PB >= 30 ? 2 : 1;
     if (groups == 0) groups = walk == 2 ? 4 : 2;
@@ -3657,7 +3701,7 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
                 T.off[0],    T.ent[0],  T.off[2], T.ent[2], ws.W,      ws.Lam,    S.invfact, S.fact,
                 S.bc == 0 ? ws.rank1 : nullptr,
                 S.wpts,      S.n_wpts,  S.rpts,   S.logtab, ws.near,   S.bw.near_gx, S.bw.near_gy, out.qc,
-                out.phi,     out.gx,    out.gy,   S.u2,     S.bc == 2 ? -1.0 : 1.0, S.nrm,
+                out.phi,     out.gx,    out.gy,   S.bc == 2 ? -1.0 : 1.0, S.nrm,
                 out.sorted ? 1 : 0};
     FMMHP_HIP(hipEventRecord(S.ev_fork, s));
     FMMHP_HIP(hipStreamWaitEvent(side_, S.ev_fork, 0));
@@ -3669,7 +3713,9 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     constexpr bool heavy_near = MODE != kPhi;
     const int64_t near_blocks = heavy_near ? std::max<int64_t>(S.near_blocks, (int64_t)kNearHeavyGroups * S.cus)
                                            : S.near_blocks;
-    const dim3 near_grid((unsigned)std::min<int64_t>(nblk(T.n, 256), near_blocks));
+    const dim3 near_grid((unsigned)std::min<int64_t>(nblk(S.near_nrec, 4), near_blocks));
+    const NearArgs na{T.n,     S.near_nrec, (const NearRec *)S.near_rec, S.near_stream, S.xy,         S.nrm, S.logtab,
+                      ws.qs,   S.bc == 2 ? -1.0 : 1.0, ws.near, S.bw.near_gx, S.bw.near_gy, out.qc};
     // walk 4 keeps each lane's targets and row sums in registers: single-vector passes only (the
     // others take walk 1)
     const bool sym_walk = MODE == kPhi && S.sym_ok && ws.part && (S.near_walk == 3 || (S.near_walk == 4 && NV == 1));
@@ -3690,10 +3736,8 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
                                T.leaf_of, T.first, S.sym_in_off, S.sym_in, ws.part, ws.near);
         }
     }
-    if (!sym_walk && S.near_walk == 2)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_near_plain<MODE, NV>), near_grid, dim3(256), 0, side_, la);
-    else if (!sym_walk)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_near<MODE, NV>), near_grid, dim3(256), 0, side_, la);
+    if (!sym_walk)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_near<MODE, NV>), near_grid, dim3(256), 0, side_, na);
     if (S.n_rpts > 0 && S.bc == 0)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_near_reaction<MODE, NV>), dim3((unsigned)S.n_rpts), dim3(64), 0,
                            side_, la);
@@ -3809,11 +3853,9 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
         if (ld > 0 && l == lf) FMMHP_CHECK(fork_deep());
     }
     FMMHP_HIP(hipGetLastError());
-    // the W list (M2P) needs every multipole and adds into the near-field sums.  With the plain
-    // near-field walk (chosen when the far field dominates, so the near-field stream has slack) it
-    // runs on that stream once the upward pass is done; otherwise on the main stream before k_leaf.
-    const bool w_side = S.n_wpts > 0 && S.near_walk == 2;
-    if (w_side) {
+    // the W list (M2P) needs every multipole and adds into the near-field sums: on the near-field stream
+    // once the upward pass is done, beside the M2L and the downward pass
+    if (S.n_wpts > 0) {
         FMMHP_HIP(hipEventRecord(S.ev_up, s));
         FMMHP_HIP(hipStreamWaitEvent(side_, S.ev_up, 0));
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_leaf_w<PB, LM, NV>), dim3(nblk(S.n_wpts, 128)), dim3(128), 0, side_,
@@ -3877,8 +3919,6 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     }
     FMMHP_HIP(hipStreamWaitEvent(s, S.ev_join, 0));
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_LEAF, s));
-    if (S.n_wpts > 0 && !w_side)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_leaf_w<PB, LM, NV>), dim3(nblk(S.n_wpts, 128)), dim3(128), 0, s, la);
     // dipoles differ from charges only in the source terms: the L2P and M2P kernels are the potential's
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_leaf<PB, LM>), dim3(nblk(T.n, 256), NV), dim3(256), 0, s, la);
     FMMHP_HIP(hipGetLastError());

@@ -183,7 +183,9 @@ struct Sched {
     int32_t *wpts = nullptr;        // sorted points whose leaf has a W list
     int64_t n_rpts = 0;
     int32_t *rpts = nullptr;        // sorted points whose leaf has image U entries
-    int2 *u2 = nullptr;             // [U entries] (first point, count | image << 31) of the source box
+    int near_nrec = 0;              // near-field records (a leaf's targets, 64 at most) and, per leaf, the
+    void *near_rec = nullptr;       // sorted indices of its U points (its own, the other free ones, the images)
+    int32_t *near_stream = nullptr;
     double2 *xy = nullptr;          // [n] sorted (x, y) pairs
     double2 *logtab = nullptr;      // near-field log table
     hipStream_t side = nullptr;     // side stream for the near field (default priority)
@@ -192,7 +194,7 @@ struct Sched {
     int deep_level = 0;             // first level of the deep M2L part (0: no split)
     std::vector<int> tile_lev, ibox_lev;  // per-level ranges of tiles and image-V boxes
     int cus = 1;                    // compute units of the device
-    int near_walk = 1;              // near-field walk: 1 prefetching, 2 plain, 3 symmetric leaf pairs
+    int near_walk = 1;              // near-field walk: 1, 2 records, 3, 4 symmetric leaf pairs
     // symmetric leaf-pair walk (potential passes): leaves with a U list, their jobs, gather lists
     bool sym_ok = false;
     bool sym_built = false;  // the symmetric walks' schedule has been built (on first use)

@@ -75,28 +75,27 @@ __device__ __forceinline__ double log_pos(double x) {
 }
 
 // Table-assisted natural logarithm of a positive finite double (the near-field pair loop).
-// x = 2^e m, m in [1, 2); the top 9 bits of the mantissa select c_k = 1 + (k + 1/2)/512, and
+// x = 2^e m, m in [1/2, 1) (both from the hardware's frexp instructions, which run at the rate of an
+// addition); the top 9 bits below the leading one select c_k = (1 + (k + 1/2)/512) / 2, and
 // log x = e ln 2 + L_k + log1p(t),  t = m r_k - 1,  r_k = fl(1/c_k),  L_k = -log(r_k),
 // with |t| <= 2^-10, so that log1p(t) = t - t^2/2 + t^3/3 leaves an error below t^4/4 <= 2^-42
 // (2.3e-13, absolute) and e ln 2 in one rounding adds at most |e| 2^-54: a pair's log term is
 // good to ~2.5e-13, which moves a potential built from ~150 such terms by ~1e-12 at most, four
 // orders below the 1e-10 accuracy target.  The table entries (r_k, L_k) are built on the host by
-// log_table_entry.  For x = +0 the result is finite (about -709), so a caller may evaluate it
+// log_table_entry.  For x = +0 the result is finite (frexp gives 0 and 0), so a caller may evaluate it
 // unconditionally and mask the result.
 constexpr int kLogTable = 512;
 
 inline void log_table_entry(int k, double *r, double *L) {
-    const double c = 1.0 + (k + 0.5) / kLogTable;
+    const double c = 0.5 * (1.0 + (k + 0.5) / kLogTable);
     *r = 1.0 / c;
     *L = -log(*r);
 }
 
 __device__ __forceinline__ double log_tab(double x, const double2 *__restrict__ tab) {
-    // exponent and mantissa bits (x > 0, normal)
-    const unsigned long long u = __double_as_longlong(x);
-    const int e = (int)(u >> 52) - 1023;
-    const int k = (int)((u >> 43) & (kLogTable - 1));
-    const double m = __longlong_as_double((u & 0x000fffffffffffffull) | 0x3ff0000000000000ull);
+    const int k = (__double2hiint(x) >> 11) & (kLogTable - 1);
+    const double m = __builtin_amdgcn_frexp_mant(x);
+    const int e = __builtin_amdgcn_frexp_exp(x);
     const double2 rl = tab[k];
     const double t = fma(m, rl.x, -1.0);
     double p = fma(1.0 / 3.0, t, -1.0 / 2.0);
