@@ -49,6 +49,7 @@
 #include "internal.hpp"
 #include "special.hpp"
 #include "m2l_pw.hpp"
+#include "updown.hpp"
 
 namespace fmmhp {
 
@@ -184,228 +185,6 @@ __global__ __launch_bounds__(256) void k_p2m(const InstInfo *__restrict__ ii, co
 #pragma unroll
         for (int n = 0; n <= PB; ++n)
             if (n % kP2MSplit == part) W[(int64_t)n * nbox + b] = w[n];
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// M2M.  (P2M and M2M raise their waves' issue priority: the upward pass is the critical path of
-// an evaluation while the near field and the deep-level M2L run beside it on other streams.)
-// A block takes kM2MParents consecutive boxes of a level; their children are a contiguous
-// range of the next level, whose multipoles are staged in LDS once.  Thread (parent, n) then forms
-// w^P_n = sum_children sum_{m<=n} (-eps)^{n-m}/(n-m)! 2^-m w^c_m.
-// k_m2m runs one level; k_m2m_sub runs every level below a cut level, one block per subtree
-// rooted at the cut (a subtree's boxes of one level are a contiguous range), deepest level first.
-// ---------------------------------------------------------------------------------------------
-constexpr int kM2MParents = 16;
-
-// Coefficient n of a parent's multipole from its children's staged multipoles: children
-// c0 .. c0 + nc - 1, child c's coefficient m (scaled by 2^-m) at sw[m * ld + c], its position in
-// the parent quad[c].  Callers put n in the fastest-varying thread index: the lanes of a wave then
-// read a few children (broadcast) and consecutive shift coefficients (no LDS bank conflicts).
-template <int PB>
-__device__ __forceinline__ cplx m2m_coef(const cplx *sE, const int *quad, const cplx *sw, int ld, int c0, int nc,
-                                         int n) {
-    cplx out = mk(0.0, 0.0);
-    for (int c = c0; c < c0 + nc; ++c) {
-        const cplx *Eq = sE + quad[c] * (PB + 1) + n;
-#pragma unroll 4
-        for (int m = 0; m <= n; ++m) cfma(out, Eq[-m], sw[m * ld + c]);
-    }
-    return out;
-}
-
-// Coefficient m of a child's local from its parent's staged local (coefficient n at sl[n * ld]):
-// sum_{n>=m} Eq[n] sl[n * ld], Eq the child's shift row offset by -m.
-template <int PB>
-__device__ __forceinline__ cplx l2l_coef(const cplx *Eq, const cplx *sl, int ld, int m) {
-    cplx s = mk(0.0, 0.0);
-#pragma unroll 4
-    for (int n = m; n <= PB; ++n) cfma(s, Eq[n], sl[n * ld]);
-    return s;
-}
-
-template <int PB>
-struct M2MShared {
-    cplx sE[4 * (PB + 1)];
-    int2 par[kM2MParents];                // (first staged child, number of children) per parent
-    int quad[4 * kM2MParents];            // position of each staged child in its parent
-    int range[2];
-};
-
-// Parents [p0, p1) of one level (p1 - p0 <= kM2MParents); called by every thread of the block
-// with block-uniform bounds.  The children's multipoles, scaled by 2^-m, are staged in the LDS
-// rows sw (row length ld >= 4 kM2MParents: coefficient m of staged child k at sw[m * ld + k]).
-// Two dependent memory round trips (the parents' child ranges, then the children's multipoles and
-// positions); ends with a barrier, so the multipoles written are visible to the whole block.
-template <int PB>
-__device__ __forceinline__ void m2m_parents(M2MShared<PB> &sh, cplx *sw, int ld, int p0, int p1, int nbox,
-                            const int32_t *__restrict__ leaf,
-                            const int32_t *__restrict__ child_first, const int32_t *__restrict__ nchild,
-                            const int32_t *__restrict__ bx, const int32_t *__restrict__ by,
-                            cplx *__restrict__ W) {
-    static_assert(kM2MParents <= 64, "the child range is reduced over one wave");
-    if (threadIdx.x < 64) {  // child range of the non-leaf parents, reduced over the first wave
-        const int p = p0 + (int)threadIdx.x;
-        int cf = 0, ncp = 0;
-        if (p < p1 && !leaf[p]) {
-            cf = child_first[p];
-            ncp = nchild[p];
-        }
-        int clo = ncp > 0 ? cf : 0x7fffffff, chi = ncp > 0 ? cf + ncp : -1;
-        for (int off = 32; off > 0; off >>= 1) {
-            clo = min(clo, __shfl_xor(clo, off));
-            chi = max(chi, __shfl_xor(chi, off));
-        }
-        if (threadIdx.x < kM2MParents) sh.par[threadIdx.x] = make_int2(cf - clo, ncp);
-        if (threadIdx.x == 0) {
-            sh.range[0] = clo;
-            sh.range[1] = chi;
-        }
-    }
-    __syncthreads();
-    const int clo = sh.range[0], nc = sh.range[1] - sh.range[0];
-    for (int idx = threadIdx.x; idx < (PB + 1) * nc; idx += blockDim.x) {
-        const int m = idx / nc, k = idx - m * nc;
-        sw[m * ld + k] = W[(int64_t)m * nbox + clo + k] * ldexp(1.0, -m);
-    }
-    for (int k = threadIdx.x; k < nc; k += blockDim.x) sh.quad[k] = (bx[clo + k] & 1) | ((by[clo + k] & 1) << 1);
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < (p1 - p0) * (PB + 1); idx += blockDim.x) {
-        const int pi = idx / (PB + 1), n = idx - pi * (PB + 1);
-        const int2 pr = sh.par[pi];
-        if (pr.y > 0) W[(int64_t)n * nbox + p0 + pi] = m2m_coef<PB>(sh.sE, sh.quad, sw, ld, pr.x, pr.y, n);
-    }
-    __syncthreads();
-}
-
-template <int PB>
-__global__ __launch_bounds__(256) void k_m2m(int lo, int nb, int nbox, const int32_t *__restrict__ leaf,
-                                             const int32_t *__restrict__ child_first,
-                                             const int32_t *__restrict__ nchild, const int32_t *__restrict__ bx,
-                                             const int32_t *__restrict__ by, const cplx *__restrict__ E,
-                                             cplx *__restrict__ W) {
-    __builtin_amdgcn_s_setprio(3);  // upward pass: the critical path
-    __shared__ M2MShared<PB> sh;
-    extern __shared__ cplx dyn_lds[];  // (PB + 1) x 4 kM2MParents
-    W += (int64_t)blockIdx.y * (PB + 1) * nbox;  // charge vector
-    for (int k = threadIdx.x; k < 4 * (PB + 1); k += blockDim.x) sh.sE[k] = E[k];
-    const int p0 = lo + blockIdx.x * kM2MParents;
-    m2m_parents<PB>(sh, dyn_lds, 4 * kM2MParents, p0, min(p0 + kM2MParents, lo + nb), nbox, leaf, child_first, nchild,
-                    bx, by, W);
-}
-
-// Subtree passes.  rng: [n_roots][nlev] box ranges (begin, end) of each subtree at the levels
-// cut + k.  The block's dynamic LDS holds ld rows slots (ld >= 4 kM2MParents); a subtree whose
-// expansions fit keeps all of them in LDS between levels (one memory round trip to load them,
-// then LDS only), a larger one runs the chunked one-level code level after level.
-constexpr int kSubMaxLev = 32;
-constexpr int kSubMaxSlots = 256;   // resident slots (the host keeps ld within this)
-
-struct SubShared {
-    int base[kSubMaxLev + 1];        // first resident slot of each level
-    int first[kSubMaxLev];           // first box of each level
-    int slot[kSubMaxSlots];          // leaf: -1; else slot of the first child (M2M) / of the parent (L2L)
-    int nch[kSubMaxSlots];           // number of children (M2M)
-    int quad[kSubMaxSlots];          // position of the box in its parent
-};
-
-// Fills ss.base and ss.first from the subtree's ranges; ends with a barrier.
-__device__ __forceinline__ void sub_ranges(SubShared &ss, const int2 *__restrict__ R, int nlev) {
-    if (threadIdx.x == 0) {
-        int tot = 0;
-        for (int k = 0; k < nlev; ++k) {
-            const int2 r = R[k];
-            ss.base[k] = tot;
-            ss.first[k] = r.x;
-            tot += r.y - r.x;
-        }
-        ss.base[nlev] = tot;
-    }
-    __syncthreads();
-}
-
-// Level of resident slot i.
-__device__ __forceinline__ int sub_level_of(const SubShared &ss, int nlev, int i) {
-    int k = 0;
-    while (k + 1 < nlev && ss.base[k + 1] <= i) ++k;
-    return k;
-}
-
-// M2M of the parents [c.x, c.y) of one level for each chunk c (at most kM2MParents parents): the
-// subtrees too large for LDS, one launch per level, deepest first.
-template <int PB>
-__global__ __launch_bounds__(256) void k_m2m_chunks(const int2 *__restrict__ chunks, int nbox,
-                                                    const int32_t *__restrict__ leaf,
-                                                    const int32_t *__restrict__ child_first,
-                                                    const int32_t *__restrict__ nchild, const int32_t *__restrict__ bx,
-                                                    const int32_t *__restrict__ by, const cplx *__restrict__ E,
-                                                    cplx *__restrict__ W) {
-    __builtin_amdgcn_s_setprio(3);  // upward pass: the critical path
-    __shared__ M2MShared<PB> sh;
-    extern __shared__ cplx dyn_lds[];  // (PB + 1) x 4 kM2MParents
-    W += (int64_t)blockIdx.y * (PB + 1) * nbox;  // charge vector
-    for (int k = threadIdx.x; k < 4 * (PB + 1); k += blockDim.x) sh.sE[k] = E[k];
-    const int2 c = chunks[blockIdx.x];
-    m2m_parents<PB>(sh, dyn_lds, 4 * kM2MParents, c.x, c.y, nbox, leaf, child_first, nchild, bx, by, W);
-}
-
-// skip_big: a subtree whose expansions do not fit the block's LDS rows is left to k_m2m_chunks
-// (otherwise the block runs it level by level itself).
-template <int PB>
-__global__ __launch_bounds__(256) void k_m2m_sub(int nlev, const int2 *__restrict__ rng, int ld, int skip_big, int nbox,
-                                                 const int32_t *__restrict__ leaf,
-                                                 const int32_t *__restrict__ child_first,
-                                                 const int32_t *__restrict__ nchild, const int32_t *__restrict__ bx,
-                                                 const int32_t *__restrict__ by, const cplx *__restrict__ E,
-                                                 cplx *__restrict__ W) {
-    __builtin_amdgcn_s_setprio(3);  // upward pass: the critical path
-    __shared__ M2MShared<PB> sh;
-    __shared__ SubShared ss;
-    extern __shared__ cplx dyn_lds[];  // (PB + 1) x ld: slot i, coefficient m at [m * ld + i]
-    cplx *sw = dyn_lds;
-    W += (int64_t)blockIdx.y * (PB + 1) * nbox;  // charge vector
-    for (int k = threadIdx.x; k < 4 * (PB + 1); k += blockDim.x) sh.sE[k] = E[k];
-    const int2 *R = rng + (int64_t)blockIdx.x * nlev;
-    sub_ranges(ss, R, nlev);
-    const int tot = ss.base[nlev];
-    if (tot > ld) {
-        if (skip_big) return;
-        for (int k = nlev - 2; k >= 0; --k) {
-            const int2 r = R[k];
-            for (int p0 = r.x; p0 < r.y; p0 += kM2MParents)
-                m2m_parents<PB>(sh, sw, ld, p0, min(p0 + kM2MParents, r.y), nbox, leaf, child_first, nchild, bx, by,
-                                W);
-        }
-        return;
-    }
-    // every box's structure and multipole (the non-leaf ones are recomputed below before use),
-    // stored scaled by 2^-m as its parent consumes it
-    for (int i = threadIdx.x; i < tot; i += blockDim.x) {
-        const int k = sub_level_of(ss, nlev, i);
-        const int b = ss.first[k] + (i - ss.base[k]);
-        const int lf = leaf[b];
-        ss.slot[i] = lf ? -1 : ss.base[k + 1] + (child_first[b] - ss.first[k + 1]);
-        ss.nch[i] = lf ? 0 : nchild[b];
-        ss.quad[i] = (bx[b] & 1) | ((by[b] & 1) << 1);
-    }
-    for (int idx = threadIdx.x; idx < tot * (PB + 1); idx += blockDim.x) {
-        const int m = idx / tot, i = idx - m * tot;
-        const int k = sub_level_of(ss, nlev, i);
-        const int b = ss.first[k] + (i - ss.base[k]);
-        sw[m * ld + i] = W[(int64_t)m * nbox + b] * ldexp(1.0, -m);
-    }
-    __syncthreads();
-    for (int k = nlev - 2; k >= 0; --k) {
-        const int i0 = ss.base[k], np = ss.base[k + 1] - i0;
-        for (int idx = threadIdx.x; idx < np * (PB + 1); idx += blockDim.x) {
-            const int ip = idx / (PB + 1), n = idx - ip * (PB + 1), i = i0 + ip;
-            const int c0 = ss.slot[i];
-            if (c0 < 0) continue;
-            const cplx out = m2m_coef<PB>(sh.sE, ss.quad, sw, ld, c0, ss.nch[i], n);
-            W[(int64_t)n * nbox + ss.first[k] + (i - i0)] = out;
-            sw[n * ld + i] = out * ldexp(1.0, -n);
-        }
-        __syncthreads();
     }
 }
 
@@ -1340,143 +1119,6 @@ __global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, con
             }
             __syncthreads();
         }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// L2L.  A block takes kL2LChildren consecutive children and stages each child's parent local in
-// LDS (siblings share cache lines).  Thread (child, m) adds 2^-m sum_{n>=m} eps^{n-m}/(n-m)!
-// lambda^P_n to lambda^c_m.  k_l2l runs one level of children; k_l2l_sub every level below a cut
-// level, one block per subtree rooted at the cut, top level first.
-// ---------------------------------------------------------------------------------------------
-constexpr int kL2LChildren = 64;
-
-template <int PB>
-struct L2LShared {
-    cplx sE[4 * (PB + 1)];
-};
-
-// Children [c0, c0 + nc) of one level, nc <= kL2LChildren; called by every thread of the block.
-// The parents' locals are staged in the LDS rows sl (row length ld >= kL2LChildren).  The
-// children's own locals are read before the parents' are staged, so that both loads overlap.
-// Ends with a barrier, so the locals written are visible to the whole block.
-template <int PB>
-__device__ __forceinline__ void l2l_children(L2LShared<PB> &sh, cplx *sl, int ld, int c0, int nc, int nbox, int nloc,
-                             const int32_t *__restrict__ parent, const int32_t *__restrict__ bx,
-                             const int32_t *__restrict__ by, cplx *__restrict__ Lam) {
-    constexpr int MS = 256 / kL2LChildren;         // threads per child
-    constexpr int MP = (PB + MS) / MS;             // coefficients per thread
-    const int ci = threadIdx.x % kL2LChildren;
-    const int mt = threadIdx.x / kL2LChildren;
-    const int c = c0 + ci;
-    const int q = ci < nc ? ((bx[c] & 1) | ((by[c] & 1) << 1)) : 0;
-    for (int loc = 0; loc < nloc; ++loc) {
-        cplx *L = Lam + (int64_t)loc * (PB + 1) * nbox;
-        cplx own[MP];
-#pragma unroll
-        for (int k = 0; k < MP; ++k) {
-            const int m = mt + k * MS;
-            own[k] = (ci < nc && m <= PB) ? L[(int64_t)m * nbox + c] : mk(0.0, 0.0);
-        }
-        for (int idx = threadIdx.x; idx < (PB + 1) * nc; idx += blockDim.x) {
-            const int n = idx / nc, k = idx - n * nc;
-            sl[n * ld + k] = L[(int64_t)n * nbox + parent[c0 + k]];
-        }
-        __syncthreads();
-        if (ci < nc) {
-#pragma unroll
-            for (int k = 0; k < MP; ++k) {
-                const int m = mt + k * MS;
-                if (m <= PB) {
-                    const cplx s = l2l_coef<PB>(sh.sE + q * (PB + 1) - m, sl + ci, ld, m);
-                    L[(int64_t)m * nbox + c] = own[k] + s * ldexp(1.0, -m);
-                }
-            }
-        }
-        __syncthreads();
-    }
-}
-
-template <int PB>
-__global__ __launch_bounds__(256) void k_l2l(int lo, int nb, int nbox, int nloc, const int32_t *__restrict__ parent,
-                                             const int32_t *__restrict__ bx, const int32_t *__restrict__ by,
-                                             const cplx *__restrict__ E, cplx *__restrict__ Lam) {
-    __shared__ L2LShared<PB> sh;
-    extern __shared__ cplx dyn_lds[];  // (PB + 1) x kL2LChildren
-    Lam += (int64_t)blockIdx.y * nloc * (PB + 1) * nbox;  // charge vector
-    for (int k = threadIdx.x; k < 4 * (PB + 1); k += blockDim.x) sh.sE[k] = E[k];
-    const int c0 = lo + blockIdx.x * kL2LChildren;
-    l2l_children<PB>(sh, dyn_lds, kL2LChildren, c0, min(kL2LChildren, lo + nb - c0), nbox, nloc, parent, bx, by,
-                     Lam);
-}
-
-// L2L of the children [c.x, c.y) of one level for each chunk c (at most kL2LChildren children): the
-// subtrees too large for LDS, one launch per level, top level first.
-template <int PB>
-__global__ __launch_bounds__(256) void k_l2l_chunks(const int2 *__restrict__ chunks, int nbox, int nloc,
-                                                    const int32_t *__restrict__ parent, const int32_t *__restrict__ bx,
-                                                    const int32_t *__restrict__ by, const cplx *__restrict__ E,
-                                                    cplx *__restrict__ Lam) {
-    __shared__ L2LShared<PB> sh;
-    extern __shared__ cplx dyn_lds[];  // (PB + 1) x kL2LChildren
-    Lam += (int64_t)blockIdx.y * nloc * (PB + 1) * nbox;  // charge vector
-    for (int k = threadIdx.x; k < 4 * (PB + 1); k += blockDim.x) sh.sE[k] = E[k];
-    const int2 c = chunks[blockIdx.x];
-    l2l_children<PB>(sh, dyn_lds, kL2LChildren, c.x, c.y - c.x, nbox, nloc, parent, bx, by, Lam);
-}
-
-// skip_big: a subtree whose locals do not fit the block's LDS rows is left to k_l2l_chunks.
-template <int PB>
-__global__ __launch_bounds__(256) void k_l2l_sub(int nlev, const int2 *__restrict__ rng, int ld, int skip_big, int nbox,
-                                                 int nloc,
-                                                 const int32_t *__restrict__ parent, const int32_t *__restrict__ bx,
-                                                 const int32_t *__restrict__ by, const cplx *__restrict__ E,
-                                                 cplx *__restrict__ Lam) {
-    __shared__ L2LShared<PB> sh;
-    __shared__ SubShared ss;
-    extern __shared__ cplx dyn_lds[];  // (PB + 1) x ld
-    cplx *sl = dyn_lds;
-    Lam += (int64_t)blockIdx.y * nloc * (PB + 1) * nbox;  // charge vector
-    for (int k = threadIdx.x; k < 4 * (PB + 1); k += blockDim.x) sh.sE[k] = E[k];
-    const int2 *R = rng + (int64_t)blockIdx.x * nlev;
-    sub_ranges(ss, R, nlev);
-    const int tot = ss.base[nlev];
-    if (tot * nloc > ld) {
-        if (skip_big) return;
-        for (int k = 1; k < nlev; ++k) {
-            const int2 r = R[k];
-            for (int c0 = r.x; c0 < r.y; c0 += kL2LChildren)
-                l2l_children<PB>(sh, sl, ld, c0, min(kL2LChildren, r.y - c0), nbox, nloc, parent, bx, by, Lam);
-        }
-        return;
-    }
-    // resident: slot loc * tot + i holds local loc of box i, coefficient n at sl[n * ld + slot];
-    // the root's local is final (the levels above ran first), the others hold their own M2L/P2L
-    // parts until their level is reached
-    for (int i = threadIdx.x; i < tot; i += blockDim.x) {
-        const int k = sub_level_of(ss, nlev, i);
-        const int b = ss.first[k] + (i - ss.base[k]);
-        ss.slot[i] = k == 0 ? -1 : ss.base[k - 1] + (parent[b] - ss.first[k - 1]);
-        ss.quad[i] = (bx[b] & 1) | ((by[b] & 1) << 1);
-    }
-    for (int idx = threadIdx.x; idx < nloc * tot * (PB + 1); idx += blockDim.x) {
-        const int n = idx / (nloc * tot), r = idx - n * nloc * tot, loc = r / tot, i = r - loc * tot;
-        const int k = sub_level_of(ss, nlev, i);
-        const int b = ss.first[k] + (i - ss.base[k]);
-        sl[n * ld + r] = Lam[((int64_t)loc * (PB + 1) + n) * nbox + b];
-    }
-    __syncthreads();
-    for (int k = 1; k < nlev; ++k) {
-        const int i0 = ss.base[k], nc = ss.base[k + 1] - i0;
-        for (int idx = threadIdx.x; idx < nloc * nc * (PB + 1); idx += blockDim.x) {
-            const int m = idx / (nloc * nc), r = idx - m * nloc * nc, loc = r / nc, i = i0 + (r - loc * nc);
-            const int ps = loc * tot + ss.slot[i], cs = loc * tot + i;
-            const cplx acc = l2l_coef<PB>(sh.sE + ss.quad[i] * (PB + 1) - m, sl + ps, ld, m);
-            const cplx v = sl[m * ld + cs] + acc * ldexp(1.0, -m);
-            sl[m * ld + cs] = v;
-            Lam[((int64_t)loc * (PB + 1) + m) * nbox + ss.first[k] + (i - i0)] = v;
-        }
-        __syncthreads();
     }
 }
 
@@ -2815,10 +2457,96 @@ static fmmhp_status build_pw_tables(Arena &A, Sched &S, const std::vector<cplx> 
     return FMMHP_OK;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Bands of the M2M and L2L passes
+// ---------------------------------------------------------------------------------------------
+// Boxes of every lane at the band's levels: tab[wave][k][lane], k = 0 the deepest; lane = (root of the
+// wave, position below it).
+__global__ void k_band_tab(int nwave, int nlev, int nroot, const int32_t *__restrict__ roots,
+                           const int32_t *__restrict__ leaf, const int32_t *__restrict__ child_first,
+                           const int32_t *__restrict__ nchild, const int32_t *__restrict__ bx,
+                           const int32_t *__restrict__ by, int32_t *__restrict__ tab) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nwave * 64) return;
+    const int wv = i >> 6, lane = i & 63;
+    const int r = (wv << (2 * (3 - nlev))) + (lane >> (2 * nlev));
+    int b = r < nroot ? roots[r] : -1;
+    int32_t *t = tab + (int64_t)wv * (nlev + 1) * 64 + lane;
+    for (int k = nlev; k >= 0; --k) {
+        const bool nl = b >= 0 && !leaf[b];
+        t[k * 64] = b < 0 ? -1 : b | (nl ? kBandNonLeaf : 0);
+        if (k == 0) break;
+        int c = -1;
+        if (nl) {
+            const int q = (lane >> (2 * (k - 1))) & 3;
+            for (int j = child_first[b]; j < child_first[b] + nchild[b]; ++j)
+                if (((bx[j] & 1) | ((by[j] & 1) << 1)) == q) c = j;
+        }
+        b = c;
+    }
+}
+
+// Splits the levels 2 .. depth into bands of at most three levels.  A band of n levels on r roots takes
+// ceil(r / 4^(3 - n)) waves; its cost is a launch, the latency of its n shifts and the issue of its waves
+// on the chip's SIMDs, whichever is longer.
+static fmmhp_status build_bands(Arena &A, const Tree &T, Sched &S, const std::vector<int32_t> &leaf, hipStream_t s) {
+    S.bands.clear();
+    std::vector<int> nonleaf(T.depth + 1, 0);
+    for (int l = 2; l <= T.depth; ++l)
+        for (int b = T.lev_start[l]; b < T.lev_start[l + 1]; ++b) nonleaf[l] += !leaf[b];
+    const int P1 = S.PB + 1;
+    const double shift_us = (P1 * (P1 + 1) + 22.0 * P1) * 4.0 / 2400.0;  // one wave's shift at one issue per 4 cycles
+    const double launch_us = 6.0, simds = 4.0 * S.cus;
+    auto cost = [&](int root, int nlev) {
+        const double waves = std::ceil(nonleaf[root] / std::ldexp(1.0, 2 * (3 - nlev)));
+        return launch_us + 1.5 * nlev * shift_us * std::max(1.0, waves / simds);
+    };
+    std::vector<double> best(T.depth + 4, 0.0);  // best[l]: levels l .. depth, l a root
+    std::vector<int> take(T.depth + 4, 0);
+    for (int l = T.depth - 1; l >= 2; --l) {
+        best[l] = INFINITY;
+        for (int n = 1; n <= 3 && l + n <= T.depth; ++n) {
+            const double c = cost(l, n) + best[l + n];
+            if (c < best[l]) best[l] = c, take[l] = n;
+        }
+    }
+    std::vector<int32_t> roots;
+    int64_t at = 0;
+    for (int l = 2; l < T.depth; l += take[l]) {
+        const int n = take[l];
+        const int nw = (nonleaf[l] + (1 << (2 * (3 - n))) - 1) >> (2 * (3 - n));
+        if (nw > 0) S.bands.push_back(Sched::Band{l, n, nw, at});
+        at += (int64_t)nw * (n + 1) * 64;
+    }
+    if (S.bands.empty()) return FMMHP_OK;
+    FMMHP_CHECK(A.alloc_n(&S.band_tab, (size_t)at, "M2M / L2L bands"));
+    for (const auto &B : S.bands)
+        for (int b = T.lev_start[B.root]; b < T.lev_start[B.root + 1]; ++b)
+            if (!leaf[b]) roots.push_back(b);
+    int32_t *d_roots = nullptr;
+    FMMHP_CHECK(to_dev(A, &d_roots, roots, "band roots", s));
+    int64_t r0 = 0;
+    for (const auto &B : S.bands) {
+        hipLaunchKernelGGL(k_band_tab, dim3(nblk((int64_t)B.nwave * 64, 256)), dim3(256), 0, s, B.nwave, B.nlev,
+                           nonleaf[B.root], d_roots + r0, T.leaf, T.child_first, T.nchild, T.bx, T.by,
+                           S.band_tab + B.tab);
+        r0 += nonleaf[B.root];
+    }
+    FMMHP_HIP(hipGetLastError());
+    FMMHP_HIP(hipStreamSynchronize(s));  // the upload reads a local vector
+    return FMMHP_OK;
+}
+
 static fmmhp_status ensure_vec_ws(Arena &A, const Tree &T, Sched &S, int nv);
 
 fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cplx *Zs, hipStream_t s) {
     S.PB = PB;
+    {
+        int dev = 0, cus = 0;
+        FMMHP_HIP(hipGetDevice(&dev));
+        FMMHP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        S.cus = std::max(1, cus);
+    }
     S.Z = Zs[0];
     S.real_Z = true;
     for (int k = 0; k < T.n_inst; ++k) S.real_Z = S.real_Z && Zs[k].im == 0.0;
@@ -3099,156 +2827,7 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
             }
     }
     FMMHP_CHECK(to_dev(A, &S.leaves, lv, "leaves", s));
-    // subtree passes: below the first level (>= 3) with at least four boxes per CU, one block per
-    // subtree runs all of that subtree's M2M (and later L2L) levels; the levels above run one
-    // launch each.  A subtree's boxes at each level are a contiguous range (boxes are ordered by
-    // level, instance, Morton prefix).
-    S.sub_level = 0;
-    {
-        std::vector<int32_t> cfirst, nch;
-        FMMHP_CHECK(to_host(cfirst, T.child_first, nbox, s));
-        FMMHP_CHECK(to_host(nch, T.nchild, nbox, s));
-        FMMHP_HIP(hipStreamSynchronize(s));
-        int cus = 0, dev = 0;
-        FMMHP_HIP(hipGetDevice(&dev));
-        FMMHP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        // box ranges per level of the subtrees rooted at the boxes of level lr, nlev levels deep;
-        // returns the largest subtree's box count; nonres (if given) gets the number of boxes in
-        // subtrees of more than cap boxes
-        auto subtree_ranges = [&](int lr, int nlev, std::vector<int2> &rng, int cap_, int64_t *nonres) {
-            const int r0 = T.lev_start[lr], nr = T.lev_start[lr + 1] - r0;
-            rng.assign((size_t)nr * nlev, make_int2(0, 0));
-            int maxtot = 0;
-            if (nonres) *nonres = 0;
-            for (int r = 0; r < nr; ++r) {
-                int a = r0 + r, b = a + 1, tot = 0;
-                for (int k = 0; k < nlev && a < b; ++k) {
-                    rng[(size_t)r * nlev + k] = make_int2(a, b);
-                    tot += b - a;
-                    int na = -1, nb = -1;
-                    for (int x = a; x < b; ++x)
-                        if (!leaf[x]) {
-                            if (na < 0) na = cfirst[x];
-                            nb = cfirst[x] + nch[x];
-                        }
-                    if (na < 0) break;
-                    a = na;
-                    b = nb;
-                }
-                maxtot = std::max(maxtot, tot);
-                if (nonres && tot > cap_) *nonres += tot;
-            }
-            return maxtot;
-        };
-        // resident LDS rows: enough for the largest subtree, within 48 KB of expansions per block
-        const int cap = std::min(kSubMaxSlots, (int)(48 * 1024 / ((PB + 1) * sizeof(cplx))));
-        // the cut: the first level (>= 3) with at least four boxes per CU whose subtrees nearly all
-        // fit in LDS (at most 5% of the boxes below the cut in larger ones, which take the slower
-        // level-by-level path inside their block); deep narrow trees with no such level run one
-        // launch per level instead
-        std::vector<int2> rng;
-        int maxtot = 0;
-        // a forest runs one launch per level: its many small subtrees, each set up once per charge
-        // vector, make the subtree blocks slower than the plain level launches there
-        for (int l = 3; l < T.depth && T.n_inst == 1; ++l) {
-            if (T.lev_start[l + 1] - T.lev_start[l] < 4 * std::max(1, cus)) continue;
-            int64_t nonres = 0;
-            const int mt = subtree_ranges(l, T.depth - l + 1, rng, cap, &nonres);
-            if (nonres * 20 <= (int64_t)(T.lev_start[T.depth + 1] - T.lev_start[l])) {
-                S.sub_level = l;
-                maxtot = mt;
-                break;
-            }
-        }
-        // consecutive subtrees whose boxes together fit the LDS rows run in one block: their box
-        // ranges at each level are contiguous (boxes are ordered by level, instance, Morton prefix),
-        // so a group is handled like one subtree with several roots.  Subtrees larger than the rows
-        // stay alone.  Returns the largest group's box count among those that fit.
-        auto group_subtrees = [&](std::vector<int2> &r, int nlev, int lim, int *ngroups) {
-            const int nr = (int)(r.size() / nlev);
-            std::vector<int2> g;
-            int gmax = 0, i = 0;
-            auto size_of = [&](int k) {
-                int t = 0;
-                for (int l = 0; l < nlev; ++l) t += r[(size_t)k * nlev + l].y - r[(size_t)k * nlev + l].x;
-                return t;
-            };
-            while (i < nr) {
-                int tot = size_of(i), j = i + 1;
-                if (tot <= lim)
-                    for (int t; j < nr && (t = size_of(j)) <= lim && tot + t <= lim; ++j) tot += t;
-                for (int l = 0; l < nlev; ++l) {
-                    int a = 0, b = 0;
-                    for (int k = i; k < j; ++k) {
-                        const int2 q = r[(size_t)k * nlev + l];
-                        if (q.y > q.x) {
-                            if (b == 0) a = q.x;
-                            b = q.y;
-                        }
-                    }
-                    g.push_back(make_int2(a, b));
-                }
-                if (tot <= lim) gmax = std::max(gmax, tot);
-                i = j;
-            }
-            r.swap(g);
-            *ngroups = (int)(r.size() / nlev);
-            return gmax;
-        };
-        S.m2m_ch_lev.assign(T.depth + 2, 0);
-        S.l2l_ch_lev.assign(T.depth + 2, 0);
-        if (S.sub_level > 0) {
-            const int lc = S.sub_level;
-            S.sub_nlev = T.depth - lc + 1;
-            maxtot = group_subtrees(rng, S.sub_nlev, cap, &S.n_sub);
-            FMMHP_CHECK(to_dev(A, &S.sub_rng, rng, "subtree ranges", s));
-            S.sub_ld_m2m = std::max(4 * kM2MParents, std::min(maxtot, cap));
-            S.sub_ld_l2l = std::max(kL2LChildren, std::min(maxtot * S.nloc, cap));
-            // the subtrees whose expansions do not fit those rows: their parents (M2M) and children
-            // (L2L) level by level in chunks, so that all of them run in parallel
-            {
-                const int nl = S.sub_nlev;
-                std::vector<std::vector<int2>> mc(T.depth + 1), lcx(T.depth + 1);
-                for (int r = 0; r < S.n_sub; ++r) {
-                    const int2 *R = &rng[(size_t)r * nl];
-                    int tot = 0;
-                    for (int k = 0; k < nl; ++k) tot += R[k].y - R[k].x;
-                    if (tot > S.sub_ld_m2m)
-                        for (int k = 0; k + 1 < nl; ++k)
-                            for (int a0 = R[k].x; a0 < R[k].y; a0 += kM2MParents)
-                                mc[lc + k].push_back(make_int2(a0, std::min(a0 + kM2MParents, R[k].y)));
-                    if (tot * S.nloc > S.sub_ld_l2l)
-                        for (int k = 1; k < nl; ++k)
-                            for (int a0 = R[k].x; a0 < R[k].y; a0 += kL2LChildren)
-                                lcx[lc + k].push_back(make_int2(a0, std::min(a0 + kL2LChildren, R[k].y)));
-                }
-                std::vector<int2> mall, lall;
-                for (int l = 0; l <= T.depth; ++l) {
-                    S.m2m_ch_lev[l] = (int)mall.size();
-                    S.l2l_ch_lev[l] = (int)lall.size();
-                    mall.insert(mall.end(), mc[l].begin(), mc[l].end());
-                    lall.insert(lall.end(), lcx[l].begin(), lcx[l].end());
-                }
-                S.m2m_ch_lev[T.depth + 1] = (int)mall.size();
-                S.l2l_ch_lev[T.depth + 1] = (int)lall.size();
-                if (!mall.empty()) FMMHP_CHECK(to_dev(A, &S.m2m_ch, mall, "M2M chunks", s));
-                if (!lall.empty()) FMMHP_CHECK(to_dev(A, &S.l2l_ch, lall, "L2L chunks", s));
-            }
-            // the L2L levels 4..lc in one launch of level-3-rooted subtrees (after level 3's own L2L)
-            // (only when those subtrees fit in LDS)
-            if (lc >= 5) {
-                std::vector<int2> trng;
-                int tmax = subtree_ranges(3, lc - 3 + 1, trng, cap, nullptr);
-                if (tmax <= cap) {
-                    S.top_nlev = lc - 3 + 1;
-                    tmax = group_subtrees(trng, S.top_nlev, cap / S.nloc, &S.n_top);
-                    FMMHP_CHECK(to_dev(A, &S.top_rng, trng, "top subtree ranges", s));
-                    S.top_ld_l2l = std::max(kL2LChildren, std::min(tmax * S.nloc, cap));
-                    S.top_ld_m2m = std::max(4 * kM2MParents, std::min(tmax, cap));
-                }
-            }
-        }
-    }
+    FMMHP_CHECK(build_bands(A, T, S, leaf, s));
     {
         std::vector<int32_t> woff, first, wp, rl;
         FMMHP_CHECK(to_host(woff, T.off[2], (size_t)nbox + 1, s));
@@ -3449,24 +3028,11 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
     FMMHP_CHECK(to_dev(A, &S.TimgG, TG, "TimgG", s));
     FMMHP_CHECK(to_dev(A, &S.Limg, Limg, "Limg", s));
 
-    std::vector<cplx> Em((size_t)4 * (PB + 1)), El((size_t)4 * (PB + 1));
-    for (int q = 0; q < 4; ++q) {
-        const C eps(((q & 1) ? 0.5 : -0.5), ((q & 2) ? 0.5 : -0.5));
-        C pm(1.0, 0.0), pl(1.0, 0.0);
-        for (int j = 0; j <= PB; ++j) {
-            Em[(size_t)q * (PB + 1) + j] = cx(pm * ifact[j]);
-            El[(size_t)q * (PB + 1) + j] = cx(pl * ifact[j]);
-            pm *= -eps;
-            pl *= eps;
-        }
-    }
-    FMMHP_CHECK(to_dev(A, &S.E_m2m, Em, "E_m2m", s));
     {
         std::vector<double2> lt(kLogTable);
         for (int k = 0; k < kLogTable; ++k) log_table_entry(k, &lt[k].x, &lt[k].y);
         FMMHP_CHECK(to_dev(A, &S.logtab, lt, "log table", s));
     }
-    FMMHP_CHECK(to_dev(A, &S.E_l2l, El, "E_l2l", s));
     // near-field records and source streams
     {
         std::vector<NearRec> rec;
@@ -3518,12 +3084,6 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
     FMMHP_HIP(hipStreamCreateWithFlags(&S.side2, hipStreamNonBlocking));
     FMMHP_HIP(hipEventCreateWithFlags(&S.ev_deep_ready, hipEventDisableTiming));
     FMMHP_HIP(hipEventCreateWithFlags(&S.ev_deep_done, hipEventDisableTiming));
-    {
-        int dev = 0, cus = 0;
-        FMMHP_HIP(hipGetDevice(&dev));
-        FMMHP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        S.cus = std::max(1, cus);
-    }
     FMMHP_HIP(hipEventCreateWithFlags(&S.ev_fork, hipEventDisableTiming));
     FMMHP_HIP(hipEventCreateWithFlags(&S.ev_join, hipEventDisableTiming));
     FMMHP_HIP(hipEventCreateWithFlags(&S.ev_up, hipEventDisableTiming));
@@ -3816,42 +3376,18 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
         FMMHP_HIP(hipEventRecord(S.ev_deep_done, side2_));
         return FMMHP_OK;
     };
-    // fork point: once the deep multipoles exist, or (S.fork_late) after the whole upward pass
-    const int lc = S.sub_level;
-    int lf = S.fork_late ? 2 : ld;
-    if (lc > 0 && lf >= lc) lf = T.depth;  // inside the subtree pass: fork right after it
-    if (lc > 0) {
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2m_sub<PB>), dim3(S.n_sub, NV), dim3(256),
-                           (PB + 1) * S.sub_ld_m2m * sizeof(cplx), s, S.sub_nlev, S.sub_rng, S.sub_ld_m2m, 1, nbox,
-                           T.leaf, T.child_first, T.nchild, T.bx, T.by, S.E_m2m, ws.W);
-        // the subtrees too large for LDS: one launch per parent level, deepest first
-        for (int l = T.depth - 1; l >= lc; --l) {
-            const int c0 = S.m2m_ch_lev[l], c1 = S.m2m_ch_lev[l + 1];
-            if (c1 > c0)
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2m_chunks<PB>), dim3(c1 - c0, NV), dim3(256),
-                                   (PB + 1) * 4 * kM2MParents * sizeof(cplx), s, S.m2m_ch + c0, nbox, T.leaf,
-                                   T.child_first, T.nchild, T.bx, T.by, S.E_m2m, ws.W);
+    // the upward pass, a launch per band, deepest first
+    bool forked = ld == 0;
+    for (int k = (int)S.bands.size() - 1; k >= 0; --k) {
+        const auto &B = S.bands[k];
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2m_band<PB>), dim3(nblk(B.nwave, 4), NV), dim3(256), 0, s, B.nwave,
+                           B.nlev, S.band_tab + B.tab, nbox, ws.W);
+        if (!forked && B.root <= ld) {
+            FMMHP_CHECK(fork_deep());
+            forked = true;
         }
     }
-    if (ld > 0 && lf > T.depth - 1) FMMHP_CHECK(fork_deep());
-    // above the cut: with a top subtree pass, the parents of levels 3..lc-1 in one launch (subtrees
-    // rooted at level 3, the cut level's multipoles their inputs), then level 2
-    int l_top = (lc > 0 ? lc : T.depth) - 1;
-    if (S.n_top > 0) {
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2m_sub<PB>), dim3(S.n_top, NV), dim3(256),
-                           (PB + 1) * S.top_ld_m2m * sizeof(cplx), s, S.top_nlev, S.top_rng, S.top_ld_m2m, 0, nbox,
-                           T.leaf, T.child_first, T.nchild, T.bx, T.by, S.E_m2m, ws.W);
-        if (ld > 0 && lf >= 3 && lf <= l_top) FMMHP_CHECK(fork_deep());
-        l_top = 2;
-    }
-    for (int l = l_top; l >= 2; --l) {
-        const int lo = T.lev_start[l], nb = T.lev_start[l + 1] - lo;
-        if (nb > 0)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2m<PB>), dim3(nblk(nb, kM2MParents), NV), dim3(256),
-                               (PB + 1) * 4 * kM2MParents * sizeof(cplx), s, lo, nb,
-                               nbox, T.leaf, T.child_first, T.nchild, T.bx, T.by, S.E_m2m, ws.W);
-        if (ld > 0 && l == lf) FMMHP_CHECK(fork_deep());
-    }
+    if (!forked) FMMHP_CHECK(fork_deep());
     FMMHP_HIP(hipGetLastError());
     // the W list (M2P) needs every multipole and adds into the near-field sums: on the near-field stream
     // once the upward pass is done, beside the M2L and the downward pass
@@ -3874,36 +3410,16 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     FMMHP_CHECK(far_levels(2, ld > 0 ? ld : T.depth + 1, s, false));
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_P2L, s));
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_L2L, s));
-    const int l2l_end = lc > 0 ? lc : T.depth;
-    // with a top subtree pass, levels 4..lc run in one launch after level 3's
-    const int l2l_last = S.n_top > 0 ? 3 : l2l_end;
-    if (S.n_top > 0 && ld > 0 && ld <= l2l_end) FMMHP_HIP(hipStreamWaitEvent(s, S.ev_deep_done, 0));
-    for (int l = 3; l <= l2l_last; ++l) {
-        if (S.n_top == 0 && ld > 0 && l == ld) FMMHP_HIP(hipStreamWaitEvent(s, S.ev_deep_done, 0));
-        const int lo = T.lev_start[l], nb = T.lev_start[l + 1] - lo;
-        if (nb > 0)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2l<PB>), dim3(nblk(nb, kL2LChildren), NV), dim3(256),
-                               (PB + 1) * kL2LChildren * sizeof(cplx), s, lo, nb,
-                               nbox, S.nloc, T.parent, T.bx, T.by, S.E_l2l, ws.Lam);
-    }
-    if (S.n_top > 0)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2l_sub<PB>), dim3(S.n_top, NV), dim3(256),
-                           (PB + 1) * S.top_ld_l2l * sizeof(cplx), s, S.top_nlev, S.top_rng, S.top_ld_l2l, 0, nbox,
-                           S.nloc, T.parent, T.bx, T.by, S.E_l2l, ws.Lam);
-    if (ld > 0 && ld > l2l_end) FMMHP_HIP(hipStreamWaitEvent(s, S.ev_deep_done, 0));
-    if (lc > 0) {
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2l_sub<PB>), dim3(S.n_sub, NV), dim3(256),
-                           (PB + 1) * S.sub_ld_l2l * sizeof(cplx), s, S.sub_nlev, S.sub_rng, S.sub_ld_l2l, 1, nbox,
-                           S.nloc, T.parent, T.bx, T.by, S.E_l2l, ws.Lam);
-        // the subtrees too large for LDS: one launch per child level, top level first
-        for (int l = lc + 1; l <= T.depth; ++l) {
-            const int c0 = S.l2l_ch_lev[l], c1 = S.l2l_ch_lev[l + 1];
-            if (c1 > c0)
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2l_chunks<PB>), dim3(c1 - c0, NV), dim3(256),
-                                   (PB + 1) * kL2LChildren * sizeof(cplx), s, S.l2l_ch + c0, nbox, S.nloc, T.parent,
-                                   T.bx, T.by, S.E_l2l, ws.Lam);
+    bool joined = ld == 0;
+    for (const auto &B : S.bands) {
+        if (!joined && B.root + B.nlev >= ld) {
+            FMMHP_HIP(hipStreamWaitEvent(s, S.ev_deep_done, 0));
+            joined = true;
         }
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2l_band<PB>), dim3(nblk(B.nwave, 4), NV * S.nloc), dim3(256), 0, s,
+                           B.nwave, B.nlev, S.band_tab + B.tab, nbox, ws.Lam);
     }
+    if (!joined) FMMHP_HIP(hipStreamWaitEvent(s, S.ev_deep_done, 0));
     if (mk_.on && ld == 0) {
         FMMHP_HIP(hipEventRecord(mk_.deep0, s));
         FMMHP_HIP(hipEventRecord(mk_.deep1, s));

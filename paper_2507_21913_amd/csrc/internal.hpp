@@ -204,15 +204,15 @@ struct Sched {
     int4 *sym_jobs = nullptr;       // (first point of B, count | image << 31, partial slot or -1, 0)
     int32_t *sym_in_off = nullptr, *sym_in = nullptr;  // per box: its partial slots (gather)
     int64_t near_blocks = 512;      // near-field grid (workgroups)
-    bool fork_late = false;         // start the deep M2L after the whole upward pass
     bool serial = false;            // every kernel on the eval stream (FMMHP_FLAG_SERIAL)
     bool rank1_side = true;         // surface sums on the near-field stream
-    int sub_level = 0;              // cut level of the subtree M2M / L2L passes (0: one launch per level)
-    int n_sub = 0, sub_nlev = 0;    // subtrees (the boxes of the cut level), levels cut..depth
-    int2 *sub_rng = nullptr;        // [n_sub][sub_nlev] box range of each subtree per level
-    int sub_ld_m2m = 0, sub_ld_l2l = 0;  // LDS expansion slots of the subtree passes
-    // subtrees below the cut too large for those slots: parent (M2M) and child (L2L) chunks by level
-    int2 *m2m_ch = nullptr, *l2l_ch = nullptr;
+    // bands of the M2M and L2L passes: levels root .. root + nlev, their waves and their part of band_tab
+    struct Band {
+        int root, nlev, nwave;
+        int64_t tab;
+    };
+    std::vector<Band> bands;
+    int32_t *band_tab = nullptr;
     // P2L groups: {first X box (index into xbox), X sources of the group, first entry of xgent, 0},
     // one sentinel {nxbox, 0, entries, 0}; groups never cross a level (xgrp_lev[l] = first group of
     // level l).  xgent: {list entry code, box slot in the group, first row in the group, first
@@ -220,10 +220,6 @@ struct Sched {
     int4 *xgrp = nullptr, *xgent = nullptr;
     double4 *xgeo = nullptr;
     std::vector<int> xgrp_lev;
-    std::vector<int> m2m_ch_lev, l2l_ch_lev;  // [depth + 2] first chunk of each level
-    // L2L of levels 4..cut in one launch: subtrees rooted at level 3 (0 subtrees: one launch per level)
-    int n_top = 0, top_nlev = 0, top_ld_l2l = 0, top_ld_m2m = 0;  // (the same subtrees serve the M2M)
-    int2 *top_rng = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     hipEvent_t ev_up = nullptr;  // upward pass done (main stream)
     // tables
@@ -239,8 +235,6 @@ struct Sched {
     double *logside = nullptr;      // [nbox] log(2 rho) of each box
     int32_t *ibase = nullptr;       // [nbox] image-table block of the box's (instance, level), or -1
     InstInfo *inst_info = nullptr;  // [n_inst]
-    cplx *E_m2m = nullptr;          // [4][PB + 1]  (-eps)^j / j!
-    cplx *E_l2l = nullptr;          // [4][PB + 1]  eps^j / j!
     double *invfact = nullptr;      // [2 PB + 2]
     double *fact = nullptr;         // [2 PB + 2]
     // surface-term chunks
