@@ -3488,18 +3488,38 @@ static fmmhp_status ensure_sym_part(Arena &A, Sched &S) {
     return A.alloc_n(&S.ws.part, (size_t)S.ws.cap * S.sym_npart, "near-field pair partial sums");
 }
 
+// Potentials of nvec vectors in passes of eight, four, two and one (each vector's result is the same in
+// any of them): pass(w) gives the workspace of a pass of width w, or null if it has none.
+template <class Pass>
+static fmmhp_status eval_passes(const Tree &T, const Sched &S, int nvec, const double *q, double *phi, hipStream_t s,
+                                Pass &&pass) {
+    for (int v = 0; v < nvec;) {
+        int w = kVecChunk;
+        while (w > nvec - v || !pass(w)) w >>= 1;
+        PassOut o;
+        o.phi = phi + (int64_t)v * 2 * T.n;
+        const double *qv = q + (int64_t)v * T.n;
+        switch (w) {
+            case 8: FMMHP_CHECK((run_pass<kPhi, 8>(T, S, *pass(8), qv, o, s))); break;
+            case 4: FMMHP_CHECK((run_pass<kPhi, 4>(T, S, *pass(4), qv, o, s))); break;
+            case 2: FMMHP_CHECK((run_pass<kPhi, 2>(T, S, *pass(2), qv, o, s))); break;
+            default: FMMHP_CHECK((run_pass<kPhi, 1>(T, S, *pass(1), qv, o, s)));
+        }
+        v += w;
+    }
+    return FMMHP_OK;
+}
+
 static fmmhp_status enqueue_eval(const Tree &T, const Sched &S, int nvec, const double *q, double *phi,
                                  hipStream_t s) {
-    int v = 0;
-    for (; v + kVecChunk <= nvec; v += kVecChunk) {
-        PassOut o;
-        o.phi = phi + (int64_t)v * 2 * T.n;
-        FMMHP_CHECK((run_pass<kPhi, kVecChunk>(T, S, S.ws, q + (int64_t)v * T.n, o, s)));
-    }
-    for (; v < nvec; ++v) {
-        PassOut o;
-        o.phi = phi + (int64_t)v * 2 * T.n;
-        FMMHP_CHECK((run_pass<kPhi, 1>(T, S, S.ws, q + (int64_t)v * T.n, o, s)));
+    return eval_passes(T, S, nvec, q, phi, s, [&](int w) { return w <= S.ws.cap ? &S.ws : nullptr; });
+}
+
+// Workspace for the widest passes that nvec vectors take; where the memory is short, for narrower ones.
+static fmmhp_status ensure_eval_ws(Arena &A, const Tree &T, Sched &S, int nvec) {
+    for (int w = nvec >= 8 ? 8 : nvec >= 4 ? 4 : nvec >= 2 ? 2 : 1; w > S.ws.cap; w >>= 1) {
+        const fmmhp_status st = ensure_vec_ws(A, T, S, w);
+        if (st != FMMHP_ENOMEM || w == 1) return st;
     }
     return FMMHP_OK;
 }
@@ -3584,27 +3604,19 @@ fmmhp_status run_eval_noalloc(const Tree &T, const Sched &S, int device, int nve
     }
     unsigned char *base = nullptr;
     FMMHP_CHECK(scratch_on(device, &base));
-    VecWs w1, w8;
-    vec_ws_layout(T, S, 1, base, &w1);
-    const bool wide = nvec >= kVecChunk && vec_ws_layout(T, S, kVecChunk, nullptr, nullptr) <= kNoAllocScratchBytes;
-    if (wide) vec_ws_layout(T, S, kVecChunk, base, &w8);
-    int v = 0;
-    if (wide)
-        for (; v + kVecChunk <= nvec; v += kVecChunk) {
-            PassOut o;
-            o.phi = phi + (int64_t)v * 2 * T.n;
-            FMMHP_CHECK((run_pass<kPhi, kVecChunk>(T, S, w8, q + (int64_t)v * T.n, o, s)));
-        }
-    for (; v < nvec; ++v) {
-        PassOut o;
-        o.phi = phi + (int64_t)v * 2 * T.n;
-        FMMHP_CHECK((run_pass<kPhi, 1>(T, S, w1, q + (int64_t)v * T.n, o, s)));
-    }
-    return FMMHP_OK;
+    VecWs w[4];  // widths 1, 2, 4, 8
+    int nw = 0;
+    for (int k = 0; k < 4 && vec_ws_layout(T, S, 1 << k, nullptr, nullptr) <= kNoAllocScratchBytes; ++k)
+        vec_ws_layout(T, S, 1 << k, base, &w[nw++]);
+    return eval_passes(T, S, nvec, q, phi, s, [&](int width) -> const VecWs * {
+        for (int k = 0; k < nw; ++k)
+            if (width == 1 << k) return &w[k];
+        return nullptr;
+    });
 }
 
 fmmhp_status run_eval(Arena &A, const Tree &T, Sched &S, int nvec, const double *q, double *phi, hipStream_t s) {
-    if (nvec >= kVecChunk) FMMHP_CHECK(ensure_vec_ws(A, T, S, kVecChunk));
+    FMMHP_CHECK(ensure_eval_ws(A, T, S, nvec));
     FMMHP_CHECK(ensure_sym_part(A, S));
     if (!S.use_graph || S.timing || s == nullptr) return enqueue_eval(T, S, nvec, q, phi, s);
     auto &G = S.graph;
@@ -3638,9 +3650,12 @@ fmmhp_status run_eval(Arena &A, const Tree &T, Sched &S, int nvec, const double 
 // Complex charges: phi[q_re + i q_im] = phi[q_re] + i phi[q_im] (the operator is real-linear in the
 // charges), evaluated as two real vectors and combined on the device.
 // ---------------------------------------------------------------------------------------------
+// complex vectors [n][2] (one per blockIdx.y) -> pairs of real ones [2][n]
 __global__ void k_split_complex(const double *__restrict__ q, int64_t n, double *__restrict__ qr) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    q += (int64_t)blockIdx.y * 2 * n;
+    qr += (int64_t)blockIdx.y * 2 * n;
     qr[i] = q[2 * i];
     qr[n + i] = q[2 * i + 1];
 }
@@ -3649,22 +3664,37 @@ __global__ void k_combine_complex(const double *__restrict__ p2, int64_t n, doub
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     // p2 = [phi[q_re]; phi[q_im]], each [n][2]
+    p2 += (int64_t)blockIdx.y * 4 * n;
+    phi += (int64_t)blockIdx.y * 2 * n;
     phi[2 * i] = p2[2 * i] - p2[2 * n + 2 * i + 1];
     phi[2 * i + 1] = p2[2 * i + 1] + p2[2 * n + 2 * i];
 }
 
 fmmhp_status run_eval_complex(Arena &A, const Tree &T, Sched &S, int nvec, const double *q, double *phi,
                               hipStream_t s) {
-    if (!S.cq) {
-        FMMHP_CHECK(A.alloc_n(&S.cq, (size_t)2 * T.n, "complex-charge split"));
-        FMMHP_CHECK(A.alloc_n(&S.cphi, (size_t)4 * T.n, "complex-charge potentials"));
+    // up to four complex vectors at once: one pass of eight real ones; where the memory is short, fewer
+    for (int g = std::min(nvec, kVecChunk / 2); g > S.ccap; g = g > 1 ? g / 2 : 0) {
+        double *cq = nullptr, *cphi = nullptr;
+        fmmhp_status st = A.alloc_n(&cq, (size_t)2 * g * T.n, "complex-charge split");
+        if (st == FMMHP_OK) st = A.alloc_n(&cphi, (size_t)4 * g * T.n, "complex-charge potentials");
+        if (st == FMMHP_OK) {
+            S.cq = cq;
+            S.cphi = cphi;
+            S.ccap = g;
+        } else if (st != FMMHP_ENOMEM || g == 1) {
+            return st;
+        }
     }
-    for (int v = 0; v < nvec; ++v) {
-        hipLaunchKernelGGL(k_split_complex, dim3(nblk(T.n, 256)), dim3(256), 0, s, q + (int64_t)v * 2 * T.n, T.n,
+    int step = std::min(S.ccap, nvec);
+    if (S.use_graph)  // one recorded graph serves every group
+        while (nvec % step) --step;
+    for (int v = 0; v < nvec; v += step) {
+        const int g = std::min(step, nvec - v);
+        hipLaunchKernelGGL(k_split_complex, dim3(nblk(T.n, 256), g), dim3(256), 0, s, q + (int64_t)v * 2 * T.n, T.n,
                            S.cq);
         FMMHP_HIP(hipGetLastError());
-        FMMHP_CHECK(run_eval(A, T, S, 2, S.cq, S.cphi, s));
-        hipLaunchKernelGGL(k_combine_complex, dim3(nblk(T.n, 256)), dim3(256), 0, s, S.cphi, T.n,
+        FMMHP_CHECK(run_eval(A, T, S, 2 * g, S.cq, S.cphi, s));
+        hipLaunchKernelGGL(k_combine_complex, dim3(nblk(T.n, 256), g), dim3(256), 0, s, S.cphi, T.n,
                            phi + (int64_t)v * 2 * T.n);
         FMMHP_HIP(hipGetLastError());
     }
@@ -3692,6 +3722,7 @@ fmmhp_status run_eval_dlp(Arena &A, const Tree &T, Sched &S, int nvec, const dou
     if (w == 2 && !S.cq) {
         FMMHP_CHECK(A.alloc_n(&S.cq, (size_t)2 * T.n, "complex-charge split"));
         FMMHP_CHECK(A.alloc_n(&S.cphi, (size_t)4 * T.n, "complex-charge potentials"));
+        S.ccap = 1;
     }
     for (int v = 0; v < nvec; ++v) {
         if (w == 1) {

@@ -243,7 +243,8 @@ struct Sched {
     int32_t *inst_ch = nullptr;     // [n_inst + 1] chunk range of each instance
     VecWs ws;                       // workspace of the plan's own evaluations
     BwdWork bw;
-    double *cq = nullptr, *cphi = nullptr;  // complex-charge workspace ([2][n], [2][n][2])
+    double *cq = nullptr, *cphi = nullptr;  // complex-charge workspace ([2 ccap][n], [2 ccap][n][2])
+    int ccap = 0;                           // complex vectors it holds
     double2 *nrm = nullptr;         // [n] source normals in sorted order (double-layer evaluation)
     // recorded evaluation (FMMHP_FLAG_GRAPH)
     bool use_graph = false;
