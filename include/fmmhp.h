@@ -108,8 +108,9 @@ typedef struct {
  * duration is then its own, not shared with concurrent kernels); slower. */
 #define FMMHP_FLAG_SERIAL 16u
 /* Form of the FP64 M2L of upper sources (eq. (truncatedM2Lcoef) and the log-kernel M2L).  The default
- * translates plane waves: the same sums through a quadrature whose error stays below the expansion's
- * own at every p (under 1% of it up to p = 25, 12% at p = 30, of the order of rounding above).  The
+ * translates plane waves: the same sums through a quadrature whose error stays below 1e-12 of a unit
+ * charge's field and below the expansion's own at every p (under 1% of it up to p = 25, 12% at p = 30,
+ * of the order of rounding above).  The
  * flags select the Hankel rows themselves, on the vector ALUs (one lane per target box, operators in
  * scalar registers) or on the FP64 matrix cores (v_mfma_f64_16x16x4f64, complex numbers as 2 x 2 real
  * blocks); at most one of the two.  Ignored with FMMHP_FLAG_M2L_FP32. */

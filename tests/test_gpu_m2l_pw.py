@@ -18,7 +18,7 @@ import re
 import numpy as np
 import pytest
 
-ERR = {5: 2.8e-7, 10: 2.4e-9, 15: 1.2e-11, 20: 1.1e-13, 25: 5.5e-15, 30: 4.7e-16, 35: 9.1e-17, 40: 9.1e-17}
+ERR = {5: 1.1e-12, 10: 9.6e-13, 15: 8.8e-13, 20: 1.1e-13, 25: 5.5e-15, 30: 4.7e-16, 35: 9.1e-17, 40: 9.1e-17}
 HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_21913_amd", "csrc",
                       "pw_nodes.hpp")
 
