@@ -96,9 +96,11 @@ __device__ __forceinline__ cplx reaction_I0_near(double x, double y, cplx Z) {
     return kInv2Pi * (e * mk(-ei.re, kPi - ei.im));
 }
 
-__global__ void k_zero_i32(int32_t *__restrict__ p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+// log(2 rho) of every box from the table [n_inst][depth + 1]
+__global__ void k_logside(int nbox, int nl, const int32_t *__restrict__ inst, const int32_t *__restrict__ level,
+                          const double *__restrict__ tab, double *__restrict__ out) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < nbox) out[b] = tab[(int64_t)inst[b] * nl + level[b]];
 }
 
 __global__ void k_pack_xy(const double *__restrict__ xs, const double *__restrict__ ys, int64_t n,
@@ -1278,12 +1280,7 @@ __device__ __forceinline__ XcdChunks xcd_chunks(int64_t nch) {
 // lane measured better than eight (72 -> 60 M instructions at 1M): the smaller step leaves fewer lanes
 // idle at a stream's end.
 constexpr int kNearTargets = 4;  // targets per lane at most
-constexpr int kNearPad = 192;    // stream entries read (and not used) past a segment's end: 3 JG at most
-struct NearRec {
-    int32_t ft, nt;      // first target, targets (at most 64)
-    int32_t nself, nfree, nimg, pad;  // points of the leaf, free ones in all, image ones
-    int64_t off;         // first entry of the stream
-};
+static_assert(kNearPad >= 3 * 64, "a segment reads up to 3 JG entries past its end");
 
 struct NearArgs {
     int64_t n;
@@ -1474,25 +1471,6 @@ __global__ __launch_bounds__(256) void k_near(NearArgs a) {
         default: near_record<MODE, NV, 4>(a, s_logtab, lane, rc, IA); break;
         }
     }
-}
-
-// The source streams of the leaves, a wave per leaf: its own points, the other free U entries' in list
-// order, the image ones'.
-__global__ __launch_bounds__(64) void k_near_stream(const int32_t *__restrict__ leaves, const int64_t *__restrict__ off,
-                                                    const int32_t *__restrict__ uoff, const int32_t *__restrict__ uent,
-                                                    const int32_t *__restrict__ first,
-                                                    const int32_t *__restrict__ count, int32_t *__restrict__ stream) {
-    const int b = leaves[blockIdx.x];
-    int32_t *out = stream + off[blockIdx.x];
-    for (int t = threadIdx.x; t < count[b]; t += 64) out[t] = first[b] + t;
-    out += count[b];
-    for (int img = 0; img < 2; ++img)
-        for (int e = uoff[b]; e < uoff[b + 1]; ++e) {
-            const int code = uent[e], c = code >> 1, m = count[c], f = first[c];
-            if ((code & 1) != img || code == 2 * b) continue;
-            for (int t = threadIdx.x; t < m; t += 64) out[t] = f + t;
-            out += m;
-        }
 }
 
 // Near field, log terms, symmetric leaf-pair walk (near_walk 3; potential only).  The log kernel of
@@ -2418,17 +2396,25 @@ static fmmhp_status build_pw_tiles(Arena &A, const Tree &T, Sched &S, const std:
 }
 
 // Node tables: source rows mu^m; target rows {f, cos and sin of mu, 3 mu, 5 mu, 2 mu} and g mu^n with
-// f = e^(-2 mu), g = omega e^(-4 mu) / (4 pi mu); Lp = L minus the quadrature's own n = m = 0 term.
-static fmmhp_status build_pw_tables(Arena &A, Sched &S, const std::vector<cplx> &Lfree, hipStream_t s) {
+// f = e^(-2 mu), g = omega e^(-4 mu) / (4 pi mu); Lp = L minus the quadrature's own n = m = 0 term.  They
+// depend on p alone: built once per process and order.
+struct PwTables {
+    std::vector<double> ts, tt;
+    std::vector<cplx> Lp;
+};
+
+static PwTables make_pw_tables(int PB, const std::vector<cplx> &Lfree) {
     using ld = long double;
-    const int PB = S.PB, K = pw_nodes(PB), K2 = 2 * pw_steps(PB), TS = pw_src_row(PB), TT = pw_tgt_row(PB);
-    std::vector<double> ts((size_t)K2 * TS, 0.0), tt((size_t)K2 * TT, 0.0);
-    std::vector<cplx> Lp(Lfree);
+    const int K = pw_nodes(PB), K2 = 2 * pw_steps(PB), TS = pw_src_row(PB), TT = pw_tgt_row(PB);
+    PwTables R;
+    R.ts.assign((size_t)K2 * TS, 0.0);
+    R.tt.assign((size_t)K2 * TT, 0.0);
+    R.Lp = Lfree;
     std::vector<std::complex<ld>> Q(kNumSlots, 0);
     const ld pi = 3.14159265358979323846264338327950288L;
     for (int k = 0; k < K; ++k) {
         const ld mu = pw_mu(PB)[k], f = std::exp(-2 * mu), g = pw_omega(PB)[k] * f * f / (4 * pi * mu);
-        double *a = ts.data() + (size_t)k * TS, *b = tt.data() + (size_t)k * TT;
+        double *a = R.ts.data() + (size_t)k * TS, *b = R.tt.data() + (size_t)k * TT;
         ld pw = 1;
         for (int n = 0; n <= PB; ++n, pw *= mu) {
             a[n] = (double)pw;
@@ -2449,11 +2435,18 @@ static fmmhp_status build_pw_tables(Arena &A, Sched &S, const std::vector<cplx> 
             }
     }
     for (int o = 0; o < kNumSlots; ++o)
-        Lp[o] = mk((double)(Lfree[o].re - Q[o].real()), (double)(Lfree[o].im - Q[o].imag()));
-    FMMHP_CHECK(to_dev(A, &S.pw_ts, ts, "M2L source node table", s));
-    FMMHP_CHECK(to_dev(A, &S.pw_tt, tt, "M2L target node table", s));
-    FMMHP_CHECK(to_dev(A, &S.pw_L, Lp, "M2L log table", s));
-    FMMHP_HIP(hipStreamSynchronize(s));  // the uploads read local vectors
+        R.Lp[o] = mk((double)(Lfree[o].re - Q[o].real()), (double)(Lfree[o].im - Q[o].imag()));
+    return R;
+}
+
+static fmmhp_status build_pw_tables(Arena &A, Sched &S, const std::vector<cplx> &Lfree, hipStream_t s) {
+    static std::once_flag once[FMMHP_MAX_P / 5 + 1];
+    static PwTables tab[FMMHP_MAX_P / 5 + 1];
+    const int k = S.PB / 5;
+    std::call_once(once[k], [&] { tab[k] = make_pw_tables(S.PB, Lfree); });
+    FMMHP_CHECK(to_dev(A, &S.pw_ts, tab[k].ts, "M2L source node table", s));
+    FMMHP_CHECK(to_dev(A, &S.pw_tt, tab[k].tt, "M2L target node table", s));
+    FMMHP_CHECK(to_dev(A, &S.pw_L, tab[k].Lp, "M2L log table", s));
     return FMMHP_OK;
 }
 
@@ -2559,89 +2552,53 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         set_error("%d boxes: the schedule supports fewer than 2^28", nbox);
         return FMMHP_EUNSUPPORTED;
     }
+    // The slot table and the tiles of the Hankel forms are built only for the plans that ask for one
+    // (the plane-wave form has tiles of its own, below).
+    const bool hankel = S.m2l_fp32 || S.m2l_form != 0;
+    const bool wx = T.len[2] > 0 || T.len[3] > 0;
+    std::vector<int32_t> vimg_off;
+    FMMHP_CHECK(list_tables(A, T, S, vimg_off, s));
     std::vector<int32_t> level, bx, by, leaf, voff, vent, xoff, binst;
     FMMHP_CHECK(to_host(binst, T.inst, nbox, s));
     FMMHP_CHECK(to_host(level, T.level, nbox, s));
-    FMMHP_CHECK(to_host(bx, T.bx, nbox, s));
-    FMMHP_CHECK(to_host(by, T.by, nbox, s));
     FMMHP_CHECK(to_host(leaf, T.leaf, nbox, s));
-    FMMHP_CHECK(to_host(voff, T.off[1], (size_t)nbox + 1, s));
-    FMMHP_CHECK(to_host(vent, T.ent[1], (size_t)T.len[1], s));
-    FMMHP_CHECK(to_host(xoff, T.off[3], (size_t)nbox + 1, s));
-    std::vector<int32_t> uoff, uent, cnt, xent;
-    FMMHP_CHECK(to_host(xent, T.ent[3], (size_t)T.len[3], s));
-    FMMHP_CHECK(to_host(uoff, T.off[0], (size_t)nbox + 1, s));
-    FMMHP_CHECK(to_host(uent, T.ent[0], (size_t)T.len[0], s));
-    FMMHP_CHECK(to_host(cnt, T.count, (size_t)nbox, s));
+    if (hankel || wx) {
+        FMMHP_CHECK(to_host(bx, T.bx, nbox, s));
+        FMMHP_CHECK(to_host(by, T.by, nbox, s));
+    }
+    if (hankel) {
+        FMMHP_CHECK(to_host(voff, T.off[1], (size_t)nbox + 1, s));
+        FMMHP_CHECK(to_host(vent, T.ent[1], (size_t)T.len[1], s));
+    }
+    std::vector<int32_t> cnt, xent;
+    if (T.len[3] > 0) {
+        FMMHP_CHECK(to_host(xoff, T.off[3], (size_t)nbox + 1, s));
+        FMMHP_CHECK(to_host(xent, T.ent[3], (size_t)T.len[3], s));
+        FMMHP_CHECK(to_host(cnt, T.count, (size_t)nbox, s));
+    }
     FMMHP_HIP(hipStreamSynchronize(s));
-    S.p2p_pairs[0] = S.p2p_pairs[1] = 0;
-    for (int b = 0; b < nbox; ++b)
-        for (int e = uoff[b]; e < uoff[b + 1]; ++e)
-            S.p2p_pairs[uent[e] & 1] += (int64_t)cnt[b] * cnt[uent[e] >> 1];
-    S.m2l_pairs[0] = S.m2l_pairs[1] = 0;
-    for (size_t e = 0; e < vent.size(); ++e) S.m2l_pairs[vent[e] & 1] += 1;
 
-    // Host threads for the slot table and the M2L tiles (each takes whole box ranges or tiles)
-    const int nthr = (int)std::max<size_t>(1, std::min<size_t>((size_t)16, (size_t)std::max(1u, std::thread::hardware_concurrency())));
-    auto run_threads = [&](auto &&fn) {
+    // Host threads for the Hankel tiles and the image tables
+    auto run_threads = [&](int nthr, auto &&fn) {
         std::vector<std::thread> pool;
         for (int t = 1; t < nthr; ++t) pool.emplace_back(fn, t);
         fn(0);
         for (auto &th : pool) th.join();
     };
-    // The slot table and the tiles of the Hankel forms are built only for the plans that ask for one
-    // (the plane-wave form has tiles of its own, below).
-    const bool hankel = S.m2l_fp32 || S.m2l_form != 0;
-    // M2L slots: vslot[b * kNumSlots + o] = upper V source of box b at offset slot o, or -1; image
-    // V entries (source << 5 | slot) per box.  Threads take contiguous box ranges.
+    const int max_thr = (int)std::max<size_t>(1, std::min<size_t>((size_t)16, (size_t)std::max(1u, std::thread::hardware_concurrency())));
+    // M2L slots: vslot[b * kNumSlots + o] = upper V source of box b at offset slot o, or -1.  Threads take
+    // contiguous box ranges.
     std::unique_ptr<int32_t[]> vslot(new int32_t[hankel ? (size_t)kNumSlots * std::max(1, nbox) : 1]);
-    std::vector<int32_t> vimg_off(nbox + 1, 0), vimg_ent;
-    {
-        std::vector<std::vector<int32_t>> img_t(nthr);
-        std::atomic<int> bad{0};  // 1: V entry outside the 7 x 7 block, 2: image entry above its target
-        run_threads([&](int t) {
-            const int b0 = (int)((int64_t)nbox * t / nthr), b1 = (int)((int64_t)nbox * (t + 1) / nthr);
-            if (hankel) std::fill(vslot.get() + (size_t)b0 * kNumSlots, vslot.get() + (size_t)b1 * kNumSlots, -1);
-            std::vector<int32_t> &out = img_t[t];
-            for (int b = b0; b < b1; ++b) {
-                const int l = level[b];
+    if (hankel)
+        run_threads(max_thr, [&](int t) {
+            const int b0 = (int)((int64_t)nbox * t / max_thr), b1 = (int)((int64_t)nbox * (t + 1) / max_thr);
+            std::fill(vslot.get() + (size_t)b0 * kNumSlots, vslot.get() + (size_t)b1 * kNumSlots, -1);
+            for (int b = b0; b < b1; ++b)
                 for (int e = voff[b]; e < voff[b + 1]; ++e) {
-                    const int c = vent[e] >> 1, img = vent[e] & 1;
-                    const int dx = bx[c] - bx[b];
-                    const int cy = img ? ((1 << l) - 1 - by[c]) : by[c];
-                    const int dy = cy - by[b];
-                    if (dx < -3 || dx > 3 || dy < -3 || dy > 3) {
-                        bad = 1;
-                        continue;
-                    }
-                    if (!img) {
-                        if (hankel) vslot[(size_t)b * kNumSlots + slot_of(dx, dy)] = c;
-                    } else {
-                        if (dy > -1) bad = 2;
-                        out.push_back((c << 5) | slot_of(dx, dy));
-                    }
+                    const int c = vent[e] >> 1;
+                    if (!(vent[e] & 1)) vslot[(size_t)b * kNumSlots + slot_of(bx[c] - bx[b], by[c] - by[b])] = c;
                 }
-                vimg_off[b + 1] = (int32_t)out.size();
-            }
         });
-        if (bad == 1) {
-            set_error("internal: V entry outside the 7x7 offset block");
-            return FMMHP_EUNSUPPORTED;
-        }
-        if (bad == 2) {
-            set_error("internal: image V entry above its target");
-            return FMMHP_EUNSUPPORTED;
-        }
-        // per-range counts to offsets, then the ranges' entries in box order
-        int32_t base = 0;
-        for (int t = 0; t < nthr; ++t) {
-            const int b0 = (int)((int64_t)nbox * t / nthr), b1 = (int)((int64_t)nbox * (t + 1) / nthr);
-            for (int b = b0; b < b1; ++b) vimg_off[b + 1] += base;
-            base += (int32_t)img_t[t].size();
-            vimg_ent.insert(vimg_ent.end(), img_t[t].begin(), img_t[t].end());
-        }
-    }
-    FMMHP_CHECK(to_dev(A, &S.vimg_off, vimg_off, "vimg_off", s));
     {
         std::vector<int32_t> ib;
         for (int b = 0; b < nbox; ++b)
@@ -2652,7 +2609,6 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         for (int l = 0; l <= T.depth + 1; ++l)
             S.ibox_lev[l] = (int)(std::lower_bound(ib.begin(), ib.end(), T.lev_start[std::max(1, std::min(l, T.depth + 1))]) - ib.begin());
     }
-    FMMHP_CHECK(to_dev(A, &S.vimg_ent, vimg_ent, "vimg_ent", s));
 
     // M2L tiles: up to kTile boxes of one level and one child class (bx & 1, by & 1), consecutive in
     // Morton order.  Boxes of one class have the same V offsets away from boundaries, so the lanes
@@ -2733,9 +2689,9 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
             o.src.insert(o.src.end(), uniq.begin(), uniq.end());
             o.nsrc.push_back((int32_t)uniq.size());
         };
-        run_threads([&](int tid) {
+        run_threads(max_thr, [&](int tid) {
             std::vector<int32_t> pos(nbox, -1), uniq;
-            for (size_t i = tid; i < init.size(); i += nthr)
+            for (size_t i = tid; i < init.size(); i += max_thr)
                 build_range(build_range, init[i].first, init[i].second, pos, uniq, outs[i]);
         });
         // the initial tiles' outputs in order (levels ascending): offsets, then threads copy
@@ -2753,8 +2709,8 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         tsrc.resize(as[ni]);
         tsoff.resize(ntile + 1);
         tsoff[0] = 0;
-        run_threads([&](int tid) {
-            for (size_t i = tid; i < ni; i += nthr) {
+        run_threads(max_thr, [&](int tid) {
+            for (size_t i = tid; i < ni; i += max_thr) {
                 const TileOut &o = outs[i];
                 std::copy(o.boxes.begin(), o.boxes.end(), tiles.begin() + at[i] * kTile);
                 std::copy(o.slot.begin(), o.slot.end(), tslot.begin() + at[i] * kNumSlots * kTile);
@@ -2776,12 +2732,11 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
     FMMHP_CHECK(to_dev(A, &S.tile_slot, tslot, "tile slots", s));
     FMMHP_CHECK(to_dev(A, &S.tile_mask, tmask, "tile masks", s));
 
-    // X-list targets, leaves
-    std::vector<int32_t> xb, lv;
-    for (int b = 0; b < nbox; ++b) {
-        if (xoff[b + 1] > xoff[b]) xb.push_back(b);
-        if (leaf[b]) lv.push_back(b);
-    }
+    // X-list targets
+    std::vector<int32_t> xb;
+    if (T.len[3] > 0)
+        for (int b = 0; b < nbox; ++b)
+            if (xoff[b + 1] > xoff[b]) xb.push_back(b);
     S.nxbox = (int)xb.size();
     FMMHP_CHECK(to_dev(A, &S.xbox, xb, "xbox", s));
     // P2L groups: consecutive X boxes of a level while their sources total at most one chunk of 64;
@@ -2826,27 +2781,7 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
                 break;
             }
     }
-    FMMHP_CHECK(to_dev(A, &S.leaves, lv, "leaves", s));
     FMMHP_CHECK(build_bands(A, T, S, leaf, s));
-    {
-        std::vector<int32_t> woff, first, wp, rl;
-        FMMHP_CHECK(to_host(woff, T.off[2], (size_t)nbox + 1, s));
-        FMMHP_CHECK(to_host(first, T.first, (size_t)nbox, s));
-        FMMHP_HIP(hipStreamSynchronize(s));
-        for (int b : lv) {
-            if (woff[b + 1] > woff[b])
-                for (int j = first[b]; j < first[b] + cnt[b]; ++j) wp.push_back(j);
-            bool img = false;
-            for (int e = uoff[b]; e < uoff[b + 1] && !img; ++e) img = (uent[e] & 1) != 0;
-            if (img)
-                for (int j = first[b]; j < first[b] + cnt[b]; ++j) rl.push_back(j);
-        }
-        S.n_wpts = (int64_t)wp.size();
-        S.n_rpts = (int64_t)rl.size();
-        FMMHP_CHECK(to_dev(A, &S.wpts, wp, "W-list targets", s));
-        FMMHP_CHECK(to_dev(A, &S.rpts, rl, "near-axis targets", s));
-    }
-
     // tables
     const int NT = 2 * PB + 1;
     const int NTP = m2l_row(PB);
@@ -2898,14 +2833,16 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
     FMMHP_CHECK(to_dev(A, &S.Lfree, Lfree, "Lfree", s));
     if (!hankel) FMMHP_CHECK(build_pw_tables(A, S, Lfree, s));
     {
-        std::vector<double> ls(nbox);
-        // log(2 rho) per (instance, level), the same value for every box there
+        // log(2 rho) per (instance, level)
         const int nl = T.depth + 1;
         std::vector<double> lt((size_t)T.n_inst * nl);
         for (int k = 0; k < T.n_inst; ++k)
             for (int l = 0; l < nl; ++l) lt[(size_t)k * nl + l] = std::log(ldexp(T.inst_S[k], -l));
-        for (int b = 0; b < nbox; ++b) ls[b] = lt[(size_t)binst[b] * nl + level[b]];
-        FMMHP_CHECK(to_dev(A, &S.logside, ls, "log side", s));
+        double *d_lt = nullptr;
+        FMMHP_CHECK(to_dev(A, &d_lt, lt, "log side table", s));
+        FMMHP_CHECK(A.alloc_n(&S.logside, (size_t)nbox, "log side"));
+        hipLaunchKernelGGL(k_logside, dim3(nblk(nbox, 256)), dim3(256), 0, s, nbox, nl, T.inst, T.level, d_lt, S.logside);
+        FMMHP_HIP(hipGetLastError());
         std::vector<InstInfo> ii(T.n_inst);
         for (int k = 0; k < T.n_inst; ++k) ii[k] = InstInfo{T.inst_xlo[k], T.inst_S[k], Zs[k], isg, react ? 1 : 0, 0};
         FMMHP_CHECK(to_dev(A, &S.inst_info, ii, "instance info", s));
@@ -2945,11 +2882,12 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         }
     // the blocks are independent (a forest has one per instance and level): host threads take them in
     // turn, each with its own scratch and its own largest |Z| x separation
-    std::vector<double> pmax_t(nthr, 0.0);
-    run_threads([&](int th) {
+    const int img_thr = (int)std::max<size_t>(1, std::min<size_t>((size_t)max_thr, blocks.size()));
+    std::vector<double> pmax_t(img_thr, 0.0);
+    run_threads(img_thr, [&](int th) {
         std::vector<cplx> K(NT), Km(NT);
         double &pmax = pmax_t[th];
-        for (size_t bi = th; bi < blocks.size(); bi += nthr) {
+        for (size_t bi = th; bi < blocks.size(); bi += img_thr) {
             const int k = blocks[bi].first, l = blocks[bi].second;
             const cplx Z = Zs[k];
             const C Zc(Z.re, Z.im);
@@ -2996,7 +2934,7 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
     }
     // P2L (X list) and M2P (W list) run the double-precision recursion on the device: keep
     // |Z| * distance within the range where it loses at most ~4 digits
-    {
+    if (wx && react) {
         std::vector<int32_t> went, woff2;
         FMMHP_CHECK(to_host(woff2, T.off[2], (size_t)nbox + 1, s));
         FMMHP_CHECK(to_host(went, T.ent[2], (size_t)T.len[2], s));
@@ -3014,10 +2952,10 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         for (int b = 0; b < nbox; ++b) {
             for (int e = woff2[b]; e < woff2[b + 1]; ++e)
                 if (went[e] & 1) wxmax = std::max(wxmax, reach(b, went[e] >> 1));
-            for (int e = xoff[b]; e < xoff[b + 1]; ++e)
+            for (int e = T.len[3] > 0 ? xoff[b] : 0; e < (T.len[3] > 0 ? xoff[b + 1] : 0); ++e)
                 if (xent[e] & 1) wxmax = std::max(wxmax, reach(b, xent[e] >> 1));
         }
-        if (react && wxmax > kMaxDevicePZ) {
+        if (wxmax > kMaxDevicePZ) {
             set_error("impedance times distance reaches %.3g on a W or X list entry; the device I_n "
                       "recursion is used up to %.0f",
                       wxmax, kMaxDevicePZ);
@@ -3033,37 +2971,6 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         for (int k = 0; k < kLogTable; ++k) log_table_entry(k, &lt[k].x, &lt[k].y);
         FMMHP_CHECK(to_dev(A, &S.logtab, lt, "log table", s));
     }
-    // near-field records and source streams
-    {
-        std::vector<NearRec> rec;
-        std::vector<int64_t> soff;
-        std::vector<int32_t> first;
-        FMMHP_CHECK(to_host(first, T.first, (size_t)nbox, s));
-        FMMHP_HIP(hipStreamSynchronize(s));
-        int64_t tot = 0;
-        for (int b : lv) {
-            int64_t len[2] = {0, 0};
-            for (int e = uoff[b]; e < uoff[b + 1]; ++e) len[uent[e] & 1] += cnt[uent[e] >> 1];
-            for (int t0 = 0; t0 < cnt[b]; t0 += 64)
-                rec.push_back(NearRec{first[b] + t0, std::min(64, cnt[b] - t0), cnt[b], (int32_t)len[0],
-                                      (int32_t)len[1], 0, tot});
-            soff.push_back(tot);
-            tot += len[0] + len[1];
-        }
-        S.near_nrec = (int)rec.size();
-        NearRec *d_rec = nullptr;
-        int64_t *d_off = nullptr;
-        FMMHP_CHECK(to_dev(A, &d_rec, rec, "near-field records", s));
-        S.near_rec = d_rec;
-        FMMHP_CHECK(to_dev(A, &d_off, soff, "near-field stream offsets", s));
-        FMMHP_CHECK(A.alloc_n(&S.near_stream, (size_t)tot + kNearPad, "near-field source streams"));
-        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(kNearPad), 0, s, S.near_stream + tot, (int64_t)kNearPad);
-        hipLaunchKernelGGL(k_near_stream, dim3((unsigned)T.nleaf), dim3(64), 0, s, S.leaves, d_off, T.off[0], T.ent[0],
-                           T.first, T.count, S.near_stream);
-        FMMHP_HIP(hipGetLastError());
-        FMMHP_HIP(hipStreamSynchronize(s));  // the uploads read local vectors
-    }
-
     // surface-term chunks: at most kSurfChunk points, within one instance
     {
         std::vector<PtChunk> ch;
@@ -3274,7 +3181,7 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     const int64_t near_blocks = heavy_near ? std::max<int64_t>(S.near_blocks, (int64_t)kNearHeavyGroups * S.cus)
                                            : S.near_blocks;
     const dim3 near_grid((unsigned)std::min<int64_t>(nblk(S.near_nrec, 4), near_blocks));
-    const NearArgs na{T.n,     S.near_nrec, (const NearRec *)S.near_rec, S.near_stream, S.xy,         S.nrm, S.logtab,
+    const NearArgs na{T.n,     S.near_nrec, S.near_rec, S.near_stream, S.xy,         S.nrm, S.logtab,
                       ws.qs,   S.bc == 2 ? -1.0 : 1.0, ws.near, S.bw.near_gx, S.bw.near_gy, out.qc};
     // walk 4 keeps each lane's targets and row sums in registers: single-vector passes only (the
     // others take walk 1)

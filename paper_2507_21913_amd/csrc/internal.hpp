@@ -64,10 +64,16 @@ void set_error(const char *fmt, ...);
         if (s_ != FMMHP_OK) return s_;       \
     } while (0)
 
-// Device allocations owned by one plan.
+// Device allocations owned by one plan.  Arrays share slabs (a plan holds some 90 arrays; a hipMalloc and
+// a hipFree for each took 5 of the 11 ms of a 200,000-point training step): a slab is twice as large as
+// everything allocated so far, from 1 to 64 MB; an array that does not fit one has an allocation of its
+// own.
 struct Arena {
-    std::vector<void *> ptrs;
-    int64_t bytes = 0;
+    std::vector<void *> ptrs;  // slabs and large arrays
+    int64_t bytes = 0;         // requested
+    int count = 0;             // arrays
+    char *cur = nullptr;       // the open slab
+    size_t left = 0;
     fmmhp_status alloc(void **p, size_t nbytes, const char *what);
     template <class T>
     fmmhp_status alloc_n(T **p, size_t n, const char *what) {
@@ -110,6 +116,14 @@ fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, 
 // the order (-1,-1) (0,-1) (1,-1) (-1,0) (1,0) (-1,1) (0,1) (1,1): nbr[8 * par.size()] on the host.
 fmmhp_status parent_colleagues(const Tree &T, const std::vector<int32_t> &par, std::vector<int32_t> &nbr,
                                hipStream_t stream);
+
+// Near-field record: up to 64 targets of one leaf and the leaf's source stream.
+constexpr int kNearPad = 192;    // stream entries read (and not used) past a segment's end
+struct NearRec {
+    int32_t ft, nt;      // first target, targets (at most 64)
+    int32_t nself, nfree, nimg, pad;  // points of the leaf, free sources in all, image ones
+    int64_t off;         // first entry of the stream
+};
 
 // Root square and impedance of one instance of a plan.
 struct InstInfo {
@@ -184,7 +198,7 @@ struct Sched {
     int64_t n_rpts = 0;
     int32_t *rpts = nullptr;        // sorted points whose leaf has image U entries
     int near_nrec = 0;              // near-field records (a leaf's targets, 64 at most) and, per leaf, the
-    void *near_rec = nullptr;       // sorted indices of its U points (its own, the other free ones, the images)
+    NearRec *near_rec = nullptr;       // sorted indices of its U points (its own, the other free ones, the images)
     int32_t *near_stream = nullptr;
     double2 *xy = nullptr;          // [n] sorted (x, y) pairs
     double2 *logtab = nullptr;      // near-field log table
@@ -288,6 +302,10 @@ fmmhp_status run_field(Arena &A, const Tree &T, Sched &S, const double *q, doubl
                        hipStream_t stream);
 // Clears n doubles on stream with a kernel (no memset node under graph capture).
 fmmhp_status zero_f64(double *p, int64_t n, hipStream_t stream);
+
+// Pair counts, image V entries, leaves, W-list and near-axis points, near-field records and streams, on
+// the device; vimg_off also to the host.
+fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t> &vimg_off, hipStream_t stream);
 
 // zsum_host: per-instance homogeneity sums copied to the host (the call synchronises), or null;
 // dlz_dev: (dl/dRe Z_k, dl/dIm Z_k) written on the device instead (no synchronisation), or null.

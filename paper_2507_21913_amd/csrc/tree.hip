@@ -43,20 +43,42 @@ fmmhp_status Arena::alloc(void **p, size_t nbytes, const char *what) {
     *p = nullptr;
     if (getenv("FMMHP_TEST_FAIL_ALLOC")) {
         long k = atol(getenv("FMMHP_TEST_FAIL_ALLOC"));
-        if (k > 0 && (long)ptrs.size() + 1 == k) {
+        if (k > 0 && (long)count + 1 == k) {
             set_error("allocation of %s (%zu bytes) failed (test hook)", what, nbytes);
             return FMMHP_ENOMEM;
         }
     }
-    hipError_t e = hipMalloc(p, nbytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        *p = nullptr;
-        set_error("hipMalloc of %s (%zu bytes) failed: %s", what, nbytes, hipGetErrorString(e));
-        return FMMHP_ENOMEM;
+    const size_t need = (nbytes + 255) / 256 * 256;
+    if (need > left) {
+        const size_t slab = std::min<size_t>((size_t)64 << 20, std::max<size_t>((size_t)1 << 20, 2 * (size_t)bytes));
+        bool own = need >= slab;
+        void *m = nullptr;
+        hipError_t e = hipMalloc(&m, own ? nbytes : slab);
+        if (e != hipSuccess && !own) {  // no room for a slab: the array alone
+            (void)hipGetLastError();
+            own = true;
+            e = hipMalloc(&m, nbytes);
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            set_error("hipMalloc of %s (%zu bytes) failed: %s", what, nbytes, hipGetErrorString(e));
+            return FMMHP_ENOMEM;
+        }
+        ptrs.push_back(m);
+        if (own) {
+            *p = m;
+        } else {
+            cur = (char *)m;
+            left = slab;
+        }
     }
-    ptrs.push_back(*p);
+    if (!*p) {
+        *p = cur;
+        cur += need;
+        left -= need;
+    }
     bytes += (int64_t)nbytes;
+    ++count;
     return FMMHP_OK;
 }
 
@@ -64,27 +86,42 @@ void Arena::release() {
     for (void *p : ptrs) (void)hipFree(p);
     ptrs.clear();
     bytes = 0;
+    count = 0;
+    cur = nullptr;
+    left = 0;
 }
 
-// RAII scratch for build-time temporaries (stream-ordered).
+// Build-time temporaries (stream-ordered), carved from slabs of at least `slab` bytes and given back
+// together at the end of the scope.
 struct Scratch {
     hipStream_t s;
+    size_t slab;
     std::vector<void *> ptrs;
-    explicit Scratch(hipStream_t st) : s(st) {}
+    char *cur = nullptr;
+    size_t left = 0;
+    explicit Scratch(hipStream_t st, size_t slab_ = (size_t)1 << 20) : s(st), slab(slab_) {}
     ~Scratch() {
         for (void *p : ptrs) (void)hipFreeAsync(p, s);
     }
     template <class T>
     fmmhp_status get(T **p, size_t n, const char *what) {
-        void *q = nullptr;
-        hipError_t e = hipMallocAsync(&q, (n ? n : 1) * sizeof(T), s);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            set_error("hipMallocAsync of %s failed: %s", what, hipGetErrorString(e));
-            return FMMHP_ENOMEM;
+        const size_t need = ((n ? n : 1) * sizeof(T) + 255) / 256 * 256;
+        if (need > left) {
+            void *q = nullptr;
+            const size_t bytes = std::max(need, slab);
+            hipError_t e = hipMallocAsync(&q, bytes, s);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                set_error("hipMallocAsync of %s failed: %s", what, hipGetErrorString(e));
+                return FMMHP_ENOMEM;
+            }
+            ptrs.push_back(q);
+            cur = (char *)q;
+            left = bytes;
         }
-        ptrs.push_back(q);
-        *p = (T *)q;
+        *p = (T *)cur;
+        cur += need;
+        left -= need;
         return FMMHP_OK;
     }
 };
@@ -98,14 +135,14 @@ constexpr int kScanThreads = 256;
 constexpr int kScanPer = 4;
 constexpr int kScanTile = kScanThreads * kScanPer;
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t *__restrict__ in,
-                                                            int32_t *__restrict__ out,
-                                                            int32_t *__restrict__ sums, int64_t n) {
-    __shared__ int32_t s[kScanThreads];
+template <class V>
+__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const V *__restrict__ in, V *__restrict__ out,
+                                                            V *__restrict__ sums, int64_t n) {
+    __shared__ V s[kScanThreads];
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)t * kScanPer;
-    int32_t v[kScanPer];
-    int32_t tot = 0;
+    V v[kScanPer];
+    V tot = 0;
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k) {
         v[k] = (base + k < n) ? in[base + k] : 0;
@@ -114,12 +151,12 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t *__res
     s[t] = tot;
     __syncthreads();
     for (int off = 1; off < kScanThreads; off <<= 1) {
-        int32_t a = (t >= off) ? s[t - off] : 0;
+        V a = (t >= off) ? s[t - off] : 0;
         __syncthreads();
         s[t] += a;
         __syncthreads();
     }
-    int32_t run = s[t] - tot;
+    V run = s[t] - tot;
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k) {
         if (base + k < n) out[base + k] = run;
@@ -128,38 +165,40 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t *__res
     if (t == kScanThreads - 1) sums[blockIdx.x] = s[t];
 }
 
-__global__ void k_scan_add(int32_t *__restrict__ out, const int32_t *__restrict__ offs, int64_t n) {
+template <class V>
+__global__ void k_scan_add(V *__restrict__ out, const V *__restrict__ offs, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) out[i] += offs[i / kScanTile];
     if (i == 0) out[n] = offs[(n + kScanTile - 1) / kScanTile];
 }
 
-__global__ void k_scan_single_total(int32_t *__restrict__ out, const int32_t *__restrict__ sums) {
+template <class V>
+__global__ void k_scan_single_total(V *__restrict__ out, const V *__restrict__ sums) {
     out[0] = 0;
     out[1] = sums[0];
 }
 
-static fmmhp_status exclusive_scan(const int32_t *in, int32_t *out, int64_t n, hipStream_t s) {
+template <class V>
+static fmmhp_status exclusive_scan(Scratch &sc, const V *in, V *out, int64_t n, hipStream_t s) {
     if (n <= 0) {
         // out[0] = 0
-        int32_t zero = 0;
-        FMMHP_HIP(hipMemcpyAsync(out, &zero, sizeof(int32_t), hipMemcpyHostToDevice, s));
+        V zero = 0;
+        FMMHP_HIP(hipMemcpyAsync(out, &zero, sizeof(V), hipMemcpyHostToDevice, s));
         FMMHP_HIP(hipStreamSynchronize(s));
         return FMMHP_OK;
     }
-    Scratch sc(s);
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    int32_t *sums = nullptr, *soffs = nullptr;
+    V *sums = nullptr, *soffs = nullptr;
     FMMHP_CHECK(sc.get(&sums, nb, "scan sums"));
     FMMHP_CHECK(sc.get(&soffs, nb + 1, "scan offsets"));
-    hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, out, sums, n);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_scan_tile<V>), dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, out, sums, n);
     FMMHP_HIP(hipGetLastError());
     if (nb == 1) {
-        hipLaunchKernelGGL(k_scan_single_total, dim3(1), dim3(1), 0, s, soffs, sums);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_scan_single_total<V>), dim3(1), dim3(1), 0, s, soffs, sums);
     } else {
-        FMMHP_CHECK(exclusive_scan(sums, soffs, nb, s));
+        FMMHP_CHECK(exclusive_scan(sc, sums, soffs, nb, s));
     }
-    hipLaunchKernelGGL(k_scan_add, dim3(nblocks(n, 256)), dim3(256), 0, s, out, soffs, n);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_scan_add<V>), dim3(nblocks(n, 256)), dim3(256), 0, s, out, soffs, n);
     FMMHP_HIP(hipGetLastError());
     return FMMHP_OK;
 }
@@ -369,9 +408,8 @@ __global__ __launch_bounds__(256) void k_scatter(const uint64_t *__restrict__ ki
     }
 }
 
-static fmmhp_status radix_sort(uint64_t *&keys, int32_t *&vals, uint64_t *keys_alt, int32_t *vals_alt,
+static fmmhp_status radix_sort(Scratch &sc, uint64_t *&keys, int32_t *&vals, uint64_t *keys_alt, int32_t *vals_alt,
                                int64_t n, hipStream_t s) {
-    Scratch sc(s);
     int32_t *tot = nullptr;
     FMMHP_CHECK(sc.get(&tot, 8 * 256, "digit totals"));
     FMMHP_HIP(hipMemsetAsync(tot, 0, 8 * 256 * sizeof(int32_t), s));
@@ -394,7 +432,7 @@ static fmmhp_status radix_sort(uint64_t *&keys, int32_t *&vals, uint64_t *keys_a
         if (trivial) continue;  // every key has the same digit: the pass is the identity
         hipLaunchKernelGGL(k_block_hist, dim3(nblk), dim3(256), 0, s, ka, n, 8 * d, hist, nblk);
         FMMHP_HIP(hipGetLastError());
-        FMMHP_CHECK(exclusive_scan(hist, offs, (int64_t)256 * nblk, s));
+        FMMHP_CHECK(exclusive_scan(sc, hist, offs, (int64_t)256 * nblk, s));
         hipLaunchKernelGGL(k_scatter, dim3(nblk), dim3(256), 0, s, ka, va, kb, vb, n, 8 * d, offs, nblk);
         FMMHP_HIP(hipGetLastError());
         std::swap(ka, kb);
@@ -718,13 +756,200 @@ fmmhp_status parent_colleagues(const Tree &T, const std::vector<int32_t> &par, s
 }
 
 // ---------------------------------------------------------------------------------------------
+// Tables read off the lists (list_tables)
+// ---------------------------------------------------------------------------------------------
+// Per box: image V entries, near-field sources (free, image) and records; the pair counts of the plan,
+// tot = {free near pairs, image near pairs, upper V pairs, image V pairs}; bad: a V entry that is not a
+// same-level offset of the interaction list.
+__global__ __launch_bounds__(256) void k_list_counts(TreeView t, int nbox, const int32_t *__restrict__ count,
+                                                     const int32_t *__restrict__ uoff, const int32_t *__restrict__ uent,
+                                                     const int32_t *__restrict__ voff, const int32_t *__restrict__ vent,
+                                                     int32_t *__restrict__ vimg, int64_t *__restrict__ nfree,
+                                                     int64_t *__restrict__ nimg, int64_t *__restrict__ len,
+                                                     int32_t *__restrict__ nrec, unsigned long long *__restrict__ tot,
+                                                     int32_t *__restrict__ bad) {
+    __shared__ unsigned long long st[4];
+    if (threadIdx.x < 4) st[threadIdx.x] = 0;
+    __syncthreads();
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < nbox) {
+        int64_t u[2] = {0, 0};
+        for (int e = uoff[b]; e < uoff[b + 1]; ++e) {
+            const int code = uent[e];
+            const int64_t c = count[code >> 1];
+            u[0] += (code & 1) ? 0 : c;
+            u[1] += (code & 1) ? c : 0;
+        }
+        int iv = 0;
+        const int l = t.level[b], v0 = voff[b], v1 = voff[b + 1];
+        for (int e = v0; e < v1; ++e) {
+            const int c = vent[e] >> 1, img = vent[e] & 1;
+            const int dx = t.bx[c] - t.bx[b], dy = (img ? (1 << l) - 1 - t.by[c] : t.by[c]) - t.by[b];
+            if (dx < -3 || dx > 3 || dy < -3 || dy > 3) atomicOr(bad, 1);
+            else if (img && dy > -1) atomicOr(bad, 2);
+            iv += img;
+        }
+        const bool leaf = t.leaf[b];
+        vimg[b] = iv;
+        nfree[b] = u[0];
+        nimg[b] = u[1];
+        len[b] = leaf ? u[0] + u[1] : 0;
+        nrec[b] = leaf ? (count[b] + 63) / 64 : 0;
+        const int64_t k = count[b];
+        if (u[0]) atomicAdd(&st[0], (unsigned long long)(k * u[0]));
+        if (u[1]) atomicAdd(&st[1], (unsigned long long)(k * u[1]));
+        if (v1 - v0 - iv) atomicAdd(&st[2], (unsigned long long)(v1 - v0 - iv));
+        if (iv) atomicAdd(&st[3], (unsigned long long)iv);
+    }
+    __syncthreads();
+    if (threadIdx.x < 4 && st[threadIdx.x]) atomicAdd(&tot[threadIdx.x], st[threadIdx.x]);
+}
+
+// Image V entries (source << 5 | offset slot), and the near-field records and source streams: a leaf's
+// own points, the other free U entries' in list order, the image ones'.
+__global__ __launch_bounds__(64) void k_list_fill(TreeView t, const int32_t *__restrict__ first,
+                                                  const int32_t *__restrict__ count, const int32_t *__restrict__ uoff,
+                                                  const int32_t *__restrict__ uent, const int32_t *__restrict__ voff,
+                                                  const int32_t *__restrict__ vent, const int32_t *__restrict__ vimg_off,
+                                                  int32_t *__restrict__ vimg_ent, const int64_t *__restrict__ nfree,
+                                                  const int64_t *__restrict__ nimg, const int64_t *__restrict__ soff,
+                                                  const int32_t *__restrict__ roff, NearRec *__restrict__ rec,
+                                                  int32_t *__restrict__ stream) {
+    const int b = blockIdx.x, lane = threadIdx.x;
+    if (lane == 0 && vimg_off[b + 1] > vimg_off[b]) {
+        int32_t *out = vimg_ent + vimg_off[b];
+        const int l = t.level[b];
+        for (int e = voff[b]; e < voff[b + 1]; ++e) {
+            if (!(vent[e] & 1)) continue;
+            const int c = vent[e] >> 1;
+            const int dx = t.bx[c] - t.bx[b], dy = (1 << l) - 1 - t.by[c] - t.by[b];
+            *out++ = (c << 5) | ((dy + 3) * 7 + dx + 3);
+        }
+    }
+    if (!t.leaf[b]) return;
+    const int f = first[b], n = count[b];
+    for (int k = lane; k < (n + 63) / 64; k += 64)
+        rec[roff[b] + k] = NearRec{f + 64 * k, min(64, n - 64 * k), n, (int32_t)nfree[b], (int32_t)nimg[b], 0, soff[b]};
+    int32_t *out = stream + soff[b];
+    for (int k = lane; k < n; k += 64) out[k] = f + k;
+    out += n;
+    for (int img = 0; img < 2; ++img)
+        for (int e = uoff[b]; e < uoff[b + 1]; ++e) {
+            const int code = uent[e], c = code >> 1, m = count[c], fc = first[c];
+            if ((code & 1) != img || code == 2 * b) continue;
+            for (int k = lane; k < m; k += 64) out[k] = fc + k;
+            out += m;
+        }
+}
+
+__global__ void k_compact(int64_t n, const int32_t *__restrict__ flag, const int32_t *__restrict__ pos,
+                          int32_t *__restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n && flag[i]) out[pos[i]] = (int32_t)i;
+}
+
+// Sorted points whose leaf has a W list (w) and near-axis points (r: image sources in the U list).
+__global__ void k_point_flags(int64_t n, const int32_t *__restrict__ leaf_of, const int32_t *__restrict__ woff,
+                              const int64_t *__restrict__ nimg, int32_t *__restrict__ w, int32_t *__restrict__ r) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int b = leaf_of[i];
+    w[i] = woff[b + 1] > woff[b];
+    r[i] = nimg[b] > 0;
+}
+
+__global__ void k_totals(const int32_t *a, const int32_t *b, const int32_t *c, const int32_t *d, const int64_t *e,
+                         int64_t *__restrict__ out) {
+    out[0] = *a;
+    out[1] = *b;
+    out[2] = *c;
+    out[3] = *d;
+    out[4] = *e;
+}
+
+fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t> &vimg_off_h, hipStream_t s) {
+    const int nb = T.nbox;
+    const int64_t n = T.n;
+    Scratch sc(s, (size_t)80 * (size_t)nb + (size_t)20 * (size_t)n + ((size_t)1 << 20));
+    int32_t *dlev = nullptr, *vimg = nullptr, *nrec = nullptr, *roff = nullptr, *bad = nullptr, *lpos = nullptr,
+            *wf = nullptr, *rf = nullptr, *wpos = nullptr, *rpos = nullptr;
+    int64_t *nfree = nullptr, *nimg = nullptr, *len = nullptr, *soff = nullptr, *tot = nullptr;
+    FMMHP_CHECK(sc.get(&dlev, 33, "level starts"));
+    FMMHP_CHECK(sc.get(&vimg, nb, "image V counts"));
+    FMMHP_CHECK(sc.get(&nrec, nb, "record counts"));
+    FMMHP_CHECK(sc.get(&roff, nb + 1, "record offsets"));
+    FMMHP_CHECK(sc.get(&lpos, nb + 1, "leaf positions"));
+    FMMHP_CHECK(sc.get(&nfree, nb, "free sources"));
+    FMMHP_CHECK(sc.get(&nimg, nb, "image sources"));
+    FMMHP_CHECK(sc.get(&len, nb, "stream lengths"));
+    FMMHP_CHECK(sc.get(&soff, nb + 1, "stream offsets"));
+    FMMHP_CHECK(sc.get(&tot, 16, "totals"));
+    FMMHP_CHECK(sc.get(&wf, n, "W flags"));
+    FMMHP_CHECK(sc.get(&rf, n, "near-axis flags"));
+    FMMHP_CHECK(sc.get(&wpos, n + 1, "W positions"));
+    FMMHP_CHECK(sc.get(&rpos, n + 1, "near-axis positions"));
+    bad = (int32_t *)(tot + 15);
+    FMMHP_CHECK(A.alloc_n(&S.vimg_off, (size_t)nb + 1, "vimg_off"));
+    FMMHP_HIP(hipMemcpyAsync(dlev, T.lev_start.data(), 33 * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    FMMHP_HIP(hipMemsetAsync(tot, 0, 16 * sizeof(int64_t), s));
+    TreeView tv{T.level, T.bx, T.by, T.parent, T.leaf, T.child_first, T.nchild, T.inst, T.prefix, dlev, T.depth,
+                T.lbits};
+    hipLaunchKernelGGL(k_list_counts, dim3(nblocks(nb, 256)), dim3(256), 0, s, tv, nb, T.count, T.off[0], T.ent[0],
+                       T.off[1], T.ent[1], vimg, nfree, nimg, len, nrec, (unsigned long long *)tot, bad);
+    hipLaunchKernelGGL(k_point_flags, dim3(nblocks(n, 256)), dim3(256), 0, s, n, T.leaf_of, T.off[2], nimg, wf, rf);
+    FMMHP_HIP(hipGetLastError());
+    FMMHP_CHECK(exclusive_scan(sc, vimg, S.vimg_off, nb, s));
+    FMMHP_CHECK(exclusive_scan(sc, nrec, roff, nb, s));
+    FMMHP_CHECK(exclusive_scan(sc, T.leaf, lpos, nb, s));
+    FMMHP_CHECK(exclusive_scan(sc, len, soff, nb, s));
+    FMMHP_CHECK(exclusive_scan(sc, wf, wpos, n, s));
+    FMMHP_CHECK(exclusive_scan(sc, rf, rpos, n, s));
+    hipLaunchKernelGGL(k_totals, dim3(1), dim3(1), 0, s, S.vimg_off + nb, roff + nb, wpos + n, rpos + n, soff + nb, tot + 4);
+    FMMHP_HIP(hipGetLastError());
+    int64_t h[16];
+    FMMHP_HIP(hipMemcpyAsync(h, tot, sizeof(h), hipMemcpyDeviceToHost, s));
+    vimg_off_h.resize((size_t)nb + 1);
+    FMMHP_HIP(hipMemcpyAsync(vimg_off_h.data(), S.vimg_off, ((size_t)nb + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    FMMHP_HIP(hipStreamSynchronize(s));
+    if (h[15]) {
+        set_error((h[15] & 1) ? "internal: V entry outside the 7x7 offset block"
+                              : "internal: image V entry above its target");
+        return FMMHP_EUNSUPPORTED;
+    }
+    S.p2p_pairs[0] = h[0];
+    S.p2p_pairs[1] = h[1];
+    S.m2l_pairs[0] = h[2];
+    S.m2l_pairs[1] = h[3];
+    S.near_nrec = (int)h[5];
+    S.n_wpts = h[6];
+    S.n_rpts = h[7];
+    FMMHP_CHECK(A.alloc_n(&S.vimg_ent, (size_t)h[4], "vimg_ent"));
+    FMMHP_CHECK(A.alloc_n(&S.near_rec, (size_t)h[5], "near-field records"));
+    FMMHP_CHECK(A.alloc_n(&S.near_stream, (size_t)h[8] + kNearPad, "near-field source streams"));
+    FMMHP_CHECK(A.alloc_n(&S.leaves, (size_t)T.nleaf, "leaves"));
+    FMMHP_CHECK(A.alloc_n(&S.wpts, (size_t)h[6], "W-list targets"));
+    FMMHP_CHECK(A.alloc_n(&S.rpts, (size_t)h[7], "near-axis targets"));
+    hipLaunchKernelGGL(k_list_fill, dim3((unsigned)nb), dim3(64), 0, s, tv, T.first, T.count, T.off[0], T.ent[0],
+                       T.off[1], T.ent[1], S.vimg_off, S.vimg_ent, nfree, nimg, soff, roff, S.near_rec, S.near_stream);
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, s, S.near_stream + h[8], (int64_t)kNearPad, 0);
+    hipLaunchKernelGGL(k_compact, dim3(nblocks(nb, 256)), dim3(256), 0, s, (int64_t)nb, T.leaf, lpos, S.leaves);
+    if (S.n_wpts > 0)
+        hipLaunchKernelGGL(k_compact, dim3(nblocks(n, 256)), dim3(256), 0, s, n, wf, wpos, S.wpts);
+    if (S.n_rpts > 0)
+        hipLaunchKernelGGL(k_compact, dim3(nblocks(n, 256)), dim3(256), 0, s, n, rf, rpos, S.rpts);
+    FMMHP_HIP(hipGetLastError());
+    return FMMHP_OK;
+}
+
+// ---------------------------------------------------------------------------------------------
 // Driver
 // ---------------------------------------------------------------------------------------------
 fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, const double *x, const double *y,
                         const double *img_x, const double *img_y, int64_t src_end, int leaf_size, int max_level,
                         hipStream_t s) {
-    Scratch sc(s);
     const int64_t n = inst_off[n_inst];
+    // keys, indices and per-point flags take 52 bytes a point, the boxes and scans a few more
+    Scratch sc(s, (size_t)64 * (size_t)n + ((size_t)1 << 20));
     T.n = n;
     T.n_inst = n_inst;
     T.lbits = n_inst == 1 ? kLBits : kLBitsForest;
@@ -802,7 +1027,7 @@ fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, 
     FMMHP_HIP(hipGetLastError());
     uint64_t *ks = keys;
     int32_t *vs = idx;
-    FMMHP_CHECK(radix_sort(ks, vs, keys2, idx2, n, s));
+    FMMHP_CHECK(radix_sort(sc, ks, vs, keys2, idx2, n, s));
 
     FMMHP_CHECK(A.alloc_n(&T.perm, n, "perm"));
     FMMHP_CHECK(A.alloc_n(&T.xs, n, "sorted x"));
@@ -817,8 +1042,8 @@ fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, 
     int32_t *act = nullptr, *flag = nullptr, *pos = nullptr, *nsplit = nullptr;
     FMMHP_CHECK(sc.get(&act, n, "act"));
     FMMHP_CHECK(sc.get(&flag, n, "flags"));
-    FMMHP_CHECK(sc.get(&pos, n + 1, "positions"));
-    FMMHP_CHECK(sc.get(&nsplit, 1, "split counter"));
+    FMMHP_CHECK(sc.get(&pos, n + 2, "positions"));
+    nsplit = pos + n + 1;  // beside the scan's total: both come to the host in one copy
     hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(n, 256)), dim3(256), 0, s, act, n, kRoot);
     FMMHP_HIP(hipGetLastError());
 
@@ -843,14 +1068,16 @@ fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, 
     T.lev_start.assign(2, 0);  // lev_start[0] unused, lev_start[1] = 0
     int total = 0;
     int level = 0;
-    for (level = 1; level <= max_level; ++level) {
-        hipLaunchKernelGGL(k_level_flags, dim3(nblocks(n, 256)), dim3(256), 0, s, ks, act, n, level, T.lbits, flag);
+    auto level_boxes = [&](int l) -> fmmhp_status {  // first points of the level's boxes and their numbers
+        hipLaunchKernelGGL(k_level_flags, dim3(nblocks(n, 256)), dim3(256), 0, s, ks, act, n, l, T.lbits, flag);
         FMMHP_HIP(hipGetLastError());
-        FMMHP_CHECK(exclusive_scan(flag, pos, n, s));
-        int32_t nb = 0;
-        FMMHP_HIP(hipMemcpyAsync(&nb, pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        FMMHP_HIP(hipStreamSynchronize(s));
-        if (nb == 0) break;
+        return exclusive_scan(sc, flag, pos, n, s);
+    };
+    FMMHP_CHECK(level_boxes(1));
+    int32_t nb = 0;
+    FMMHP_HIP(hipMemcpyAsync(&nb, pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    FMMHP_HIP(hipStreamSynchronize(s));
+    for (level = 1; level <= max_level && nb > 0; ++level) {
         if ((int64_t)total + nb > cap) {
             // grow: copy existing arrays
             int ncap = (int)std::min<int64_t>(0x7fffffff, std::max<int64_t>(2ll * cap, (int64_t)total + nb));
@@ -880,12 +1107,16 @@ fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, 
         hipLaunchKernelGGL(k_update_act, dim3(nblocks(n, 256)), dim3(256), 0, s, flag, pos, n, total, b_leaf,
                            act, T.leaf_of);
         FMMHP_HIP(hipGetLastError());
-        int32_t hsplit = 0;
-        FMMHP_HIP(hipMemcpyAsync(&hsplit, nsplit, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        // the next level's boxes are counted before the host knows whether there is one: one
+        // synchronisation per level
+        if (level < max_level) FMMHP_CHECK(level_boxes(level + 1));
+        int32_t next[2] = {0, 0};  // boxes of the next level, boxes of this one that split
+        FMMHP_HIP(hipMemcpyAsync(next, pos + n, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
         FMMHP_HIP(hipStreamSynchronize(s));
         total += nb;
         T.lev_start.push_back(total);
-        if (hsplit == 0) {
+        nb = next[0];
+        if (next[1] == 0) {
             ++level;
             break;
         }
@@ -944,7 +1175,7 @@ fmmhp_status build_tree(Arena &A, Tree &T, int n_inst, const int64_t *inst_off, 
     FMMHP_HIP(hipGetLastError());
     for (int li = 0; li < 4; ++li) {
         FMMHP_CHECK(A.alloc_n(&T.off[li], (size_t)nbx + 1, "list offsets"));
-        FMMHP_CHECK(exclusive_scan(cnt + (size_t)li * nbx, T.off[li], nbx, s));
+        FMMHP_CHECK(exclusive_scan(sc, cnt + (size_t)li * nbx, T.off[li], nbx, s));
     }
     int32_t tot[4];
     for (int li = 0; li < 4; ++li)
