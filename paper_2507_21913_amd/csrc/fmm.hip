@@ -50,6 +50,7 @@
 #include "special.hpp"
 #include "m2l_pw.hpp"
 #include "updown.hpp"
+#include "p2l.hpp"
 
 namespace fmmhp {
 
@@ -802,47 +803,24 @@ __global__ void k_zero_lam(int lo, int hi, int nbox, int ncoef, int nrow, cplx *
     Lam[r * nbox + b] = mk(0.0, 0.0);
 }
 
-// Lane moves within a wave by DPP (no LDS traffic, a few cycles), for doubles as two 32-bit halves.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_move(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-
-// Lane l's value of x in every lane (l uniform; reads the lane's register whatever the exec mask).
-__device__ __forceinline__ double read_lane_f64(double x, int l) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(x), l);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
-    return __hiloint2double(hi, lo);
-}
-
-// Sum over aligned groups of IA = 1, 2, 4 or 8 consecutive lanes (every lane of a group gets it).
-__device__ __forceinline__ double lane_group_sum(double s, int IA) {
-    if (IA >= 2) s += dpp_move<0xB1, 0xF>(s);   // quad_perm [1, 0, 3, 2]
-    if (IA >= 4) s += dpp_move<0x4E, 0xF>(s);   // quad_perm [2, 3, 0, 1]
-    if (IA >= 8) s += dpp_move<0x141, 0xF>(s);  // row_half_mirror
-    return s;
-}
-
 // ---------------------------------------------------------------------------------------------
-// P2L (X list): sources of a coarse leaf straight into the local of a finer box.  A wave takes a
-// group of X boxes of one level (consecutive boxes whose X sources total at most 64, or one larger
-// box) and walks the group's sources in chunks of 64, one source per lane in the order (box, list
-// entry, point).  Each lane computes its source's terms for unit charge into LDS, a phase of
-// coefficients at a time: 16 when the chunk has no reaction rows (the G local's terms then equal the
-// H local's), else 8 of every local.  With one vector, lane (k, g) sums coefficient k of each box of
-// the chunk over the box's rows g, g + G, ... (G = 4 or 8) times the charges, and the G partial sums
-// meet by lane moves; with several, lane (k, vector group) forms the same G partial sums itself and
-// joins them in the same order.  The sums are added to the locals by atomics that return nothing.
+// P2L (X list) of rows with reaction terms: image sources of a coarse leaf, log and reaction part, into
+// the local of a finer box (the other rows: k_p2l).  A wave takes a group of such boxes of one level
+// (consecutive boxes whose rows total at most 64, or one larger box) and walks the group's rows in
+// chunks of 64, one source per lane in the order (box, list entry, point).  Each lane computes its
+// source's terms for unit charge into LDS, eight coefficients of every local at a time.  With one
+// vector, lane (k, g) sums coefficient k of each box of the chunk over the box's rows g, g + 8, ...
+// times the charges, and the partial sums meet by lane moves; with several, lane (k, vector group)
+// forms the same partial sums itself and joins them in the same order.  The sums are added to the
+// locals by atomics that return nothing.
 // Dipole sources (DIP) take the derivative of these contributions along the source normal: the log
 // local is holomorphic in d = z_j - c_b (upper box) or in conj(z_j) - c_b (image), so the derivative
 // is nu d/dd (nu = n_x + i n_y, or its conjugate for the image), and for the reaction local
 // n_j . grad_{r_j} [n! rho^n I_n] = -(1/rho) i conj(nu) K_{n+1} (d_X I_n = i (n+1) I_{n+1},
 // d_Y I_n = -(n+1) I_{n+1}, from eq. (generalintegral)); the same holds for the mirrored G local.
 // ---------------------------------------------------------------------------------------------
-constexpr int kP2LPhase = 8;   // coefficients per LDS phase with reaction rows (16 without)
-constexpr int kP2LRows = 72;   // row stride of the 8-coefficient layout (68 in the 16-coefficient one)
+constexpr int kP2LPhase = 8;   // coefficients per LDS phase
+constexpr int kP2LRows = 72;   // row stride (65 with several vectors): an access's 16 lanes on distinct banks
 
 // Plan-time tables of the P2L: each group entry's first source point (w), and each X box's centre,
 // half side and instance, so that a chunk's loads depend only on its group entries.
@@ -851,12 +829,12 @@ __global__ void k_xgent_first(int64_t m, int4 *__restrict__ gent, const int32_t 
     if (e < m) gent[e].w = first[gent[e].x >> 1];
 }
 
-__global__ void k_xgeo(int nx, const int32_t *__restrict__ xbox, const InstInfo *__restrict__ ii,
+__global__ void k_xgeo(int nx, const int32_t *__restrict__ xbox, int stride, const InstInfo *__restrict__ ii,
                        const int32_t *__restrict__ inst, const int32_t *__restrict__ level,
                        const int32_t *__restrict__ bx, const int32_t *__restrict__ by, double4 *__restrict__ xgeo) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nx) return;
-    const int b = xbox[i], l = level[b], k = inst[b];
+    const int b = xbox[(int64_t)i * stride], l = level[b], k = inst[b];
     const Geo g = geo_of(ii, k);
     const cplx cb = centre_of(g, l, bx[b], by[b]);
     xgeo[i] = make_double4(cb.re, cb.im, 0.5 * side_of(g, l), (double)k);
@@ -868,8 +846,7 @@ __global__ void k_xgeo(int nx, const int32_t *__restrict__ xbox, const InstInfo 
 // so that every vector's result is bitwise the one of a single-vector pass.
 template <int PB, int NV, int G, int VPL>
 __device__ __forceinline__ void p2l_slot_vectors(const cplx *Ck, const double (*sq)[NV], int r0, int r1, int vg,
-                                                 int m, int ld0, int ld1, int nloc, int nbox, int bsl,
-                                                 cplx *__restrict__ Lam) {
+                                                 int m, int ld, int nloc, int nbox, int bsl, cplx *__restrict__ Lam) {
     constexpr int P1 = PB + 1;
     cplx pg[G][VPL];
 #pragma unroll
@@ -906,24 +883,21 @@ __device__ __forceinline__ void p2l_slot_vectors(const cplx *Ck, const double (*
         if (v >= NV) continue;
         cplx a = (pg[0][u] + pg[1][u]) + (pg[2][u] + pg[3][u]);
         if constexpr (G == 8) a = a + ((pg[4][u] + pg[5][u]) + (pg[6][u] + pg[7][u]));
-        for (int ld = ld0; ld < ld1; ++ld) {
-            cplx *dst = Lam + (((int64_t)v * nloc + ld) * P1 + m) * nbox + bsl;
-            unsafeAtomicAdd(&dst->re, a.re);
-            unsafeAtomicAdd(&dst->im, a.im);
-        }
+        cplx *dst = Lam + (((int64_t)v * nloc + ld) * P1 + m) * nbox + bsl;
+        unsafeAtomicAdd(&dst->re, a.re);
+        unsafeAtomicAdd(&dst->im, a.im);
     }
 }
 
 template <int PB, bool DIP, int NV>
-__global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, const int32_t *__restrict__ inst,
+__global__ __launch_bounds__(64) void k_p2l_react(const InstInfo *__restrict__ ii, const int32_t *__restrict__ inst,
                                             int nloc, const int4 *__restrict__ grp, const int4 *__restrict__ gent,
                                             const int32_t *__restrict__ xbox, const double4 *__restrict__ xgeo,
                                             int nbox, const double *__restrict__ xs, const double *__restrict__ ys,
                                             const double *__restrict__ qs, const double2 *__restrict__ nrm,
                                             const double *__restrict__ fact, cplx *__restrict__ Lam) {
     constexpr int P1 = PB + 1;
-    // [local][coefficient in phase][source row], 2 x 8 coefficients or 1 x 16 (row strides 72 and 68
-    // with one vector, 65 with several)
+    // [local][coefficient in phase][source row]
     __shared__ cplx C[2 * kP2LPhase * kP2LRows];
     __shared__ double sq[64][NV];
     const int lane = threadIdx.x;
@@ -962,7 +936,6 @@ __global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, con
         const cplx cb = mk(bg.x, bg.y);
         const double rho = bg.z;
         const int k = (int)bg.w;
-        const bool rx = act && img && ii[k].react;
         cplx sig = mk(0.0, 0.0), pw = mk(0.0, 0.0), l0 = mk(0.0, 0.0);
         double sgn = 0.0;
         cplx sw[2], Fr[2], Kr[2], zr = mk(0.0, 0.0), cn = mk(0.0, 0.0);
@@ -984,7 +957,7 @@ __global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, con
                 l0 = (sgn * kInv4Pi) * clog_(-d);
                 pw = sig;
             }
-            if (rx) {
+            {
                 // reaction S2L (eq. (LEcoefficients)) re-expanded in powers of (z - c_b):
                 // lambda_n += i^n n! rho^n q I_n(x_c - x_j, y_c + y_j)  (G: conj of I_n(-X, Y))
                 const double X = cb.re - xs[j], Y = cb.im + ys[j];
@@ -1011,22 +984,16 @@ __global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, con
         // box slots present in this chunk
         const int sa = __builtin_amdgcn_readlane(s, 0);
         const int sb = __builtin_amdgcn_readlane(s, K - F < 64 ? K - F - 1 : 63);
-        // Without reaction rows the G terms equal the H terms: one set of terms, one sum added to
-        // every local, 16 coefficients a phase summed by 4 lanes each.  With reaction rows, every
-        // local has its own terms, 8 coefficients a phase summed by 8 lanes each.  Row strides keep
-        // the 16 lanes of an LDS access on distinct banks in either layout.
-        const bool mixed = __ballot(rx) != 0;
-        const int ph = mixed ? kP2LPhase : 2 * kP2LPhase;
-        const int nl = mixed ? nloc : 1;
-        const int G = mixed ? 8 : 4;
-        const int rs = NV > 1 ? kP2LRows - 7 : mixed ? kP2LRows : kP2LRows - 4;
-        const int gq = lane & (G - 1), kq = mixed ? lane >> 3 : lane >> 2;
+        constexpr int ph = kP2LPhase, G = 8;
+        const int nl = nloc;
+        constexpr int rs = NV > 1 ? kP2LRows - 7 : kP2LRows;
+        const int gq = lane & (G - 1), kq = lane >> 3;
         for (int m0 = 0; m0 <= PB; m0 += ph) {
             if (act) {
 #pragma unroll
-                for (int kk = 0; kk < 2 * kP2LPhase; ++kk) {
+                for (int kk = 0; kk < ph; ++kk) {
                     const int m = m0 + kk;
-                    if (kk == ph || m > PB) break;
+                    if (m > PB) break;
                     cplx t;
                     if (DIP) {
                         t = read_lane_f64(fact_l, m) * pw;
@@ -1041,15 +1008,13 @@ __global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, con
                     for (int lc = 0; lc < 2; ++lc) {
                         if (lc == nl) break;
                         cplx u = t;
-                        if (rx) {
-                            const int n = DIP ? m + 1 : m;  // order of I_n this coefficient takes
-                            if (n > 0) {
-                                Fr[lc] = Fr[lc] * sw[lc] * (n > 1 ? (double)(n - 1) : 1.0);  // (n-1)! sw^n
-                                Kr[lc] = Fr[lc] * kInv2Pi + zr * Kr[lc];
-                            }
-                            const cplx kn = mul_ipow(lc == 0 ? Kr[lc] : conj(Kr[lc]), n);
-                            u += DIP ? cn * kn : kn;
+                        const int n = DIP ? m + 1 : m;  // order of I_n this coefficient takes
+                        if (n > 0) {
+                            Fr[lc] = Fr[lc] * sw[lc] * (n > 1 ? (double)(n - 1) : 1.0);  // (n-1)! sw^n
+                            Kr[lc] = Fr[lc] * kInv2Pi + zr * Kr[lc];
                         }
+                        const cplx kn = mul_ipow(lc == 0 ? Kr[lc] : conj(Kr[lc]), n);
+                        u += DIP ? cn * kn : kn;
                         C[(lc * ph + kk) * rs + lane] = u;
                     }
                 }
@@ -1062,17 +1027,10 @@ __global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, con
                 const int bsl = __builtin_amdgcn_readlane(b, r0);  // the slot's box, from its first row
                 for (int lc = 0; lc < nl; ++lc) {
                     if constexpr (NV > 1) {
-                        // lane (coefficient, vector group); row stride 65: the 16 coefficient rows
-                        // of an access fall on distinct banks
+                        // lane (coefficient, vector group)
                         const int kv = lane & (ph - 1), vg = lane / ph;
-                        const cplx *Cv = C + (lc * ph + kv) * rs;
-                        const int ld0 = mixed ? lc : 0, ld1 = mixed ? lc + 1 : nloc;
-                        if (mixed)
-                            p2l_slot_vectors<PB, NV, 8, (NV + 7) / 8>(Cv, sq, r0, r1, vg, m0 + kv, ld0, ld1, nloc,
-                                                                       nbox, bsl, Lam);
-                        else
-                            p2l_slot_vectors<PB, NV, 4, (NV + 3) / 4>(Cv, sq, r0, r1, vg, m0 + kv, ld0, ld1, nloc,
-                                                                       nbox, bsl, Lam);
+                        p2l_slot_vectors<PB, NV, 8, (NV + 7) / 8>(C + (lc * ph + kv) * rs, sq, r0, r1, vg, m0 + kv, lc,
+                                                                  nloc, nbox, bsl, Lam);
                         continue;
                     }
                     const cplx *Ck = C + (lc * ph + kq) * rs;
@@ -1107,14 +1065,12 @@ __global__ __launch_bounds__(64) void k_p2l(const InstInfo *__restrict__ ii, con
                     // only this wave adds to the box's locals here, one lane per coefficient in
                     // program order, so the sums stay deterministic; the adds return nothing and the
                     // wave does not wait for them
-                    if (gq == 0 && m <= PB && kq < ph) {
-                        for (int ld = mixed ? lc : 0; ld < (mixed ? lc + 1 : nloc); ++ld) {
+                    if (gq == 0 && m <= PB) {
 #pragma unroll
-                            for (int v = 0; v < NV; ++v) {
-                                cplx *dst = Lam + (((int64_t)v * nloc + ld) * P1 + m) * nbox + bsl;
-                                unsafeAtomicAdd(&dst->re, acc[v].re);
-                                unsafeAtomicAdd(&dst->im, acc[v].im);
-                            }
+                        for (int v = 0; v < NV; ++v) {
+                            cplx *dst = Lam + (((int64_t)v * nloc + lc) * P1 + m) * nbox + bsl;
+                            unsafeAtomicAdd(&dst->re, acc[v].re);
+                            unsafeAtomicAdd(&dst->im, acc[v].im);
                         }
                     }
                 }
@@ -2732,44 +2688,85 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
     FMMHP_CHECK(to_dev(A, &S.tile_slot, tslot, "tile slots", s));
     FMMHP_CHECK(to_dev(A, &S.tile_mask, tmask, "tile masks", s));
 
-    // X-list targets
-    std::vector<int32_t> xb;
-    if (T.len[3] > 0)
-        for (int b = 0; b < nbox; ++b)
-            if (xoff[b + 1] > xoff[b]) xb.push_back(b);
-    S.nxbox = (int)xb.size();
-    FMMHP_CHECK(to_dev(A, &S.xbox, xb, "xbox", s));
-    // P2L groups: consecutive X boxes of a level while their sources total at most one chunk of 64;
-    // per group its list entries that hold sources, {code, box slot, first row}, in row order
+    // X list.  Rows without reaction terms: a slot per box {box, rows, upper rows, 0} and its row stream,
+    // the boxes of 64 neighbours of a level sorted by their rows.  Rows with them (images, Robin): groups
+    // of consecutive boxes of a level while their rows total at most one chunk of 64; per group its list
+    // entries that hold sources, {code, box slot, first row}, in row order.
     {
-        std::vector<int4> grp, gent;
+        std::vector<int32_t> xb;
+        std::vector<int4> slot, grp, gent, sent;
+        std::vector<int64_t> row0;
+        int64_t rows = 0;
+        S.xslot_lev.assign(T.depth + 2, 0);
         S.xgrp_lev.assign(T.depth + 2, 0);
         int l = 0;
-        for (int i = 0; i < (int)xb.size(); ++i) {
-            const int b = xb[i];
-            int kb = 0;
-            for (int e = xoff[b]; e < xoff[b + 1]; ++e) kb += cnt[xent[e] >> 1];
-            const bool new_level = level[b] != l;
-            while (level[b] > l) S.xgrp_lev[++l] = (int)grp.size();
-            if (new_level || grp.empty() || grp.back().y + kb > 64)
-                grp.push_back(make_int4(i, 0, (int)gent.size(), 0));
+        size_t lev0 = 0;  // first slot of the level
+        auto next_level = [&]() {
+            for (size_t c = lev0; c < slot.size(); c += kP2LChunk) {
+                const size_t n = std::min<size_t>(kP2LChunk, slot.size() - c);
+                std::vector<std::pair<int4, int64_t>> t(n);
+                for (size_t i = 0; i < n; ++i) t[i] = {slot[c + i], row0[c + i]};
+                std::stable_sort(t.begin(), t.end(), [](const auto &p, const auto &q) { return p.first.y > q.first.y; });
+                for (size_t i = 0; i < n; ++i) slot[c + i] = t[i].first, row0[c + i] = t[i].second;
+            }
+            lev0 = slot.size();
+            S.xslot_lev[++l] = (int)slot.size();
+            S.xgrp_lev[l] = (int)grp.size();
+        };
+        for (int b = 0; T.len[3] > 0 && b < nbox; ++b) {
+            if (xoff[b + 1] == xoff[b]) continue;
+            while (level[b] > l) next_level();
+            int k[2] = {0, 0}, kr = 0;  // rows of the slot (upper, image) and of the group
+            const int64_t first_row = rows;
+            for (int img = 0; img < 2; ++img)
+                for (int e = xoff[b]; e < xoff[b + 1]; ++e) {
+                    const int c = cnt[xent[e] >> 1];
+                    if ((xent[e] & 1) != img || c == 0) continue;
+                    if (img && react) {
+                        kr += c;
+                        continue;
+                    }
+                    sent.push_back(make_int4(xent[e] >> 1, 0, (int)(uint32_t)rows, (int)(rows >> 32)));
+                    rows += c;
+                    k[img] += c;
+                }
+            if (rows > first_row) {
+                slot.push_back(make_int4(b, k[0] + k[1], k[0], 0));
+                row0.push_back(first_row);
+            }
+            if (kr == 0) continue;
+            if (S.xgrp_lev[l] == (int)grp.size() || grp.back().y + kr > 64)
+                grp.push_back(make_int4((int)xb.size(), 0, (int)gent.size(), 0));
             int4 &g = grp.back();
             for (int e = xoff[b]; e < xoff[b + 1]; ++e) {
-                const int k = cnt[xent[e] >> 1];
-                if (k == 0) continue;
-                gent.push_back(make_int4(xent[e], i - g.x, g.y, 0));
-                g.y += k;
+                const int c = cnt[xent[e] >> 1];
+                if (!(xent[e] & 1) || c == 0) continue;
+                gent.push_back(make_int4(xent[e], (int)xb.size() - g.x, g.y, 0));
+                g.y += c;
             }
+            xb.push_back(b);
         }
-        while (l < T.depth + 1) S.xgrp_lev[++l] = (int)grp.size();
+        while (l < T.depth + 1) next_level();
         grp.push_back(make_int4((int)xb.size(), 0, (int)gent.size(), 0));
+        S.nxbox = (int)xb.size();
+        S.nxslot = (int)slot.size();
+        FMMHP_CHECK(to_dev(A, &S.xbox, xb, "P2L reaction boxes", s));
         FMMHP_CHECK(to_dev(A, &S.xgrp, grp, "P2L groups", s));
         FMMHP_CHECK(to_dev(A, &S.xgent, gent, "P2L group entries", s));
         FMMHP_CHECK(A.alloc_n(&S.xgeo, xb.size(), "P2L box geometry"));
         if (!gent.empty())
             hipLaunchKernelGGL(k_xgent_first, dim3(nblk((int64_t)gent.size(), 256)), dim3(256), 0, s,
                                (int64_t)gent.size(), S.xgent, T.first);
-        FMMHP_HIP(hipGetLastError());  // (xgeo is filled once the instance table is on the device)
+        FMMHP_CHECK(to_dev(A, &S.xslot, slot, "P2L slots", s));
+        FMMHP_CHECK(to_dev(A, &S.xrow0, row0, "P2L rows", s));
+        FMMHP_CHECK(A.alloc_n(&S.xsgeo, slot.size(), "P2L slot geometry"));
+        FMMHP_CHECK(A.alloc_n(&S.xstream, (size_t)rows, "P2L source streams"));
+        int4 *d_sent = nullptr;
+        FMMHP_CHECK(to_dev(A, &d_sent, sent, "P2L entries", s));
+        if (!sent.empty())
+            hipLaunchKernelGGL(k_p2l_rows, dim3(nblk((int64_t)sent.size(), 256)), dim3(256), 0, s,
+                               (int64_t)sent.size(), d_sent, T.first, T.count, S.xstream);
+        FMMHP_HIP(hipGetLastError());  // (the geometry is filled once the instance table is on the device)
     }
     // deep split: the finest levels holding at least half of the M2L tiles run on a second stream
     // as soon as their multipoles exist, beside the rest of the upward pass
@@ -2846,11 +2843,14 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         std::vector<InstInfo> ii(T.n_inst);
         for (int k = 0; k < T.n_inst; ++k) ii[k] = InstInfo{T.inst_xlo[k], T.inst_S[k], Zs[k], isg, react ? 1 : 0, 0};
         FMMHP_CHECK(to_dev(A, &S.inst_info, ii, "instance info", s));
-        if (S.nxbox > 0) {  // P2L box geometry (the instance table is needed)
-            hipLaunchKernelGGL(k_xgeo, dim3(nblk((int64_t)S.nxbox, 256)), dim3(256), 0, s, S.nxbox, S.xbox,
+        // P2L box geometry (the instance table is needed)
+        if (S.nxbox > 0)
+            hipLaunchKernelGGL(k_xgeo, dim3(nblk((int64_t)S.nxbox, 256)), dim3(256), 0, s, S.nxbox, S.xbox, 1,
                                S.inst_info, T.inst, T.level, T.bx, T.by, S.xgeo);
-            FMMHP_HIP(hipGetLastError());
-        }
+        if (S.nxslot > 0)
+            hipLaunchKernelGGL(k_xgeo, dim3(nblk((int64_t)S.nxslot, 256)), dim3(256), 0, s, S.nxslot,
+                               (const int32_t *)S.xslot, 4, S.inst_info, T.inst, T.level, T.bx, T.by, S.xsgeo);
+        FMMHP_HIP(hipGetLastError());
     }
 
     // image M2L tables: one block of kNumImgSlots operators per (instance, level) that has image V
@@ -3265,8 +3265,22 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
                                S.nloc, S.ibase, S.vimg_off, S.vimg_ent, S.TimgH, S.TimgG, S.Limg, S.logside,
                                S.bc == 2 ? -1.0 : 1.0, ws.W, ws.Lam);
         const int x0 = S.xgrp_lev[l0], x1 = S.xgrp_lev[l1];
+        const int y0 = S.xslot_lev[l0], y1 = S.xslot_lev[l1];
+        if (y1 > y0) {
+            constexpr int VP = p2l_vecs(PB, NV);
+            const P2LArgs pa{y1 - y0,  nbox,  S.nloc, NV,        S.xslot + y0, S.xrow0 + y0,              S.xsgeo + y0, S.xstream,
+                             S.xy,     S.nrm, ws.qs,  S.logside, S.fact,       S.bc == 2 ? -1.0 : 1.0, ws.Lam};
+            // four lanes a box once that gives each of the 1,024 SIMDs a wave; below, a box's chain of rows is
+            // what a launch takes (100,000 uniform points, p = 15, two vectors: 29 us a launch with four lanes, 12 with sixteen)
+            if (S.nxslot >= kP2LManyBoxes)
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2l<PB, DIP, VP, 4>), dim3(nblk(nblk(y1 - y0, 64), 8) * 8, NV / VP),
+                                   dim3(256), 0, st, pa);
+            else
+                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2l<PB, DIP, VP, 16>), dim3(nblk(nblk(y1 - y0, 16), 8) * 8, NV / VP),
+                                   dim3(256), 0, st, pa);
+        }
         if (x1 > x0)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2l<PB, DIP, NV>), dim3(x1 - x0), dim3(64), 0, st, S.inst_info, T.inst,
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2l_react<PB, DIP, NV>), dim3(x1 - x0), dim3(64), 0, st, S.inst_info, T.inst,
                                S.nloc, S.xgrp + x0, S.xgent, S.xbox, S.xgeo, nbox, T.xs, T.ys, ws.qs, S.nrm, S.fact,
                                ws.Lam);
         FMMHP_HIP(hipGetLastError());

@@ -189,9 +189,6 @@ struct Sched {
     uint64_t *pw_cells = nullptr;
     double *pw_ts = nullptr, *pw_tt = nullptr;
     cplx *pw_L = nullptr;           // [kNumSlots]
-    // X list targets
-    int nxbox = 0;
-    int32_t *xbox = nullptr;
     int32_t *leaves = nullptr;      // [nleaf]
     int64_t n_wpts = 0;
     int32_t *wpts = nullptr;        // sorted points whose leaf has a W list
@@ -227,13 +224,22 @@ struct Sched {
     };
     std::vector<Band> bands;
     int32_t *band_tab = nullptr;
-    // P2L groups: {first X box (index into xbox), X sources of the group, first entry of xgent, 0},
-    // one sentinel {nxbox, 0, entries, 0}; groups never cross a level (xgrp_lev[l] = first group of
-    // level l).  xgent: {list entry code, box slot in the group, first row in the group, first
-    // source point}; xgeo: per X box {centre x, centre y, half side, instance}
+    // P2L rows without reaction terms: a slot per box and its source stream (see P2LArgs); xslot_lev[l] =
+    // first slot of level l
+    int nxslot = 0;
+    int4 *xslot = nullptr;
+    int64_t *xrow0 = nullptr;
+    double4 *xsgeo = nullptr;
+    int32_t *xstream = nullptr;
+    // P2L groups of the rows with reaction terms: {first box (index into xbox), rows of the group, first
+    // entry of xgent, 0}, one sentinel {nxbox, 0, entries, 0}; groups never cross a level (xgrp_lev[l] =
+    // first group of level l).  xgent: {list entry code, box slot in the group, first row in the group,
+    // first source point}; xgeo: per box {centre x, centre y, half side, instance}
+    int nxbox = 0;
+    int32_t *xbox = nullptr;
     int4 *xgrp = nullptr, *xgent = nullptr;
     double4 *xgeo = nullptr;
-    std::vector<int> xgrp_lev;
+    std::vector<int> xslot_lev, xgrp_lev;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     hipEvent_t ev_up = nullptr;  // upward pass done (main stream)
     // tables
