@@ -67,7 +67,7 @@ struct P2LArgs {
     cplx *Lam;
 };
 
-__host__ __device__ constexpr int p2l_vecs(int PB, int NV) { return NV > 1 && PB <= 20 ? 2 : 1; }
+__host__ __device__ constexpr int p2l_vecs(int PB, int NV) { return NV % 2 == 0 && PB <= 20 ? 2 : 1; }
 
 // The stream's rows of one list entry {leaf, 0, row (low, high)}.
 __global__ void k_p2l_rows(int64_t m, const int4 *__restrict__ ent, const int32_t *__restrict__ first,
