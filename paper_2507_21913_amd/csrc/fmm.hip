@@ -1147,7 +1147,7 @@ __global__ __launch_bounds__(256) void k_rank1_final(const cplx *__restrict__ pa
 // ---------------------------------------------------------------------------------------------
 // Leaf evaluation.  k_near: the log parts of the U list; k_near_reaction: the reaction part of the
 // U list's image entries, for the targets whose leaf has them; k_leaf: L2P of the local(s) plus
-// the near-field sums and the surface term; k_leaf_w: the rarer W list (M2P).
+// the near-field sums and the surface term; k_m2p, k_m2p_react: the W list (M2P).
 //
 // Each kernel has three modes: kPhi (the potential, in caller order), kGrad (the gradient
 // (d_x phi, d_y phi) only) and kPhiGrad (both); the near-field kernels have a fourth, kDip, the
@@ -1182,8 +1182,11 @@ struct LeafArgs {
     const cplx *W, *Lam;
     const double *invfact, *fact;
     const cplx *rank1;       // [nv][n_inst] surface sums (real impedance) or null
-    const int32_t *wpts;     // targets whose leaf has a W list
-    int64_t n_wpts;
+    const int4 *wrec;        // [nwrec] targets and entries of the leaves with a W list (see WRec)
+    int nwrec;
+    const double4 *wgeo;     // [W entries] centre, half side, log of the half side
+    const int32_t *wipts;    // targets whose leaf's W list has image entries
+    int64_t n_wipts;
     const int32_t *rpts;     // targets whose leaf has image U entries
     const double2 *logtab;   // [kLogTable] (1/c_k, -log(1/c_k))
     double2 *near;           // [nv][n] near-field potential per sorted target
@@ -1816,160 +1819,239 @@ __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
     }
 }
 
-// Steps of the W-list evaluation below: term k of the log-kernel multipole (powers of tau) and
-// term n of the reaction ME (the I_n recursion), for every vector of the pass.
-template <int MODE, int NV>
-__device__ __forceinline__ void leafw_log_step(const LeafArgs &a, int64_t vstride, int d, int img, int k, cplx &pw,
-                                               const cplx &tau, cplx (&u)[NV], cplx (&ud)[NV]) {
-    const double fk1 = a.fact[k - 1], fk = a.fact[k];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        cplx wk = a.W[(int64_t)v * vstride + (int64_t)k * a.nbox + d];
-        if (img) wk = conj(wk);
-        const cplx pk = pw * wk;
-        if (has_phi(MODE)) u[v] -= fk1 * pk;
-        if (has_grad(MODE)) ud[v] += fk * pk;
-    }
-    pw = pw * tau;
-}
+// W list (M2P), log kernel: the multipoles of smaller non-adjacent boxes at the points of a leaf.  As in
+// the near field a wave takes up to 64 targets of one leaf, up to kNearTargets of them a lane, and its lane
+// groups take every JG-th entry of the leaf's list; more lanes share the targets when the list leaves half
+// of the groups without an entry.  A lane reads a coefficient once for its targets; per coefficient and
+// target a complex multiply steps c_k = s (k-1)! tau^k (tau = -rho / (z - c), s = -+1/2pi) and two
+// multiply-adds per vector take its real part: both locals H and G of the log kernel are equal, so that
+// phi = H + conj(G) is twice the real part (w_0 is real), and the gradient likewise
+// (2 Re, -2 Im) u', u' = -(1/rho) sum_k c_(k+1) w_k.  An image box's multipole is the conjugate: the lane
+// conjugates the target offset instead.  Adds to the near-field sums (before k_leaf reads them).
+//
+// What bounds it: the loads of a wave (record, entry, coefficients, sums) at two waves per SIMD, then FP64
+// issue.  The kernel it replaced took a lane per target, formed complex sums of every vector and both
+// locals, and held one wave per SIMD.  Alone on the GPU: 4M points along a curve, p = 30: 314 -> 141 us;
+// 2M points in 64 instances, p = 20, eight vectors: 1,302 -> 308 us (and 51 us in k_m2p_react).
+struct WRec {
+    int ft, nt, e0, e1;      // first target, targets (at most 64), entries
+};
 
-template <int PB, int MODE, int NV>
-__device__ __forceinline__ void leafw_react_step(const LeafArgs &a, int64_t vstride, int d, int pass, int n,
-                                                 const cplx &sw, const cplx &zr, cplx &F, cplx &K, cplx (&acc)[NV],
-                                                 cplx (&accd)[NV]) {
-    F = F * sw * (n > 1 ? (double)(n - 1) : 1.0);
-    K = F * kInv2Pi + zr * K;
-    const cplx Kn = mul_ipow(pass == 0 ? K : conj(K), n);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const cplx *Wv = a.W + (int64_t)v * vstride;
-        if (has_phi(MODE) && n <= PB) acc[v] += Kn * conj(Wv[(int64_t)n * a.nbox + d]);
-        if (has_grad(MODE)) accd[v] += Kn * conj(Wv[(int64_t)(n - 1) * a.nbox + d]);
-    }
-}
-
-// W list for the targets whose leaf has one: multipoles of smaller non-adjacent boxes evaluated
-// at the target (log kernel, and the paper's reaction ME for image boxes).  Adds to the near-field
-// sums (before k_leaf reads them).
-template <int PB, int MODE, int NV>
-__global__ __launch_bounds__(128) void k_leaf_w(LeafArgs a) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= a.n_wpts) return;
-    // one thread per target, every charge vector of the pass: the geometric factors (powers of
-    // tau, the logarithm, the reaction integrals) are computed once for all vectors
+template <int PB, int MODE, int NV, int TI>
+__device__ __forceinline__ void m2p_record(const LeafArgs &a, int lane, const WRec &rc, int IA) {
+    constexpr bool PHI = has_phi(MODE), GRAD = has_grad(MODE);
+    constexpr int T2 = NearSums<MODE, NV, TI>::T2;
+    const int JG = 64 / IA, ig = lane & (IA - 1), jg = lane / IA;
     const int64_t vstride = (int64_t)(PB + 1) * a.nbox;
-    const int64_t i = a.wpts[t];
-    const int b = a.leaf_of[i];
-    const Geo g = geo_of(a.ii, a.inst[b]);
-    const cplx Zk = a.ii[a.inst[b]].Z;
-    const double x = a.xs[i], y = a.ys[i];
-    const cplx z = mk(x, y);
-    cplx H[NV], G[NV], Hd[NV], Gd[NV];
+    NearSums<MODE, NV, TI> S;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) H[v] = G[v] = Hd[v] = Gd[v] = mk(0.0, 0.0);
-    for (int e = a.woff[b]; e < a.woff[b + 1]; ++e) {
+    for (int k = 0; k < TI; ++k) {
+        const int i = ig + IA * k;
+        const double2 P = a.xy[rc.ft + (i < rc.nt ? i : 0)];
+        S.tx[k] = P.x;
+        S.ty[k] = P.y;
+    }
+#pragma unroll
+    for (int k = 0; k < T2; ++k)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (PHI) S.acc[v][k] = 0.0;
+            if (GRAD) S.gx[v][k] = S.gy[v][k] = 0.0;
+        }
+    for (int e = rc.e0 + jg; e < rc.e1; e += JG) {
         const int code = a.went[e];
-        const int d = code >> 1, img = code & 1;
-        const int ld = a.level[d];
-        const cplx cd0 = centre_of(g, ld, a.bx[d], a.by[d]);
-        const double rd = 0.5 * side_of(g, ld);
-        const cplx cd = img ? conj(cd0) : cd0;
-        const cplx dz = z - cd;
-        const cplx idz = inv(dz);
-        const cplx tau = -rd * idz;
-        // u = w0 log(z - c) - sum_k (k-1)! tau^k w_k,  u' = (w0 + sum_k k! tau^k w_k) / (z - c)
-        // (conjugated w for the image box)
-        const cplx lg = has_phi(MODE) ? clog_(dz) : mk(0.0, 0.0);
-        cplx u[NV], ud[NV];
+        const double4 g = a.wgeo[e];  // centre, half side, log of the half side
+        const bool img = code & 1;
+        const cplx *w = a.W + (code >> 1);
+        const double s = img ? a.isg * kInv2Pi : -kInv2Pi, ir = 1.0 / g.z;
+        const double fy = img ? -1.0 : 1.0;  // the sign of the gradient's y component
+        cplx c[TI], tau[TI];
+        double lg[TI];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            cplx w0 = a.W[(int64_t)v * vstride + d];
-            if (img) w0 = conj(w0);
-            u[v] = has_phi(MODE) ? w0 * lg : mk(0.0, 0.0);
-            ud[v] = w0;
+        for (int k = 0; k < TI; ++k) {
+            const double dx = (S.tx[k] - g.x) * ir, dy = (img ? -(S.ty[k] + g.y) : S.ty[k] - g.y) * ir;
+            const double r2 = fma(dx, dx, dy * dy), i2 = 1.0 / r2;
+            tau[k] = mk(-(dx * i2), dy * i2);
+            c[k] = mk(s * tau[k].re, s * tau[k].im);
+            if (PHI) lg[k] = s * fma(0.5, log(r2), g.w);
         }
-        cplx pw = tau;
-        // one vector: the k loop unrolled in full; several: the compiler's own choice (unrolling a
-        // body that already spans every vector crowds the registers)
-        if constexpr (NV == 1) {
+#pragma unroll(NV >= 8 ? 2 : NV >= 2 ? 4 : 8)
+        for (int m = 0; m <= PB; ++m) {
+            cplx wm[NV];
 #pragma unroll
-            for (int k = 1; k <= PB; ++k) leafw_log_step<MODE, NV>(a, vstride, d, img, k, pw, tau, u, ud);
-        } else {
-            for (int k = 1; k <= PB; ++k) leafw_log_step<MODE, NV>(a, vstride, d, img, k, pw, tau, u, ud);
-        }
-        const double sgn = (img ? a.ii[a.inst[b]].isg : -1.0) * kInv4Pi;
+            for (int v = 0; v < NV; ++v) wm[v] = w[(int64_t)v * vstride];
+            w += a.nbox;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            H[v] += sgn * u[v];
-            G[v] += sgn * u[v];
-            const cplx udv = sgn * (ud[v] * idz);
-            Hd[v] += udv;
-            Gd[v] += udv;
-        }
-        if (img && a.ii[a.inst[b]].react) {
-            // reaction ME (eq. (truncatedME)) of the image box: sum_n alpha_n I_n(x - x'_c, y - y'_c),
-            // alpha_n = rho^n (-i)^n conj(mu_n) = i^n n! rho^n conj(w_n); with K_n = n! rho^n I_n its
-            // z-derivative is (1/rho) sum_n i^(n+1) K_(n+1) conj(w_n)
-            const double X = x - cd0.re, Y = y + cd0.im;
-            for (int pass = 0; pass < a.nloc; ++pass) {
-                const double Xs = pass == 0 ? X : -X;
-                const cplx sw = rd * inv(mk(Y, -Xs));
-                const cplx zr = rd * Zk;
-                cplx K = reaction_I0_general(Xs, Y, Zk);
-                cplx F = mk(1.0, 0.0);
-                cplx acc[NV], accd[NV];
-                const cplx K0 = pass == 0 ? K : conj(K);
+            for (int k = 0; k < TI; ++k) {
+                // here c = s (m-1)! tau^m (m >= 1), for the gradient s m! tau^(m+1)
+                if (PHI && m == 0) {
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    acc[v] = has_phi(MODE) ? K0 * conj(a.W[(int64_t)v * vstride + d]) : mk(0.0, 0.0);
-                    accd[v] = mk(0.0, 0.0);
+                    for (int v = 0; v < NV; ++v) S.acc[v][k] = fma(lg[k], wm[v].re, S.acc[v][k]);
+                } else if (PHI) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)
+                        S.acc[v][k] = fma(c[k].im, wm[v].im, fma(-c[k].re, wm[v].re, S.acc[v][k]));
                 }
-                constexpr int NTOP = has_grad(MODE) ? PB + 1 : PB;
-                if constexpr (NV == 1) {
-#pragma unroll
-                    for (int n = 1; n <= NTOP; ++n)
-                        leafw_react_step<PB, MODE, NV>(a, vstride, d, pass, n, sw, zr, F, K, acc, accd);
-                } else {
-                    for (int n = 1; n <= NTOP; ++n)
-                        leafw_react_step<PB, MODE, NV>(a, vstride, d, pass, n, sw, zr, F, K, acc, accd);
+                if (m > 0) {
+                    c[k] = c[k] * tau[k];
+                    c[k].re *= (double)m;
+                    c[k].im *= (double)m;
                 }
+                if (GRAD) {
+                    const double cr = -ir * c[k].re, ci = ir * c[k].im, yr = fy * cr, yi = fy * ci;
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    if (pass == 0) {
-                        H[v] += acc[v];
-                        Hd[v] += accd[v] * (1.0 / rd);
-                    } else {
-                        G[v] += acc[v];
-                        Gd[v] += accd[v] * (1.0 / rd);
+                    for (int v = 0; v < NV; ++v) {
+                        S.gx[v][k] = fma(ci, wm[v].im, fma(cr, wm[v].re, S.gx[v][k]));
+                        S.gy[v][k] = fma(yi, wm[v].re, fma(-yr, wm[v].im, S.gy[v][k]));
                     }
                 }
             }
         }
     }
-    // into the near-field sums of the target (sorted order), which k_leaf adds to the far field
+    int k = 0, off = IA;  // the lane's target after the reduction, as in near_record
+#pragma unroll
+    for (int h = T2 / 2; h >= 1; h >>= 1, off <<= 1) k += (lane & off) ? h : 0;
+    const int i = ig + IA * k;
+    const bool wr = (lane & ~(off - 1)) == 0 && k < TI && i < rc.nt;
+    const int64_t o = rc.ft + i;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        if (has_phi(MODE)) {
-            double2 *nr = a.near + (int64_t)v * a.n + i;
-            double2 hv = *nr;
-            if (a.nloc == 1) {
-                hv.x += 2.0 * H[v].re;
-            } else {
-                const cplx c = H[v] + conj(G[v]);
-                hv.x += c.re;
-                hv.y += c.im;
-            }
-            *nr = hv;
+        if (PHI) {
+            near_reduce<T2>(S.acc[v], lane, IA);
+            if (wr) a.near[(int64_t)v * a.n + o].x += S.acc[v][0];
         }
-        if (has_grad(MODE)) {
-            cplx *gx = a.near_gx + (int64_t)v * a.n + i, *gy = a.near_gy + (int64_t)v * a.n + i;
-            if (a.nloc == 1) {
-                *gx += mk(2.0 * Hd[v].re, 0.0);
-                *gy += mk(-2.0 * Hd[v].im, 0.0);
-            } else {
-                *gx += Hd[v] + conj(Gd[v]);
-                *gy += mul_ipow(Hd[v] - conj(Gd[v]), 1);
+        if (GRAD) {
+            near_reduce<T2>(S.gx[v], lane, IA);
+            near_reduce<T2>(S.gy[v], lane, IA);
+            if (wr) {
+                a.near_gx[(int64_t)v * a.n + o].re += S.gx[v][0];
+                a.near_gy[(int64_t)v * a.n + o].re += S.gy[v][0];
             }
+        }
+    }
+}
+
+template <int PB, int MODE, int NV>
+__global__ __launch_bounds__(256, 2) void k_m2p(LeafArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int ri = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (ri >= a.nwrec) return;
+    const int4 r4 = a.wrec[ri];
+    const WRec rc{r4.x, r4.y, r4.z, r4.w};
+    int IA = rc.nt <= 4 ? 1 : rc.nt <= 8 ? 2 : rc.nt <= 16 ? 4 : rc.nt <= 32 ? 8 : 16;
+    while (IA < rc.nt && 32 / IA >= rc.e1 - rc.e0) IA *= 2;
+    switch ((rc.nt + IA - 1) / IA) {
+    case 1: m2p_record<PB, MODE, NV, 1>(a, lane, rc, IA); break;
+    case 2: m2p_record<PB, MODE, NV, 2>(a, lane, rc, IA); break;
+    case 3: m2p_record<PB, MODE, NV, 3>(a, lane, rc, IA); break;
+    default: m2p_record<PB, MODE, NV, 4>(a, lane, rc, IA); break;
+    }
+}
+
+// A W entry's box: centre, half side and its logarithm.
+__global__ void k_wgeo(int64_t m, const int32_t *__restrict__ went, const InstInfo *__restrict__ ii,
+                       const int32_t *__restrict__ inst, const int32_t *__restrict__ level,
+                       const int32_t *__restrict__ bx, const int32_t *__restrict__ by,
+                       const double *__restrict__ logside, double4 *__restrict__ wgeo) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= m) return;
+    const int b = went[e] >> 1, l = level[b];
+    const Geo g = geo_of(ii, inst[b]);
+    const cplx c = centre_of(g, l, bx[b], by[b]);
+    wgeo[e] = make_double4(c.re, c.im, 0.5 * side_of(g, l), logside[b] - (kLn2Hi + kLn2Lo));
+}
+
+// W list, reaction multipoles of image boxes (eq. (truncatedME)), at the targets whose leaf has such entries
+// (few: leaves near y = 0 with smaller image boxes in their list): sum_n alpha_n I_n(x - x'_c, y - y'_c),
+// alpha_n = rho^n (-i)^n conj(mu_n) = i^n n! rho^n conj(w_n); with K_n = n! rho^n I_n its z-derivative is
+// (1/rho) sum_n i^(n+1) K_(n+1) conj(w_n).  Eight lanes take a target's (entry, local) items in turn, each
+// for every vector of the pass: an item is one long chain (I_0 and the recursion), and the chains are what a
+// launch takes (2M points in 64 instances, eight vectors: 132 us with a lane per target, 51 with eight).
+constexpr int kReactLanes = 8;
+
+template <int PB, int MODE, int NV>
+__global__ __launch_bounds__(128) void k_m2p_react(LeafArgs a) {
+    constexpr bool PHI = has_phi(MODE), GRAD = has_grad(MODE);
+    constexpr int NTOP = GRAD ? PB + 1 : PB;
+    const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kReactLanes;
+    const int sub = threadIdx.x & (kReactLanes - 1);
+    const bool have = t < a.n_wipts;
+    const int64_t vstride = (int64_t)(PB + 1) * a.nbox;
+    const int64_t i = a.wipts[have ? t : 0];
+    const int b = a.leaf_of[i];
+    const cplx Z = a.ii[a.inst[b]].Z;
+    const double x = a.xs[i], y = a.ys[i];
+    cplx P[NV], Gx[NV], Gy[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) P[v] = Gx[v] = Gy[v] = mk(0.0, 0.0);
+    int e = have ? a.woff[b] : 0, first = 0;  // first: items before entry e
+    const int e1 = have ? a.woff[b + 1] : 0;
+    for (int want = sub;; want += kReactLanes) {
+        // every lane finds its next item, then all work on theirs together
+        int code = 0;
+        for (; e < e1; ++e) {
+            code = a.went[e];
+            if (!(code & 1)) continue;
+            if (want < first + a.nloc) break;
+            first += a.nloc;
+        }
+        if (e >= e1) break;
+        const int pass = want - first;
+        const double4 g = a.wgeo[e];
+        const cplx *w = a.W + (code >> 1);
+        const double X = pass == 0 ? x - g.x : g.x - x, Y = y + g.y;
+        const cplx sw = g.z * inv(mk(Y, -X)), zr = g.z * Z;
+        cplx K = reaction_I0_general(X, Y, Z);
+        cplx F = mk(1.0, 0.0), acc[NV], accd[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            acc[v] = PHI ? (pass == 0 ? K : conj(K)) * conj(w[(int64_t)v * vstride]) : mk(0.0, 0.0);
+            accd[v] = mk(0.0, 0.0);
+        }
+#pragma unroll(NV == 1 ? 8 : 2)
+        for (int n = 1; n <= NTOP; ++n) {
+            F = F * sw * (n > 1 ? (double)(n - 1) : 1.0);
+            K = F * kInv2Pi + zr * K;
+            const cplx Kn = mul_ipow(pass == 0 ? K : conj(K), n);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                if (PHI && n <= PB) acc[v] += Kn * conj(w[(int64_t)v * vstride + (int64_t)n * a.nbox]);
+                if (GRAD) accd[v] += Kn * conj(w[(int64_t)v * vstride + (int64_t)(n - 1) * a.nbox]);
+            }
+        }
+        // phi = H + conj(G), d_x phi = H' + conj(G'), d_y phi = i (H' - conj(G')); a real impedance
+        // has G = H
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const cplx d = accd[v] * (1.0 / g.z);
+            if (a.nloc == 1) {
+                P[v].re += 2.0 * acc[v].re;
+                Gx[v].re += 2.0 * d.re;
+                Gy[v].re -= 2.0 * d.im;
+            } else if (pass == 0) {
+                P[v] += acc[v];
+                Gx[v] += d;
+                Gy[v] += mul_ipow(d, 1);
+            } else {
+                P[v] += conj(acc[v]);
+                Gx[v] += conj(d);
+                Gy[v] += mul_ipow(conj(d), 3);
+            }
+        }
+    }
+    // into the near-field sums of the target (sorted order), which k_leaf adds to the far field
+    auto add = [&](cplx &dst, cplx c) {
+        c.re = lane_group_sum(c.re, kReactLanes);
+        c.im = lane_group_sum(c.im, kReactLanes);
+        if (have && sub == 0) dst += c;
+    };
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int64_t o = (int64_t)v * a.n + i;
+        if (PHI) add(((cplx *)a.near)[o], P[v]);
+        if (GRAD) {
+            add(a.near_gx[o], Gx[v]);
+            add(a.near_gy[o], Gy[v]);
         }
     }
 }
@@ -2850,6 +2932,10 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         if (S.nxslot > 0)
             hipLaunchKernelGGL(k_xgeo, dim3(nblk((int64_t)S.nxslot, 256)), dim3(256), 0, s, S.nxslot,
                                (const int32_t *)S.xslot, 4, S.inst_info, T.inst, T.level, T.bx, T.by, S.xsgeo);
+        FMMHP_CHECK(A.alloc_n(&S.wgeo, (size_t)T.len[2], "W entry geometry"));
+        if (T.len[2] > 0)
+            hipLaunchKernelGGL(k_wgeo, dim3(nblk(T.len[2], 256)), dim3(256), 0, s, (int64_t)T.len[2], T.ent[2],
+                               S.inst_info, T.inst, T.level, T.bx, T.by, S.logside, S.wgeo);
         FMMHP_HIP(hipGetLastError());
     }
 
@@ -3167,7 +3253,7 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
                 ws.qs,        S.xy,      T.perm,   T.leaf_of, T.level, T.bx,     T.by,     T.first,  T.count,
                 T.off[0],    T.ent[0],  T.off[2], T.ent[2], ws.W,      ws.Lam,    S.invfact, S.fact,
                 S.bc == 0 ? ws.rank1 : nullptr,
-                S.wpts,      S.n_wpts,  S.rpts,   S.logtab, ws.near,   S.bw.near_gx, S.bw.near_gy, out.qc,
+                S.wrec,      S.nwrec,    S.wgeo,  S.wipts,  S.n_wipts, S.rpts,   S.logtab, ws.near,   S.bw.near_gx, S.bw.near_gy, out.qc,
                 out.phi,     out.gx,    out.gy,   S.bc == 2 ? -1.0 : 1.0, S.nrm,
                 out.sorted ? 1 : 0};
     FMMHP_HIP(hipEventRecord(S.ev_fork, s));
@@ -3312,11 +3398,13 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     FMMHP_HIP(hipGetLastError());
     // the W list (M2P) needs every multipole and adds into the near-field sums: on the near-field stream
     // once the upward pass is done, beside the M2L and the downward pass
-    if (S.n_wpts > 0) {
+    if (S.nwrec > 0) {
         FMMHP_HIP(hipEventRecord(S.ev_up, s));
         FMMHP_HIP(hipStreamWaitEvent(side_, S.ev_up, 0));
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_leaf_w<PB, LM, NV>), dim3(nblk(S.n_wpts, 128)), dim3(128), 0, side_,
-                           la);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2p<PB, LM, NV>), dim3(nblk(S.nwrec, 4)), dim3(256), 0, side_, la);
+        if (S.bc == 0 && S.n_wipts > 0)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2p_react<PB, LM, NV>), dim3(nblk(S.n_wipts * kReactLanes, 128)), dim3(128), 0,
+                               side_, la);
         FMMHP_HIP(hipGetLastError());
     }
     FMMHP_HIP(hipEventRecord(S.ev_join, side_));

@@ -190,8 +190,13 @@ struct Sched {
     double *pw_ts = nullptr, *pw_tt = nullptr;
     cplx *pw_L = nullptr;           // [kNumSlots]
     int32_t *leaves = nullptr;      // [nleaf]
-    int64_t n_wpts = 0;
-    int32_t *wpts = nullptr;        // sorted points whose leaf has a W list
+    // W list: records {first target, targets (at most 64), first entry, end} of the leaves that have one,
+    // per entry {centre x, centre y, half side, its log}, sorted points whose leaf has image entries
+    int nwrec = 0;
+    int4 *wrec = nullptr;
+    double4 *wgeo = nullptr;
+    int64_t n_wipts = 0;
+    int32_t *wipts = nullptr;
     int64_t n_rpts = 0;
     int32_t *rpts = nullptr;        // sorted points whose leaf has image U entries
     int near_nrec = 0;              // near-field records (a leaf's targets, 64 at most) and, per leaf, the
@@ -309,8 +314,8 @@ fmmhp_status run_field(Arena &A, const Tree &T, Sched &S, const double *q, doubl
 // Clears n doubles on stream with a kernel (no memset node under graph capture).
 fmmhp_status zero_f64(double *p, int64_t n, hipStream_t stream);
 
-// Pair counts, image V entries, leaves, W-list and near-axis points, near-field records and streams, on
-// the device; vimg_off also to the host.
+// Pair counts, image V entries, leaves, W-list records and image points, near-axis points, near-field
+// records and streams, on the device; vimg_off also to the host.
 fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t> &vimg_off, hipStream_t stream);
 
 // zsum_host: per-instance homogeneity sums copied to the host (the call synchronises), or null;

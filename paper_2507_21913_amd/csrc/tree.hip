@@ -758,12 +758,15 @@ fmmhp_status parent_colleagues(const Tree &T, const std::vector<int32_t> &par, s
 // ---------------------------------------------------------------------------------------------
 // Tables read off the lists (list_tables)
 // ---------------------------------------------------------------------------------------------
-// Per box: image V entries, near-field sources (free, image) and records; the pair counts of the plan,
+// Per box: image V entries, near-field sources (free, image) and records, W-list records and whether the
+// list has image entries; the pair counts of the plan,
 // tot = {free near pairs, image near pairs, upper V pairs, image V pairs}; bad: a V entry that is not a
 // same-level offset of the interaction list.
 __global__ __launch_bounds__(256) void k_list_counts(TreeView t, int nbox, const int32_t *__restrict__ count,
                                                      const int32_t *__restrict__ uoff, const int32_t *__restrict__ uent,
                                                      const int32_t *__restrict__ voff, const int32_t *__restrict__ vent,
+                                                     const int32_t *__restrict__ woff, const int32_t *__restrict__ went,
+                                                     int32_t *__restrict__ nwrec, int32_t *__restrict__ wimg,
                                                      int32_t *__restrict__ vimg, int64_t *__restrict__ nfree,
                                                      int64_t *__restrict__ nimg, int64_t *__restrict__ len,
                                                      int32_t *__restrict__ nrec, unsigned long long *__restrict__ tot,
@@ -795,6 +798,10 @@ __global__ __launch_bounds__(256) void k_list_counts(TreeView t, int nbox, const
         nimg[b] = u[1];
         len[b] = leaf ? u[0] + u[1] : 0;
         nrec[b] = leaf ? (count[b] + 63) / 64 : 0;
+        nwrec[b] = woff[b + 1] > woff[b] ? (count[b] + 63) / 64 : 0;  // (only leaves have W entries)
+        int wi = 0;
+        for (int e = woff[b]; e < woff[b + 1]; ++e) wi |= went[e] & 1;
+        wimg[b] = wi;
         const int64_t k = count[b];
         if (u[0]) atomicAdd(&st[0], (unsigned long long)(k * u[0]));
         if (u[1]) atomicAdd(&st[1], (unsigned long long)(k * u[1]));
@@ -814,7 +821,8 @@ __global__ __launch_bounds__(64) void k_list_fill(TreeView t, const int32_t *__r
                                                   int32_t *__restrict__ vimg_ent, const int64_t *__restrict__ nfree,
                                                   const int64_t *__restrict__ nimg, const int64_t *__restrict__ soff,
                                                   const int32_t *__restrict__ roff, NearRec *__restrict__ rec,
-                                                  int32_t *__restrict__ stream) {
+                                                  int32_t *__restrict__ stream, const int32_t *__restrict__ woff,
+                                                  const int32_t *__restrict__ wroff, int4 *__restrict__ wrec) {
     const int b = blockIdx.x, lane = threadIdx.x;
     if (lane == 0 && vimg_off[b + 1] > vimg_off[b]) {
         int32_t *out = vimg_ent + vimg_off[b];
@@ -830,6 +838,9 @@ __global__ __launch_bounds__(64) void k_list_fill(TreeView t, const int32_t *__r
     const int f = first[b], n = count[b];
     for (int k = lane; k < (n + 63) / 64; k += 64)
         rec[roff[b] + k] = NearRec{f + 64 * k, min(64, n - 64 * k), n, (int32_t)nfree[b], (int32_t)nimg[b], 0, soff[b]};
+    if (woff[b + 1] > woff[b])
+        for (int k = lane; k < (n + 63) / 64; k += 64)
+            wrec[wroff[b] + k] = make_int4(f + 64 * k, min(64, n - 64 * k), woff[b], woff[b + 1]);
     int32_t *out = stream + soff[b];
     for (int k = lane; k < n; k += 64) out[k] = f + k;
     out += n;
@@ -848,23 +859,24 @@ __global__ void k_compact(int64_t n, const int32_t *__restrict__ flag, const int
     if (i < n && flag[i]) out[pos[i]] = (int32_t)i;
 }
 
-// Sorted points whose leaf has a W list (w) and near-axis points (r: image sources in the U list).
-__global__ void k_point_flags(int64_t n, const int32_t *__restrict__ leaf_of, const int32_t *__restrict__ woff,
+// Sorted points whose leaf has image W entries (w) and near-axis points (r: image sources in the U list).
+__global__ void k_point_flags(int64_t n, const int32_t *__restrict__ leaf_of, const int32_t *__restrict__ wimg,
                               const int64_t *__restrict__ nimg, int32_t *__restrict__ w, int32_t *__restrict__ r) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int b = leaf_of[i];
-    w[i] = woff[b + 1] > woff[b];
+    w[i] = wimg[b];
     r[i] = nimg[b] > 0;
 }
 
 __global__ void k_totals(const int32_t *a, const int32_t *b, const int32_t *c, const int32_t *d, const int64_t *e,
-                         int64_t *__restrict__ out) {
+                         const int32_t *f, int64_t *__restrict__ out) {
     out[0] = *a;
     out[1] = *b;
     out[2] = *c;
     out[3] = *d;
     out[4] = *e;
+    out[5] = *f;
 }
 
 fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t> &vimg_off_h, hipStream_t s) {
@@ -872,13 +884,16 @@ fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t>
     const int64_t n = T.n;
     Scratch sc(s, (size_t)80 * (size_t)nb + (size_t)20 * (size_t)n + ((size_t)1 << 20));
     int32_t *dlev = nullptr, *vimg = nullptr, *nrec = nullptr, *roff = nullptr, *bad = nullptr, *lpos = nullptr,
-            *wf = nullptr, *rf = nullptr, *wpos = nullptr, *rpos = nullptr;
+            *wf = nullptr, *rf = nullptr, *nwrec = nullptr, *wroff = nullptr, *wimg = nullptr, *wpos = nullptr, *rpos = nullptr;
     int64_t *nfree = nullptr, *nimg = nullptr, *len = nullptr, *soff = nullptr, *tot = nullptr;
     FMMHP_CHECK(sc.get(&dlev, 33, "level starts"));
     FMMHP_CHECK(sc.get(&vimg, nb, "image V counts"));
     FMMHP_CHECK(sc.get(&nrec, nb, "record counts"));
     FMMHP_CHECK(sc.get(&roff, nb + 1, "record offsets"));
     FMMHP_CHECK(sc.get(&lpos, nb + 1, "leaf positions"));
+    FMMHP_CHECK(sc.get(&nwrec, nb, "W record counts"));
+    FMMHP_CHECK(sc.get(&wroff, nb + 1, "W record offsets"));
+    FMMHP_CHECK(sc.get(&wimg, nb, "W image flags"));
     FMMHP_CHECK(sc.get(&nfree, nb, "free sources"));
     FMMHP_CHECK(sc.get(&nimg, nb, "image sources"));
     FMMHP_CHECK(sc.get(&len, nb, "stream lengths"));
@@ -895,16 +910,17 @@ fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t>
     TreeView tv{T.level, T.bx, T.by, T.parent, T.leaf, T.child_first, T.nchild, T.inst, T.prefix, dlev, T.depth,
                 T.lbits};
     hipLaunchKernelGGL(k_list_counts, dim3(nblocks(nb, 256)), dim3(256), 0, s, tv, nb, T.count, T.off[0], T.ent[0],
-                       T.off[1], T.ent[1], vimg, nfree, nimg, len, nrec, (unsigned long long *)tot, bad);
-    hipLaunchKernelGGL(k_point_flags, dim3(nblocks(n, 256)), dim3(256), 0, s, n, T.leaf_of, T.off[2], nimg, wf, rf);
+                       T.off[1], T.ent[1], T.off[2], T.ent[2], nwrec, wimg, vimg, nfree, nimg, len, nrec, (unsigned long long *)tot, bad);
+    hipLaunchKernelGGL(k_point_flags, dim3(nblocks(n, 256)), dim3(256), 0, s, n, T.leaf_of, wimg, nimg, wf, rf);
     FMMHP_HIP(hipGetLastError());
     FMMHP_CHECK(exclusive_scan(sc, vimg, S.vimg_off, nb, s));
     FMMHP_CHECK(exclusive_scan(sc, nrec, roff, nb, s));
+    FMMHP_CHECK(exclusive_scan(sc, nwrec, wroff, nb, s));
     FMMHP_CHECK(exclusive_scan(sc, T.leaf, lpos, nb, s));
     FMMHP_CHECK(exclusive_scan(sc, len, soff, nb, s));
     FMMHP_CHECK(exclusive_scan(sc, wf, wpos, n, s));
     FMMHP_CHECK(exclusive_scan(sc, rf, rpos, n, s));
-    hipLaunchKernelGGL(k_totals, dim3(1), dim3(1), 0, s, S.vimg_off + nb, roff + nb, wpos + n, rpos + n, soff + nb, tot + 4);
+    hipLaunchKernelGGL(k_totals, dim3(1), dim3(1), 0, s, S.vimg_off + nb, roff + nb, wpos + n, rpos + n, soff + nb, wroff + nb, tot + 4);
     FMMHP_HIP(hipGetLastError());
     int64_t h[16];
     FMMHP_HIP(hipMemcpyAsync(h, tot, sizeof(h), hipMemcpyDeviceToHost, s));
@@ -921,20 +937,23 @@ fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t>
     S.m2l_pairs[0] = h[2];
     S.m2l_pairs[1] = h[3];
     S.near_nrec = (int)h[5];
-    S.n_wpts = h[6];
+    S.n_wipts = h[6];
+    S.nwrec = (int)h[9];
     S.n_rpts = h[7];
     FMMHP_CHECK(A.alloc_n(&S.vimg_ent, (size_t)h[4], "vimg_ent"));
     FMMHP_CHECK(A.alloc_n(&S.near_rec, (size_t)h[5], "near-field records"));
     FMMHP_CHECK(A.alloc_n(&S.near_stream, (size_t)h[8] + kNearPad, "near-field source streams"));
     FMMHP_CHECK(A.alloc_n(&S.leaves, (size_t)T.nleaf, "leaves"));
-    FMMHP_CHECK(A.alloc_n(&S.wpts, (size_t)h[6], "W-list targets"));
+    FMMHP_CHECK(A.alloc_n(&S.wrec, (size_t)h[9], "W records"));
+    FMMHP_CHECK(A.alloc_n(&S.wipts, (size_t)h[6], "W image targets"));
     FMMHP_CHECK(A.alloc_n(&S.rpts, (size_t)h[7], "near-axis targets"));
     hipLaunchKernelGGL(k_list_fill, dim3((unsigned)nb), dim3(64), 0, s, tv, T.first, T.count, T.off[0], T.ent[0],
-                       T.off[1], T.ent[1], S.vimg_off, S.vimg_ent, nfree, nimg, soff, roff, S.near_rec, S.near_stream);
+                       T.off[1], T.ent[1], S.vimg_off, S.vimg_ent, nfree, nimg, soff, roff, S.near_rec, S.near_stream,
+                       T.off[2], wroff, S.wrec);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, s, S.near_stream + h[8], (int64_t)kNearPad, 0);
     hipLaunchKernelGGL(k_compact, dim3(nblocks(nb, 256)), dim3(256), 0, s, (int64_t)nb, T.leaf, lpos, S.leaves);
-    if (S.n_wpts > 0)
-        hipLaunchKernelGGL(k_compact, dim3(nblocks(n, 256)), dim3(256), 0, s, n, wf, wpos, S.wpts);
+    if (S.n_wipts > 0)
+        hipLaunchKernelGGL(k_compact, dim3(nblocks(n, 256)), dim3(256), 0, s, n, wf, wpos, S.wipts);
     if (S.n_rpts > 0)
         hipLaunchKernelGGL(k_compact, dim3(nblocks(n, 256)), dim3(256), 0, s, n, rf, rpos, S.rpts);
     FMMHP_HIP(hipGetLastError());
