@@ -114,80 +114,113 @@ __global__ void k_pack_xy(const double *__restrict__ xs, const double *__restric
 // Charges into sorted order
 // ---------------------------------------------------------------------------------------------
 // ---------------------------------------------------------------------------------------------
-// nv charge vectors [nv][n] (caller order) -> qs[i * nv + v] (sorted, vectors interleaved)
-__global__ void k_gather_q(const double *__restrict__ q, const int32_t *__restrict__ perm, int64_t n, int nv,
-                           double *__restrict__ qs) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Workgroup -> chunk of 256 points such that an XCD takes one contiguous eighth of the sorted points (the
+// grid is a multiple of 8 workgroups): the points of an instance then meet in one L2, in which their
+// scattered reads in caller order share lines.
+__device__ __forceinline__ int xcd_chunk() { return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3); }
+static inline unsigned xcd_grid(int64_t n) { return 8 * nblk(n, 8 * 256); }
+
+// NV charge vectors [NV][n] (caller order) -> qs[i * NV + v] (sorted, vectors interleaved).  Bound by the
+// scattered reads: 2M points in 64 instances, eight vectors: 351 -> 167 us by the order of the chunks
+// and whole stores.
+template <int NV>
+__global__ __launch_bounds__(256) void k_gather_q(const double *__restrict__ q, const int32_t *__restrict__ perm,
+                                                  int64_t n, double *__restrict__ qs) {
+    const int64_t i = (int64_t)xcd_chunk() * 256 + threadIdx.x;
     if (i >= n) return;
     const int64_t o = perm[i];
-    for (int v = 0; v < nv; ++v) qs[i * nv + v] = q[(int64_t)v * n + o];
+    double t[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) t[v] = q[(int64_t)v * n + o];
+    if constexpr (NV % 2 == 0) {
+#pragma unroll
+        for (int v = 0; v < NV; v += 2) ((double2 *)qs)[(i * NV + v) / 2] = make_double2(t[v], t[v + 1]);
+    } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) qs[i * NV + v] = t[v];
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
-// P2M: leaves.  kP2MSplit consecutive lanes share a leaf, each summing every kP2MSplit-th point;
-// a butterfly over the lanes combines the partial sums (the same value, bitwise, in every lane).
-// ---------------------------------------------------------------------------------------------
-constexpr int kP2MSplit = 4;
-
+// P2M: leaves.  kP2MSplit consecutive lanes share a leaf, each summing every kP2MSplit-th point into
+// coefficients in registers (a power of -(z - c)/rho per point and order, two multiply-adds a vector); the
+// partial sums meet by lane moves, 1/n! comes last, and lane k writes coefficients k, k + 4, ...  Bound by
+// the writes of the multipoles with many vectors, by latency otherwise (2M points, p = 20, eight vectors:
+// 351 -> 255 us, 1M points, one vector: 27 -> 17 us, against a kernel per vector that scaled every term).
 //
 // Dipole sources (DIP: density mu_j, normal n_j, potential mu_j n_j . grad_{r_j} G): the expansions
 // of this method are real-linear in the per-source terms q_j f_n(z_j), f_n(z) = (-(z - c)/rho)^n/n!,
 // and f_n is holomorphic, so n_j . grad f_n = nu_j f_n' with nu_j = n_x + i n_y; the multipole of a
 // dipole is w_n = mu_j nu_j (-1/rho) f_{n-1}(z_j) (w_0 = 0), and every translation is unchanged.
-template <int PB, bool DIP>
+// ---------------------------------------------------------------------------------------------
+constexpr int kP2MSplit = 4;
+
+template <int PB, bool DIP, int VP>
 __global__ __launch_bounds__(256) void k_p2m(const InstInfo *__restrict__ ii, const int32_t *__restrict__ inst,
                                              const int32_t *__restrict__ leaves, int nleaf, int nbox, int nv,
                                              const int32_t *__restrict__ level, const int32_t *__restrict__ bx,
                                              const int32_t *__restrict__ by, const int32_t *__restrict__ first,
-                                             const int32_t *__restrict__ count, const double *__restrict__ xs,
-                                             const double *__restrict__ ys, const double *__restrict__ qs,
-                                             const double2 *__restrict__ nrm, cplx *__restrict__ W) {
+                                             const int32_t *__restrict__ count, const double2 *__restrict__ xy,
+                                             const double *__restrict__ qs, const double2 *__restrict__ nrm,
+                                             cplx *__restrict__ W) {
     __builtin_amdgcn_s_setprio(3);  // upward pass: the critical path
+    constexpr InvFact inv;
     const int gt = blockIdx.x * blockDim.x + threadIdx.x;
     const int t = gt / kP2MSplit, part = gt % kP2MSplit;
-    const bool ok = t < nleaf;  // no early exit: every lane of a leaf group takes part in the butterfly
-    const int v = blockIdx.y;   // charge vector
-    W += (int64_t)v * (PB + 1) * nbox;
+    const bool ok = t < nleaf;  // no early exit: every lane of a leaf group takes part in the sums
+    const int v0 = blockIdx.y * VP;
     const int b = ok ? leaves[t] : 0;
-    cplx w[PB + 1];
+    const Geo g = geo_of(ii, inst[b]);
+    const cplx c = centre_of(g, level[b], bx[b], by[b]);
+    const double irho = 2.0 / side_of(g, level[b]);
+    const int e = first[b] + (ok ? count[b] : 0);
+    cplx w[VP][PB + 1];
 #pragma unroll
-    for (int n = 0; n <= PB; ++n) w[n] = mk(0.0, 0.0);
-    if (ok) {
-        const int l = level[b];
-        const Geo g = geo_of(ii, inst[b]);
-        const cplx c = centre_of(g, l, bx[b], by[b]);
-        const double irho = 2.0 / side_of(g, l);
-        const int f = first[b], e = f + count[b];
-        for (int j = f + part; j < e; j += kP2MSplit) {
-            const cplx mz = mk((c.re - xs[j]) * irho, (c.im - ys[j]) * irho);  // -(z_j - c) / rho
-            if (DIP) {
-                const double2 nj = nrm[j];
-                cplx term = (-irho * qs[(int64_t)j * nv + v]) * mk(nj.x, nj.y);  // mu nu (-1/rho) f_0
+    for (int v = 0; v < VP; ++v)
 #pragma unroll
-                for (int n = 1; n <= PB; ++n) {
-                    w[n] += term;
-                    term = term * mz * (1.0 / n);
-                }
-            } else {
-                cplx term = mk(qs[(int64_t)j * nv + v], 0.0);
+        for (int n = 0; n <= PB; ++n) w[v][n] = mk(0.0, 0.0);
+    for (int j = first[b] + part; j < e; j += kP2MSplit) {
+        const double2 z = xy[j];
+        double q[VP];
+        if constexpr (VP == 2) {
+            const double2 t2 = *(const double2 *)(qs + (int64_t)j * nv + v0);  // v0 and nv are even
+            q[0] = t2.x;
+            q[1] = t2.y;
+        } else {
+            q[0] = qs[(int64_t)j * nv + v0];
+        }
+        const cplx mz = mk((c.re - z.x) * irho, (c.im - z.y) * irho);  // -(z_j - c) / rho
+        cplx pw = mk(1.0, 0.0);
+        if (DIP) pw = mk(nrm[j].x, nrm[j].y);
 #pragma unroll
-                for (int n = 0; n <= PB; ++n) {
-                    w[n] += term;
-                    term = term * mz * (1.0 / (n + 1));
-                }
+        for (int n = DIP ? 1 : 0; n <= PB; ++n) {
+#pragma unroll
+            for (int v = 0; v < VP; ++v) {
+                w[v][n].re = fma(q[v], pw.re, w[v][n].re);
+                w[v][n].im = fma(q[v], pw.im, w[v][n].im);
             }
+            pw = pw * mz;
         }
     }
+    const double sc = DIP ? -irho : 1.0;
 #pragma unroll
-    for (int n = 0; n <= PB; ++n)
-        for (int off = 1; off < kP2MSplit; off <<= 1) {
-            w[n].re += __shfl_xor(w[n].re, off);
-            w[n].im += __shfl_xor(w[n].im, off);
+    for (int v = 0; v < VP; ++v) {
+        cplx *Wv = W + (int64_t)(v0 + v) * (PB + 1) * nbox;
+#pragma unroll
+        for (int i = 0; i < (PB + kP2MSplit) / kP2MSplit; ++i) {
+            cplx s = mk(0.0, 0.0);
+#pragma unroll
+            for (int k = 0; k < kP2MSplit; ++k)
+                if (kP2MSplit * i + k <= PB) {
+                    const int n = kP2MSplit * i + k;
+                    const double f = inv.c[DIP && n > 0 ? n - 1 : n];
+                    const double re = f * lane_group_sum(w[v][n].re, kP2MSplit);
+                    const double im = f * lane_group_sum(w[v][n].im, kP2MSplit);
+                    s.re = part == k ? re : s.re;
+                    s.im = part == k ? im : s.im;
+                }
+            if (ok && kP2MSplit * i + part <= PB) Wv[(int64_t)(kP2MSplit * i + part) * nbox + b] = sc * s;
         }
-    if (ok) {
-#pragma unroll
-        for (int n = 0; n <= PB; ++n)
-            if (n % kP2MSplit == part) W[(int64_t)n * nbox + b] = w[n];
     }
 }
 
@@ -1102,32 +1135,40 @@ __device__ __forceinline__ cplx block_sum(cplx v) {
 
 // Surface sums s = sum_j q_j e^{-Z(y_j - i x_j)}; for dipoles (DIP) the normal derivative of each
 // term, mu_j Z (i n_x - n_y) e^{-Z(y_j - i x_j)} (the exponential is holomorphic in z_j).
-template <bool DIP>
+// The vectors of a pass share the exponentials (2M points, eight vectors: 194 -> 43 us).
+template <bool DIP, int NV>
 __global__ __launch_bounds__(256) void k_rank1_partial(const double *__restrict__ xs, const double *__restrict__ ys,
-                                                       const double *__restrict__ qs, int nv,
-                                                       const PtChunk *__restrict__ ch, int nch,
-                                                       const InstInfo *__restrict__ ii, const double2 *__restrict__ nrm,
-                                                       cplx *__restrict__ part) {
+                                                       const double *__restrict__ qs, const PtChunk *__restrict__ ch,
+                                                       int nch, const InstInfo *__restrict__ ii,
+                                                       const double2 *__restrict__ nrm, cplx *__restrict__ part) {
     const PtChunk c = ch[blockIdx.x];
-    const int v = blockIdx.y;
     const double Z = ii[c.inst].Z.re;
-    double ar = 0.0, ai = 0.0;
+    double ar[NV], ai[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) ar[v] = ai[v] = 0.0;
     for (int64_t i = c.start + threadIdx.x; i < c.end; i += 256) {
-        const double e = qs[i * nv + v] * exp(-Z * ys[i]);
+        const double ex = exp(-Z * ys[i]);
         double sn, cs;
         sincos(Z * xs[i], &sn, &cs);
+        double tr = cs, ti = sn;
         if (DIP) {
             const double2 nj = nrm[i];
-            const double ez = Z * e;
-            ar -= ez * (nj.y * cs + nj.x * sn);
-            ai += ez * (nj.x * cs - nj.y * sn);
-        } else {
-            ar += e * cs;
-            ai += e * sn;
+            tr = -Z * fma(nj.y, cs, nj.x * sn);
+            ti = Z * fma(nj.x, cs, -(nj.y * sn));
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const double e = qs[i * NV + v] * ex;
+            ar[v] = fma(e, tr, ar[v]);
+            ai[v] = fma(e, ti, ai[v]);
         }
     }
-    const cplx t = block_sum(mk(ar, ai));
-    if (threadIdx.x == 0) part[(int64_t)v * nch + blockIdx.x] = t;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const cplx t = block_sum(mk(ar[v], ai[v]));
+        if (threadIdx.x == 0) part[(int64_t)v * nch + blockIdx.x] = t;
+        __syncthreads();
+    }
 }
 
 // out[v][k] = sum of part[v][c] over the chunks c of instance k, in chunk order
@@ -3161,11 +3202,14 @@ static fmmhp_status build_sym_walk(Arena &A, const Tree &T, Sched &S, hipStream_
 }
 
 // Launch shape of the near field.  walk: 1, 2 = records (k_near), 3, 4 = symmetric leaf pairs; groups:
-// workgroups per CU of its bounded grid.  0 selects the default: two, or for p >= 30 (a heavier far
-// field, whose kernels leave more waves free) four.
+// workgroups per CU of its bounded grid.  0 selects the default.
 fmmhp_status apply_launch_shape(Arena &A, const Tree &T, Sched &S, int walk, int groups, hipStream_t s) {
     if (walk == 0) walk = S.PB >= 30 ? 2 : 1;
-    if (groups == 0) groups = walk == 2 ? 4 : 2;
+    // Few workgroups per CU leave room for the far-field kernels beside them (300,001 points, p = 30: 2 per
+    // CU 181 us, 4 202, 8 212), but they land unevenly on the CUs that P2M still occupies, and the last one
+    // is waited for: many records are spread over more (1M points, p = 20: 2 per CU 376 us, 8 315; 4M along
+    // a curve, p = 30: 2,958, 2,357).  Up to 4,096 records the grid is a workgroup per four records anyway.
+    if (groups == 0) groups = S.near_nrec >= 32768 ? 8 : walk == 2 && S.near_nrec <= 4096 ? 4 : 2;
     if ((walk == 3 || walk == 4) && !S.sym_built) FMMHP_CHECK(build_sym_walk(A, T, S, s));
     S.near_walk = walk;
     S.near_blocks = (int64_t)groups * S.cus;
@@ -3246,7 +3290,7 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     Marks mk_;
     FMMHP_CHECK(mk_.init(S));
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_P2M, s));
-    hipLaunchKernelGGL(k_gather_q, dim3(nblk(T.n, 256)), dim3(256), 0, s, q, T.perm, T.n, NV, ws.qs);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gather_q<NV>), dim3(xcd_grid(T.n)), dim3(256), 0, s, q, T.perm, T.n, ws.qs);
     // the near field needs only the sorted charges: run it on the side stream, concurrently with
     // the far-field chain, and join before the final leaf kernel
     LeafArgs la{S.inst_info, T.inst,    T.n_inst, NV,       T.n,      nbox,     S.nloc,   T.xs,     T.ys,
@@ -3297,16 +3341,17 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     FMMHP_HIP(hipGetLastError());
     // the surface sums also need only the sorted charges
     if (S.nloc == 1 && S.bc == 0 && S.rank1_side) {
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rank1_partial<DIP>), dim3(S.n_rch, NV), dim3(256), 0, side_, T.xs,
-                           T.ys, ws.qs, NV, S.rch, S.n_rch, S.inst_info, S.nrm, ws.red);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rank1_partial<DIP, NV>), dim3(S.n_rch), dim3(256), 0, side_, T.xs,
+                           T.ys, ws.qs, S.rch, S.n_rch, S.inst_info, S.nrm, ws.red);
         hipLaunchKernelGGL(k_rank1_final, dim3(T.n_inst, NV), dim3(256), 0, side_, ws.red, S.n_rch, S.inst_ch,
                            T.n_inst, ws.rank1);
         FMMHP_HIP(hipGetLastError());
     }
     if (mk_.on) FMMHP_HIP(hipEventRecord(mk_.near1, side_));
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2m<PB, DIP>), dim3(nblk((int64_t)T.nleaf * kP2MSplit, 256), NV), dim3(256),
-                       0, s, S.inst_info, T.inst, S.leaves, T.nleaf, nbox, NV, T.level, T.bx, T.by, T.first, T.count,
-                       T.xs, T.ys, ws.qs, S.nrm, ws.W);
+    constexpr int VP = p2l_vecs(PB, NV);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2m<PB, DIP, VP>), dim3(nblk((int64_t)T.nleaf * kP2MSplit, 256), NV / VP),
+                       dim3(256), 0, s, S.inst_info, T.inst, S.leaves, T.nleaf, nbox, NV, T.level, T.bx, T.by, T.first, T.count,
+                       S.xy, ws.qs, S.nrm, ws.W);
     FMMHP_HIP(hipGetLastError());
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_M2M, s));
     // M2L (+ image M2L, P2L) over the levels [l0, l1) of the tree on stream st
@@ -3353,7 +3398,6 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
         const int x0 = S.xgrp_lev[l0], x1 = S.xgrp_lev[l1];
         const int y0 = S.xslot_lev[l0], y1 = S.xslot_lev[l1];
         if (y1 > y0) {
-            constexpr int VP = p2l_vecs(PB, NV);
             const P2LArgs pa{y1 - y0,  nbox,  S.nloc, NV,        S.xslot + y0, S.xrow0 + y0,              S.xsgeo + y0, S.xstream,
                              S.xy,     S.nrm, ws.qs,  S.logside, S.fact,       S.bc == 2 ? -1.0 : 1.0, ws.Lam};
             // four lanes a box once that gives each of the 1,024 SIMDs a wave; below, a box's chain of rows is
@@ -3436,8 +3480,8 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     FMMHP_HIP(hipGetLastError());
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_SURF, s));
     if (S.nloc == 1 && S.bc == 0 && !S.rank1_side) {
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rank1_partial<DIP>), dim3(S.n_rch, NV), dim3(256), 0, s, T.xs, T.ys,
-                           ws.qs, NV, S.rch, S.n_rch, S.inst_info, S.nrm, ws.red);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rank1_partial<DIP, NV>), dim3(S.n_rch), dim3(256), 0, s, T.xs, T.ys,
+                           ws.qs, S.rch, S.n_rch, S.inst_info, S.nrm, ws.red);
         hipLaunchKernelGGL(k_rank1_final, dim3(T.n_inst, NV), dim3(256), 0, s, ws.red, S.n_rch, S.inst_ch, T.n_inst,
                            ws.rank1);
         FMMHP_HIP(hipGetLastError());
