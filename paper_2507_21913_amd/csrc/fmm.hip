@@ -2892,9 +2892,11 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         FMMHP_HIP(hipGetLastError());  // (the geometry is filled once the instance table is on the device)
     }
     // deep split: the finest levels holding at least half of the M2L tiles run on a second stream
-    // as soon as their multipoles exist, beside the rest of the upward pass
+    // as soon as their multipoles exist, beside the rest of the upward pass.  Below 32 tiles its
+    // launches, events and waits cost the host more than the overlap gives (2,000 points: 132 us with
+    // it, 115 without; 33,000 points, 24 tiles: 176, 174; 100,000 complex points: 270, 290)
     S.deep_level = 0;
-    if (S.ntiles > 0) {
+    if (S.ntiles >= kDeepTiles) {
         for (int l = T.depth; l >= 3; --l)
             if (2 * (S.tile_lev[T.depth + 1] - S.tile_lev[l]) >= S.ntiles) {
                 S.deep_level = l;
