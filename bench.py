@@ -29,13 +29,23 @@ PEAK_FP64_TFLOPS = 78.6     # MI355X fp64 vector (and matrix) peak
 PEAK_HBM_GBS = 8000.0
 PEAK_FP32_MATRIX_TFLOPS = 157.3  # MI355X fp32 matrix peak
 
-# HBM bytes of k_m2l per evaluation measured with rocprofv3 counter runs (2.00 x FETCH_SIZE + 1.00 x
+# HBM bytes of k_m2l_pw per evaluation measured with rocprofv3 counter runs (2.00 x FETCH_SIZE + 1.00 x
 # WRITE_SIZE, the factors a plain 256 MiB copy gives), keyed by a hash of the evaluation sources and
-# (p, leaf size): reported (per launch) only while the kernels are the ones that were measured.
-# (k_m2l runs as two launches per evaluation, deep and coarse levels; the figures are their sum.)
-M2L_TRAFFIC = {("40e128ed52690a09", 20, 32): 160.0e6}
+# (p, leaf size): reported (per launch) only while the kernels are the ones that were measured (not
+# measured for the present ones).
+M2L_TRAFFIC = {}
 # k_near per launch (rocprofv3 FETCH_SIZE and WRITE_SIZE, scaled as above), same key
-NEAR_TRAFFIC = {("40e128ed52690a09", 20, 32): 52.4e6}
+NEAR_TRAFFIC = {}
+# Nodes of the plane-wave quadrature by compiled order
+PW_NODES = {5: 22, 10: 25, 15: 29, 20: 34, 25: 40, 30: 40, 35: 44, 40: 44}
+NEAR_FLOPS = 17.0  # float64 flops of a near pair: 7 FMA (log 5), 1 mul, 2 add
+
+
+def m2l_flops_of(info):
+    """Flops of the plane-wave M2L per evaluation: 2 (p + 1) multiply-adds per node at either end of
+    every box, one complex multiply-add per node and upper V pair (image pairs are k_m2l_img's)."""
+    k = PW_NODES[max(5, (info["p"] + 4) // 5 * 5)]
+    return 8.0 * k * ((info["p"] + 1) * info["nbox"] + info["m2l_pairs"][0])
 
 
 def NEAR_ALG_BYTES(info):
@@ -45,7 +55,7 @@ def NEAR_ALG_BYTES(info):
 
 
 def M2L_ALG_BYTES(info):
-    """Algorithmic HBM bytes of k_m2l per evaluation: every box's multipole read once and its local
+    """Algorithmic HBM bytes of k_m2l_pw per evaluation: every box's multipole read once and its local
     written once (16 (p + 1) bytes each)."""
     return 2.0 * 16.0 * (info["p"] + 1) * info["nbox"]
 
@@ -53,7 +63,8 @@ def M2L_ALG_BYTES(info):
 def eval_source_hash() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("fmm.hip", "internal.hpp", "special.hpp", "cplx.hpp"):
+    for f in ("fmm.hip", "tree.hip", "internal.hpp", "special.hpp", "cplx.hpp", "m2l_pw.hpp", "pw_nodes.hpp",
+              "updown.hpp", "p2l.hpp"):
         with open(os.path.join(ROOT, "paper_2507_21913_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -501,22 +512,20 @@ def main():
         print(f"accuracy check skipped: {ex}", file=sys.stderr)
 
     # roofline of the dominant kernel, from algorithmic work per launch / measured launch time
-    P1 = info["p"] + 1
-    # k_m2l: the upper-source pairs, (p + 1)^2 complex FMA (8 flops) each; image pairs are k_m2l_img's
-    m2l_flops = 8.0 * P1 * P1 * info["m2l_pairs"][0]
+    m2l_flops = m2l_flops_of(info)
     # dominant kernel: the one with the most algorithmic work per evaluation (the near field runs
     # concurrently on its own stream, so phase durations overlap)
-    near_flops = 27.0 * (info["p2p_pairs"][0] + info["p2p_pairs"][1])
+    near_flops = NEAR_FLOPS * (info["p2p_pairs"][0] + info["p2p_pairs"][1])
     dom = "m2l" if m2l_flops >= near_flops else "near"
     if dom == "m2l" and m2l_launches > 0:
-        # k_m2l runs as up to two launches per evaluation (deep levels on a second stream, coarse
+        # k_m2l_pw runs as up to two launches per evaluation (deep levels on a second stream, coarse
         # levels on the eval stream), each bracketed by HIP events on its own stream
         per_eval = m2l_launches / max(1, nev)
         fl = m2l_flops / per_eval
         avg_ms = m2l_ms_sum / m2l_launches
         achieved = fl / (avg_ms * 1e-3) / 1e12
         traffic = M2L_TRAFFIC.get((eval_source_hash(), info["p"], leaf_use))
-        roof = {"kernel": "k_m2l", "bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
+        roof = {"kernel": "k_m2l_pw", "bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
                 "traffic": None if traffic is None else traffic / per_eval,
                 "schedule": "concurrent: the launches share the GPU with the near field (the kernel alone: "
@@ -525,20 +534,19 @@ def main():
         if traffic is not None:
             roof["traffic_over_algorithmic"] = traffic / M2L_ALG_BYTES(info)
     else:
-        # near field (k_near): 27 float64 flops per pair, counted from its compiled inner loop
-        # (12 FMA incl. the table-assisted log, 2 add, 1 mul); image-source pairs counted alike
+        # near field (k_near); image-source pairs counted alike
         pairs = info["p2p_pairs"][0] + info["p2p_pairs"][1]
-        fl = 27.0 * pairs
+        fl = NEAR_FLOPS * pairs
         achieved = fl / (phase_avg["near"] * 1e-3) / 1e12
         roof = {"kernel": "k_near", "bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS, "traffic": None,
                 "flops_per_launch": fl}
 
-    # the same evaluation with every kernel on one stream: each k_m2l launch's duration is its own
+    # the same evaluation with every kernel on one stream: each M2L launch's duration is its own
     # (the concurrent schedule above shares the CUs with the near field)
     alone = None
     roof_near = None
-    if dom == "m2l":
+    if m2l_launches > 0:
         plan_s = F.HalfPlaneFMM(x, y, w.impedance, p=p_use, leaf_size=leaf_use, serial=True, **shape)
         for _ in range(2):
             plan_s(q, out=out)
@@ -555,9 +563,9 @@ def main():
         plan_s.set_timing(False)
         plan_s.close()
         # the near field alone (its phase on the one stream: k_near, the reaction pairs and the surface
-        # sums), 27 flops per pair as in the dominant-kernel fallback below
+        # sums)
         near_ms = ph_s["near"] / max(1, nev_s)
-        near_fl = 27.0 * (info["p2p_pairs"][0] + info["p2p_pairs"][1])
+        near_fl = NEAR_FLOPS * (info["p2p_pairs"][0] + info["p2p_pairs"][1])
         roof_near = {"kernel": "k_near (+ k_near_reaction, surface sums)", "bound": "alu",
                      "schedule": "every kernel on one stream (FMMHP_FLAG_SERIAL)",
                      "achieved": near_fl / (near_ms * 1e-3) / 1e12, "peak": PEAK_FP64_TFLOPS,
@@ -572,7 +580,7 @@ def main():
             per_eval_s = n_s / max(1, a.steps)
             avg_s = m2l_ms_s / n_s
             ach_s = (m2l_flops / per_eval_s) / (avg_s * 1e-3) / 1e12
-            alone = {"kernel": "k_m2l", "schedule": "every kernel on one stream (FMMHP_FLAG_SERIAL)",
+            alone = {"kernel": "k_m2l_pw", "schedule": "every kernel on one stream (FMMHP_FLAG_SERIAL)",
                      "achieved": ach_s, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                      "frac": ach_s / PEAK_FP64_TFLOPS, "avg_launch_us": avg_s * 1e3,
                      "launches_per_eval": per_eval_s, "ms_per_step_serial": ms_s}
@@ -657,7 +665,7 @@ def main():
         res["m2l_fp32"] = {"mpts_s": w.n / (ms32 * 1e-3) / 1e6, "ms_per_step": ms32, "over_fp64": ms / ms32,
                            "m2l_phase_ms": ph32["m2l"] / max(1, nev32), "rel_l2_vs_oracle_sample": rel32,
                            "kernel_alone_us_per_eval": k32_eval_ms * 1e3,
-                           "kernel_alone_frac_fp32_matrix_peak": m2l_flops / (k32_eval_ms * 1e-3) / 1e12
+                           "kernel_alone_frac_fp32_matrix_peak": 8.0 * (info["p"] + 1) ** 2 * info["m2l_pairs"][0] / (k32_eval_ms * 1e-3) / 1e12
                            / PEAK_FP32_MATRIX_TFLOPS,
                            "kernel_alone_note": "algorithmic flops 8 (p+1)^2 per upper V pair over the summed "
                                                 "duration of the FP32 row conversion and matrix-core M2L launches"}
