@@ -12,7 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfmmhp.so")
 SOURCES = ["api.hip", "tree.hip", "fmm.hip", "tune.hip"]
-HEADERS = ["cplx.hpp", "special.hpp", "internal.hpp", "m2l_pw.hpp", "pw_nodes.hpp", "updown.hpp", "p2l.hpp"]
+HEADERS = ["arena.hpp", "cplx.hpp", "special.hpp", "internal.hpp", "m2l_pw.hpp", "pw_nodes.hpp", "updown.hpp", "p2l.hpp",
+           "workspace.hpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("FMMHP_ARCH", "gfx950")

@@ -282,16 +282,21 @@ __global__ void k_take_targets(const double *__restrict__ pp, int64_t ns, int64_
     for (int v = 0; v < nv; ++v) phi[(int64_t)v * 2 * nt + t] = pp[(int64_t)v * 2 * n + 2 * ns + t];
 }
 
+// Padded charges and potentials of n_vec vectors (real or complex).
+static fmmhp_status ensure_pad(fmmhp_plan_t plan, int n_vec) {
+    if (plan->pad_cap >= n_vec) return FMMHP_OK;
+    const size_t m = (size_t)n_vec * plan->tree.n * 2;
+    FMMHP_CHECK(plan->arena.alloc_all({part(&plan->qpad, m), part(&plan->phipad, m)}, "padded charges and potentials"));
+    plan->pad_cap = n_vec;
+    return FMMHP_OK;
+}
+
 // Evaluation on a plan with separate targets: charges padded to all tree points, potentials of
 // the targets kept.  w = 1 (real charges) or 2 (complex).
 static fmmhp_status eval_targets(fmmhp_plan_t plan, int n_vec, const double *q, double *phi, int w,
                                  hipStream_t stream) {
     const int64_t n = plan->tree.n, ns = plan->n_src;
-    if (plan->pad_cap < n_vec) {
-        FMMHP_CHECK(plan->arena.alloc_n(&plan->qpad, (size_t)n_vec * n * 2, "padded charges"));
-        FMMHP_CHECK(plan->arena.alloc_n(&plan->phipad, (size_t)n_vec * n * 2, "potentials at all points"));
-        plan->pad_cap = n_vec;
-    }
+    FMMHP_CHECK(ensure_pad(plan, n_vec));
     const unsigned nb = (unsigned)((n * w + 255) / 256);
     hipLaunchKernelGGL(k_pad_charges, dim3(nb), dim3(256), 0, stream, q, ns, n, w, n_vec, plan->qpad);
     FMMHP_HIP(hipGetLastError());
@@ -356,11 +361,7 @@ fmmhp_status fmmhp_eval_double_layer(fmmhp_plan_t plan, int n_vec, const double 
         return run_eval_dlp(plan->arena, plan->tree, plan->sched, n_vec, mu, w, nx, ny, phi, stream);
     // separate targets: densities and normals padded with zeros to all tree points
     const int64_t n = plan->tree.n, ns = plan->n_src;
-    if (plan->pad_cap < n_vec) {
-        FMMHP_CHECK(plan->arena.alloc_n(&plan->qpad, (size_t)n_vec * n * 2, "padded charges"));
-        FMMHP_CHECK(plan->arena.alloc_n(&plan->phipad, (size_t)n_vec * n * 2, "potentials at all points"));
-        plan->pad_cap = n_vec;
-    }
+    FMMHP_CHECK(ensure_pad(plan, n_vec));
     if (!plan->npad) FMMHP_CHECK(plan->arena.alloc_n(&plan->npad, (size_t)2 * n, "padded normals"));
     hipLaunchKernelGGL(k_pad_charges, dim3((unsigned)((n * w + 255) / 256)), dim3(256), 0, stream, mu, ns, n, w, n_vec,
                        plan->qpad);
@@ -395,11 +396,7 @@ fmmhp_status fmmhp_eval_field(fmmhp_plan_t plan, const double *q, double *phi, d
         return run_field(plan->arena, plan->tree, plan->sched, q, phi, (cplx *)grad_x, (cplx *)grad_y, stream);
     // separate targets: charges padded to all tree points, the targets' values kept
     const int64_t n = plan->tree.n, ns = plan->n_src;
-    if (plan->pad_cap < 1) {
-        FMMHP_CHECK(plan->arena.alloc_n(&plan->qpad, (size_t)n * 2, "padded charges"));
-        FMMHP_CHECK(plan->arena.alloc_n(&plan->phipad, (size_t)n * 2, "potentials at all points"));
-        plan->pad_cap = 1;
-    }
+    FMMHP_CHECK(ensure_pad(plan, 1));
     if (!plan->gpad) FMMHP_CHECK(plan->arena.alloc_n(&plan->gpad, (size_t)n * 4, "gradients at all points"));
     hipLaunchKernelGGL(k_pad_charges, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, q, ns, n, 1, 1,
                        plan->qpad);

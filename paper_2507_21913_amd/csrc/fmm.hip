@@ -51,6 +51,7 @@
 #include "m2l_pw.hpp"
 #include "updown.hpp"
 #include "p2l.hpp"
+#include "workspace.hpp"
 
 namespace fmmhp {
 
@@ -513,9 +514,6 @@ __global__ __launch_bounds__(64 * mf_ncb(PB)) void k_m2l_mf(M2LArgs a) {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Row length of a source in the FP32 M2L: 2(p+1) embedded coefficients, the low parts of Re w_0 and
-// Im w_0, zero padding to a multiple of 4.
-__host__ __device__ constexpr int m2l32_kp(int PB) { return ((2 * (PB + 1) + 2 + 3) / 4) * 4; }
 __host__ __device__ constexpr int m2l32_np(int PB) { return ((2 * (PB + 1) + 15) / 16) * 16; }
 
 struct M2L32Args {
@@ -2609,8 +2607,6 @@ static fmmhp_status build_bands(Arena &A, const Tree &T, Sched &S, const std::ve
     return FMMHP_OK;
 }
 
-static fmmhp_status ensure_vec_ws(Arena &A, const Tree &T, Sched &S, int nv);
-
 fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cplx *Zs, hipStream_t s) {
     S.PB = PB;
     {
@@ -3518,31 +3514,6 @@ static fmmhp_status run_pass(const Tree &T, const Sched &S, const VecWs &ws, con
 }
 
 
-// Per-vector workspace (multipoles, locals, sorted charges, near-field sums, surface sums) for nv
-// vectors at once; grown on demand, owned by the plan.
-static fmmhp_status ensure_vec_ws(Arena &A, const Tree &T, Sched &S, int nv) {
-    VecWs &w = S.ws;
-    if (w.cap >= nv) return FMMHP_OK;
-    const size_t nb = (size_t)T.nbox, P1 = (size_t)S.PB + 1;
-    FMMHP_CHECK(A.alloc_n(&w.W, nv * P1 * nb, "multipoles"));
-    FMMHP_CHECK(A.alloc_n(&w.Lam, nv * (size_t)S.nloc * P1 * nb, "locals"));
-    FMMHP_CHECK(A.alloc_n(&w.qs, nv * (size_t)T.n, "sorted charges"));
-    FMMHP_CHECK(A.alloc_n(&w.near, nv * (size_t)T.n, "near-field sums"));
-    FMMHP_CHECK(A.alloc_n(&w.red, nv * (size_t)S.n_rch, "surface partial sums"));
-    FMMHP_CHECK(A.alloc_n(&w.rank1, nv * (size_t)T.n_inst, "surface sums"));
-    if (S.m2l_fp32) FMMHP_CHECK(A.alloc_n(&w.Wf, nv * nb * (size_t)m2l32_kp(S.PB), "FP32 M2L source rows"));
-    w.part = nullptr;  // the symmetric walk's partial sums come with the walk (ensure_sym_part)
-    w.cap = nv;
-    return FMMHP_OK;
-}
-
-// Partial sums of the symmetric near-field walk for the plan's workspace, allocated when the walk is
-// in use (walk 3 or 4 on a plan whose lists allow it).
-static fmmhp_status ensure_sym_part(Arena &A, Sched &S) {
-    if (!((S.near_walk == 3 || S.near_walk == 4) && S.sym_ok) || S.ws.part) return FMMHP_OK;
-    return A.alloc_n(&S.ws.part, (size_t)S.ws.cap * S.sym_npart, "near-field pair partial sums");
-}
-
 // Potentials of nvec vectors in passes of eight, four, two and one (each vector's result is the same in
 // any of them): pass(w) gives the workspace of a pass of width w, or null if it has none.
 template <class Pass>
@@ -3568,15 +3539,6 @@ static fmmhp_status eval_passes(const Tree &T, const Sched &S, int nvec, const d
 static fmmhp_status enqueue_eval(const Tree &T, const Sched &S, int nvec, const double *q, double *phi,
                                  hipStream_t s) {
     return eval_passes(T, S, nvec, q, phi, s, [&](int w) { return w <= S.ws.cap ? &S.ws : nullptr; });
-}
-
-// Workspace for the widest passes that nvec vectors take; where the memory is short, for narrower ones.
-static fmmhp_status ensure_eval_ws(Arena &A, const Tree &T, Sched &S, int nvec) {
-    for (int w = nvec >= 8 ? 8 : nvec >= 4 ? 4 : nvec >= 2 ? 2 : 1; w > S.ws.cap; w >>= 1) {
-        const fmmhp_status st = ensure_vec_ws(A, T, S, w);
-        if (st != FMMHP_ENOMEM || w == 1) return st;
-    }
-    return FMMHP_OK;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -3614,34 +3576,6 @@ static fmmhp_status scratch_on(int dev, unsigned char **out) {
     }
     *out = (unsigned char *)g_scratch_ptr[dev];
     return FMMHP_OK;
-}
-
-// Bytes of a pass workspace for nv vectors (each array aligned to 256 bytes); carves it from base
-// when base is given.
-static size_t vec_ws_layout(const Tree &T, const Sched &S, int nv, unsigned char *base, VecWs *w) {
-    const size_t nb = (size_t)T.nbox, P1 = (size_t)S.PB + 1;
-    const size_t sizes[8] = {nv * P1 * nb * sizeof(cplx), nv * (size_t)S.nloc * P1 * nb * sizeof(cplx),
-                             nv * (size_t)T.n * sizeof(double), nv * (size_t)T.n * sizeof(double2),
-                             nv * (size_t)S.n_rch * sizeof(cplx), nv * (size_t)T.n_inst * sizeof(cplx),
-                             S.m2l_fp32 ? nv * nb * (size_t)m2l32_kp(S.PB) * sizeof(float) : 0,
-                             S.sym_ok && (S.near_walk == 3 || S.near_walk == 4) ? nv * (size_t)S.sym_npart * sizeof(double) : 0};
-    size_t off[8], at = 0;
-    for (int k = 0; k < 8; ++k) {
-        off[k] = at;
-        at += (sizes[k] + 255) / 256 * 256;
-    }
-    if (base) {
-        w->cap = nv;
-        w->W = (cplx *)(base + off[0]);
-        w->Lam = (cplx *)(base + off[1]);
-        w->qs = (double *)(base + off[2]);
-        w->near = (double2 *)(base + off[3]);
-        w->red = (cplx *)(base + off[4]);
-        w->rank1 = (cplx *)(base + off[5]);
-        w->Wf = S.m2l_fp32 ? (float *)(base + off[6]) : nullptr;
-        w->part = S.sym_ok && (S.near_walk == 3 || S.near_walk == 4) ? (double *)(base + off[7]) : nullptr;
-    }
-    return at;
 }
 
 fmmhp_status run_eval_noalloc(const Tree &T, const Sched &S, int device, int nvec, const double *q, double *phi,
@@ -3728,18 +3662,7 @@ __global__ void k_combine_complex(const double *__restrict__ p2, int64_t n, doub
 fmmhp_status run_eval_complex(Arena &A, const Tree &T, Sched &S, int nvec, const double *q, double *phi,
                               hipStream_t s) {
     // up to four complex vectors at once: one pass of eight real ones; where the memory is short, fewer
-    for (int g = std::min(nvec, kVecChunk / 2); g > S.ccap; g = g > 1 ? g / 2 : 0) {
-        double *cq = nullptr, *cphi = nullptr;
-        fmmhp_status st = A.alloc_n(&cq, (size_t)2 * g * T.n, "complex-charge split");
-        if (st == FMMHP_OK) st = A.alloc_n(&cphi, (size_t)4 * g * T.n, "complex-charge potentials");
-        if (st == FMMHP_OK) {
-            S.cq = cq;
-            S.cphi = cphi;
-            S.ccap = g;
-        } else if (st != FMMHP_ENOMEM || g == 1) {
-            return st;
-        }
-    }
+    FMMHP_CHECK(widen(std::min(nvec, kVecChunk / 2), S.ccap, S.ccap_limit, [&](int g) { return ensure_split(A, T, S, g); }));
     int step = std::min(S.ccap, nvec);
     if (S.use_graph)  // one recorded graph serves every group
         while (nvec % step) --step;
@@ -3774,11 +3697,7 @@ fmmhp_status run_eval_dlp(Arena &A, const Tree &T, Sched &S, int nvec, const dou
     if (!S.nrm) FMMHP_CHECK(A.alloc_n(&S.nrm, (size_t)T.n, "sorted normals"));
     hipLaunchKernelGGL(k_gather_nrm, dim3(nblk(T.n, 256)), dim3(256), 0, s, nx, ny, T.perm, T.n, S.nrm);
     FMMHP_HIP(hipGetLastError());
-    if (w == 2 && !S.cq) {
-        FMMHP_CHECK(A.alloc_n(&S.cq, (size_t)2 * T.n, "complex-charge split"));
-        FMMHP_CHECK(A.alloc_n(&S.cphi, (size_t)4 * T.n, "complex-charge potentials"));
-        S.ccap = 1;
-    }
+    if (w == 2) FMMHP_CHECK(ensure_split(A, T, S, 1));
     for (int v = 0; v < nvec; ++v) {
         if (w == 1) {
             PassOut o;
@@ -3866,19 +3785,6 @@ __global__ __launch_bounds__(256) void k_bwd_combine(BwdArgs a) {
     }
     const cplx t = block_sum(mk(ar, ai));
     if (threadIdx.x == 0) a.part[blockIdx.x] = t;
-}
-
-static fmmhp_status ensure_bwd(Arena &A, const Tree &T, Sched &S) {
-    if (S.bw.ready) return FMMHP_OK;
-    const size_t n = (size_t)T.n;
-    BwdWork &b = S.bw;
-    FMMHP_CHECK(A.alloc_n(&b.q3, 3 * n, "adjoint charge vectors"));
-    FMMHP_CHECK(A.alloc_n(&b.qc, n, "coincident charge sums"));
-    cplx **bufs[] = {&b.phi3, &b.gx3, &b.gy3, &b.near_gx, &b.near_gy};
-    for (cplx **pp : bufs) FMMHP_CHECK(A.alloc_n(pp, 3 * n, "adjoint fields"));
-    FMMHP_CHECK(A.alloc_n(&b.red, (size_t)S.n_rch + T.n_inst, "adjoint reduction"));
-    b.ready = true;
-    return FMMHP_OK;
 }
 
 __global__ void k_zero_f64(double *__restrict__ p, int64_t n) {

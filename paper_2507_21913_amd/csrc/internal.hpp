@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/fmmhp.h"
+#include "arena.hpp"
 #include "cplx.hpp"
 
 namespace fmmhp {
@@ -47,8 +48,6 @@ __host__ __device__ constexpr int m2l_row(int PB) {
                : 8 * mf_ncb(PB) + 4 * mf_nks(PB) - 1;
 }
 
-void set_error(const char *fmt, ...);
-
 #define FMMHP_HIP(expr)                                                              \
     do {                                                                             \
         hipError_t e_ = (expr);                                                      \
@@ -64,24 +63,6 @@ void set_error(const char *fmt, ...);
         fmmhp_status s_ = (expr);            \
         if (s_ != FMMHP_OK) return s_;       \
     } while (0)
-
-// Device allocations owned by one plan.  Arrays share slabs (a plan holds some 90 arrays; a hipMalloc and
-// a hipFree for each took 5 of the 11 ms of a 200,000-point training step): a slab is twice as large as
-// everything allocated so far, from 1 to 64 MB; an array that does not fit one has an allocation of its
-// own.
-struct Arena {
-    std::vector<void *> ptrs;  // slabs and large arrays
-    int64_t bytes = 0;         // requested
-    int count = 0;             // arrays
-    char *cur = nullptr;       // the open slab
-    size_t left = 0;
-    fmmhp_status alloc(void **p, size_t nbytes, const char *what);
-    template <class T>
-    fmmhp_status alloc_n(T **p, size_t n, const char *what) {
-        return alloc((void **)p, (n ? n : 1) * sizeof(T), what);
-    }
-    void release();
-};
 
 struct Tree {
     int64_t n = 0;
@@ -268,9 +249,11 @@ struct Sched {
     PtChunk *rch = nullptr;         // [n_rch]
     int32_t *inst_ch = nullptr;     // [n_inst + 1] chunk range of each instance
     VecWs ws;                       // workspace of the plan's own evaluations
+    int ws_limit = kVecChunk;       // widest pass whose workspace may be tried
     BwdWork bw;
     double *cq = nullptr, *cphi = nullptr;  // complex-charge workspace ([2 ccap][n], [2 ccap][n][2])
     int ccap = 0;                           // complex vectors it holds
+    int ccap_limit = kVecChunk / 2;         // most that may be tried
     double2 *nrm = nullptr;         // [n] source normals in sorted order (double-layer evaluation)
     // recorded evaluation (FMMHP_FLAG_GRAPH)
     bool use_graph = false;

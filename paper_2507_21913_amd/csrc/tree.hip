@@ -39,58 +39,6 @@ namespace fmmhp {
 // ---------------------------------------------------------------------------------------------
 // Arena
 // ---------------------------------------------------------------------------------------------
-fmmhp_status Arena::alloc(void **p, size_t nbytes, const char *what) {
-    *p = nullptr;
-    if (getenv("FMMHP_TEST_FAIL_ALLOC")) {
-        long k = atol(getenv("FMMHP_TEST_FAIL_ALLOC"));
-        if (k > 0 && (long)count + 1 == k) {
-            set_error("allocation of %s (%zu bytes) failed (test hook)", what, nbytes);
-            return FMMHP_ENOMEM;
-        }
-    }
-    const size_t need = (nbytes + 255) / 256 * 256;
-    if (need > left) {
-        const size_t slab = std::min<size_t>((size_t)64 << 20, std::max<size_t>((size_t)1 << 20, 2 * (size_t)bytes));
-        bool own = need >= slab;
-        void *m = nullptr;
-        hipError_t e = hipMalloc(&m, own ? nbytes : slab);
-        if (e != hipSuccess && !own) {  // no room for a slab: the array alone
-            (void)hipGetLastError();
-            own = true;
-            e = hipMalloc(&m, nbytes);
-        }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            set_error("hipMalloc of %s (%zu bytes) failed: %s", what, nbytes, hipGetErrorString(e));
-            return FMMHP_ENOMEM;
-        }
-        ptrs.push_back(m);
-        if (own) {
-            *p = m;
-        } else {
-            cur = (char *)m;
-            left = slab;
-        }
-    }
-    if (!*p) {
-        *p = cur;
-        cur += need;
-        left -= need;
-    }
-    bytes += (int64_t)nbytes;
-    ++count;
-    return FMMHP_OK;
-}
-
-void Arena::release() {
-    for (void *p : ptrs) (void)hipFree(p);
-    ptrs.clear();
-    bytes = 0;
-    count = 0;
-    cur = nullptr;
-    left = 0;
-}
-
 // Build-time temporaries (stream-ordered), carved from slabs of at least `slab` bytes and given back
 // together at the end of the scope.
 struct Scratch {

@@ -1,0 +1,85 @@
+// Workspaces that a plan's evaluations grow on demand.  Each is one allocation: where it fails, the
+// workspace stays what it was, and what fitted before still runs.
+#pragma once
+#include "internal.hpp"
+
+namespace fmmhp {
+
+// Row length of a source in the FP32 M2L: 2(p+1) embedded coefficients, the low parts of Re w_0 and
+// Im w_0, zero padding to a multiple of 4.
+__host__ __device__ constexpr int m2l32_kp(int PB) { return ((2 * (PB + 1) + 2 + 3) / 4) * 4; }
+
+// Bytes of a pass workspace for nv vectors (each array aligned to 256 bytes); carves it from base
+// when base is given.
+inline size_t vec_ws_layout(const Tree &T, const Sched &S, int nv, unsigned char *base, VecWs *w) {
+    const size_t nb = (size_t)T.nbox, P1 = (size_t)S.PB + 1;
+    const size_t sizes[8] = {nv * P1 * nb * sizeof(cplx), nv * (size_t)S.nloc * P1 * nb * sizeof(cplx),
+                             nv * (size_t)T.n * sizeof(double), nv * (size_t)T.n * sizeof(double2),
+                             nv * (size_t)S.n_rch * sizeof(cplx), nv * (size_t)T.n_inst * sizeof(cplx),
+                             S.m2l_fp32 ? nv * nb * (size_t)m2l32_kp(S.PB) * sizeof(float) : 0,
+                             S.sym_ok && (S.near_walk == 3 || S.near_walk == 4) ? nv * (size_t)S.sym_npart * sizeof(double) : 0};
+    size_t off[8], at = 0;
+    for (int k = 0; k < 8; ++k) {
+        off[k] = at;
+        at += (sizes[k] + 255) / 256 * 256;
+    }
+    if (base) {
+        w->cap = nv;
+        w->W = (cplx *)(base + off[0]);
+        w->Lam = (cplx *)(base + off[1]);
+        w->qs = (double *)(base + off[2]);
+        w->near = (double2 *)(base + off[3]);
+        w->red = (cplx *)(base + off[4]);
+        w->rank1 = (cplx *)(base + off[5]);
+        w->Wf = S.m2l_fp32 ? (float *)(base + off[6]) : nullptr;
+        w->part = S.sym_ok && (S.near_walk == 3 || S.near_walk == 4) ? (double *)(base + off[7]) : nullptr;
+    }
+    return at;
+}
+
+// Per-vector workspace (multipoles, locals, sorted charges, near-field sums, surface sums) for nv
+// vectors at once; grown on demand, owned by the plan.  One allocation: where it fails, the workspace
+// stays what it was.
+inline fmmhp_status ensure_vec_ws(Arena &A, const Tree &T, Sched &S, int nv) {
+    if (S.ws.cap >= nv) return FMMHP_OK;
+    unsigned char *base = nullptr;
+    FMMHP_CHECK(A.alloc_n(&base, vec_ws_layout(T, S, nv, nullptr, nullptr), "pass workspace"));
+    vec_ws_layout(T, S, nv, base, &S.ws);
+    return FMMHP_OK;
+}
+
+// Partial sums of the symmetric near-field walk for the plan's workspace, allocated when the walk is
+// in use (walk 3 or 4 on a plan whose lists allow it).
+inline fmmhp_status ensure_sym_part(Arena &A, Sched &S) {
+    if (!((S.near_walk == 3 || S.near_walk == 4) && S.sym_ok) || S.ws.part) return FMMHP_OK;
+    return A.alloc_n(&S.ws.part, (size_t)S.ws.cap * S.sym_npart, "near-field pair partial sums");
+}
+
+// Workspace for the widest passes that nvec vectors take; where the memory is short, for narrower ones.
+inline fmmhp_status ensure_eval_ws(Arena &A, const Tree &T, Sched &S, int nvec) {
+    return widen(nvec >= 8 ? 8 : nvec >= 4 ? 4 : nvec >= 2 ? 2 : 1, S.ws.cap, S.ws_limit,
+                 [&](int w) { return ensure_vec_ws(A, T, S, w); });
+}
+
+// Split charges and the potentials of their parts, for g complex vectors.
+inline fmmhp_status ensure_split(Arena &A, const Tree &T, Sched &S, int g) {
+    if (S.ccap >= g) return FMMHP_OK;
+    FMMHP_CHECK(A.alloc_all({part(&S.cq, (size_t)2 * g * T.n), part(&S.cphi, (size_t)4 * g * T.n)},
+                            "complex-charge workspace"));
+    S.ccap = g;
+    return FMMHP_OK;
+}
+
+inline fmmhp_status ensure_bwd(Arena &A, const Tree &T, Sched &S) {
+    if (S.bw.ready) return FMMHP_OK;
+    const size_t n = (size_t)T.n;
+    BwdWork &b = S.bw;
+    FMMHP_CHECK(A.alloc_all({part(&b.q3, 3 * n), part(&b.qc, n), part(&b.phi3, 3 * n), part(&b.gx3, 3 * n),
+                             part(&b.gy3, 3 * n), part(&b.near_gx, 3 * n), part(&b.near_gy, 3 * n),
+                             part(&b.red, (size_t)S.n_rch + T.n_inst)},
+                            "adjoint workspace"));
+    b.ready = true;
+    return FMMHP_OK;
+}
+
+}  // namespace fmmhp
