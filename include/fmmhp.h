@@ -218,10 +218,13 @@ fmmhp_status fmmhp_batch_plan_create(int n_inst, const int64_t *offsets, const d
  *           points of all instances)
  *   phi     [device] output, [n_vec][n][2] (re, im) interleaved, caller's point order
  *
- * Vectors are evaluated eight at a time where possible: the near field computes each pair's kernel
- * once for the eight, the far-field kernels take the vector as a grid dimension.  The first call
- * with n_vec >= 8 grows the plan's workspace for eight vectors.  Complex charges: see
- * fmmhp_eval_complex.  No host synchronisation.
+ * Vectors are evaluated in passes of eight, four, two and one: the near field computes each pair's
+ * kernel once for a pass, the far-field kernels share what does not depend on the charges; a vector's
+ * result is the same in any of them.  A call of two or more vectors grows the plan's workspace to its
+ * widest pass the first time; the plan keeps the narrower workspace as well, which a recorded graph may
+ * hold.  Where the memory is short, and while stream records a graph of the caller's, the call takes the
+ * widest passes that the present workspace serves instead (warm up with the same n_vec before recording
+ * for the wide ones).  Complex charges: see fmmhp_eval_complex.  No host synchronisation.
  */
 fmmhp_status fmmhp_eval(fmmhp_plan_t plan, int n_vec, const double *q, double *phi,
                         hipStream_t stream);
@@ -234,8 +237,8 @@ fmmhp_status fmmhp_eval(fmmhp_plan_t plan, int n_vec, const double *q, double *p
  * not used).  Same arguments, layout, ordering and results as fmmhp_eval, for plans whose points are
  * the targets (fmmhp_plan_create, fmmhp_batch_plan_create).
  *
- * Eight vectors share a pass when their workspace fits the array, else vectors run one at a time;
- * the workspace of one vector is 16 (p + 1)(1 + nloc) bytes per box plus 24 bytes per point (nloc =
+ * Eight, four or two vectors share a pass when their workspace fits the array, else vectors run one at
+ * a time; the workspace of one vector is 16 (p + 1)(1 + nloc) bytes per box plus 24 bytes per point (nloc =
  * 1 for a real impedance, 2 for a complex one, p rounded up to a multiple of 5).  The plan's device
  * must be the current device.  The first call on a device looks up the array's address there
  * (hipGetSymbolAddress); each device holds the array until the process ends.  Every call on a device
@@ -253,14 +256,15 @@ fmmhp_status fmmhp_eval_noalloc(fmmhp_plan_t plan, int n_vec, const double *q, d
                                 hipStream_t stream);
 
 /* Evaluate phi = A q for n_vec complex charge vectors: the operator is linear over the reals in the
- * charges, so phi[q] = phi[Re q] + i phi[Im q], computed as two real passes and combined on the
+ * charges, so phi[q] = phi[Re q] + i phi[Im q], computed as two real vectors each and combined on the
  * device (eqs. (potential1), (1.2), (reactioncomp1) with complex q_j).
  *
  *   q     [device] charges, [n_vec][n][2] (re, im) interleaved, caller's point order
  *   phi   [device] output, [n_vec][n][2], caller's point order
  *
- * The first call allocates 48 bytes per point of workspace, owned by the plan.  No host
- * synchronisation.  Errors as for fmmhp_eval.
+ * Up to four complex vectors share a pass of eight real ones; the first call allocates 48 bytes per point
+ * and vector of the pass, owned by the plan, and the pass workspace of fmmhp_eval grows as it does there.
+ * No host synchronisation.  Errors as for fmmhp_eval.
  */
 fmmhp_status fmmhp_eval_complex(fmmhp_plan_t plan, int n_vec, const double *q, double *phi,
                                 hipStream_t stream);

@@ -3605,7 +3605,7 @@ fmmhp_status run_eval_noalloc(const Tree &T, const Sched &S, int device, int nve
 }
 
 fmmhp_status run_eval(Arena &A, const Tree &T, Sched &S, int nvec, const double *q, double *phi, hipStream_t s) {
-    FMMHP_CHECK(ensure_eval_ws(A, T, S, nvec));
+    FMMHP_CHECK(grow_eval_ws(A, T, S, nvec, s));
     FMMHP_CHECK(ensure_sym_part(A, S));
     if (!S.use_graph || S.timing || s == nullptr) return enqueue_eval(T, S, nvec, q, phi, s);
     auto &G = S.graph;
@@ -3661,8 +3661,7 @@ __global__ void k_combine_complex(const double *__restrict__ p2, int64_t n, doub
 
 fmmhp_status run_eval_complex(Arena &A, const Tree &T, Sched &S, int nvec, const double *q, double *phi,
                               hipStream_t s) {
-    // up to four complex vectors at once: one pass of eight real ones; where the memory is short, fewer
-    FMMHP_CHECK(widen(std::min(nvec, kVecChunk / 2), S.ccap, S.ccap_limit, [&](int g) { return ensure_split(A, T, S, g); }));
+    FMMHP_CHECK(grow_split(A, T, S, nvec, s));
     int step = std::min(S.ccap, nvec);
     if (S.use_graph)  // one recorded graph serves every group
         while (nvec % step) --step;

@@ -55,10 +55,38 @@ inline fmmhp_status ensure_sym_part(Arena &A, Sched &S) {
     return A.alloc_n(&S.ws.part, (size_t)S.ws.cap * S.sym_npart, "near-field pair partial sums");
 }
 
+// Widest pass that nvec vectors take.
+inline int pass_width(int nvec) { return nvec >= 8 ? 8 : nvec >= 4 ? 4 : nvec >= 2 ? 2 : 1; }
+
 // Workspace for the widest passes that nvec vectors take; where the memory is short, for narrower ones.
 inline fmmhp_status ensure_eval_ws(Arena &A, const Tree &T, Sched &S, int nvec) {
-    return widen(nvec >= 8 ? 8 : nvec >= 4 ? 4 : nvec >= 2 ? 2 : 1, S.ws.cap, S.ws_limit,
-                 [&](int w) { return ensure_vec_ws(A, T, S, w); });
+    return widen(pass_width(nvec), S.ws.cap, S.ws_limit, [&](int w) { return ensure_vec_ws(A, T, S, w); });
+}
+
+// Whether s records a graph.  A workspace is then taken as it is: an allocation is refused there.
+inline bool recording(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Lets this thread allocate while another stream or thread records a graph.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+};
+
+// ensure_eval_ws for a call on s: narrower passes rather than an allocation within a recording.
+inline fmmhp_status grow_eval_ws(Arena &A, const Tree &T, Sched &S, int nvec, hipStream_t s) {
+    if (S.ws.cap >= std::min(pass_width(nvec), S.ws_limit) || recording(s)) return FMMHP_OK;
+    RelaxedCapture relaxed;
+    return ensure_eval_ws(A, T, S, nvec);
 }
 
 // Split charges and the potentials of their parts, for g complex vectors.
@@ -68,6 +96,16 @@ inline fmmhp_status ensure_split(Arena &A, const Tree &T, Sched &S, int g) {
                             "complex-charge workspace"));
     S.ccap = g;
     return FMMHP_OK;
+}
+
+// Split workspace of a call of nvec complex vectors on s: up to four at once (one pass of eight real ones);
+// where the memory is short, fewer, and within a recording those that there are.
+inline fmmhp_status grow_split(Arena &A, const Tree &T, Sched &S, int nvec, hipStream_t s) {
+    auto grow = [&](int g) { return ensure_split(A, T, S, g); };
+    if (S.ccap == 0) return widen(std::min(nvec, kVecChunk / 2), 0, S.ccap_limit, grow);
+    if (S.ccap >= std::min(nvec, S.ccap_limit) || recording(s)) return FMMHP_OK;
+    RelaxedCapture relaxed;
+    return widen(std::min(nvec, kVecChunk / 2), S.ccap, S.ccap_limit, grow);
 }
 
 inline fmmhp_status ensure_bwd(Arena &A, const Tree &T, Sched &S) {
