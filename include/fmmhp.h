@@ -70,9 +70,11 @@ typedef struct {
                        one of FMMHP_FLAG_DIRICHLET, FMMHP_FLAG_NEUMANN */
     /* Launch shape of the near field (the U-list sums), which runs beside the far-field kernels on
      * a bounded grid.  Neither changes what is computed beyond rounding; fmmhp_tune picks both by
-     * timing.  0 selects the default for the plan's p. */
-    int near_walk;   /* 0: default; 1, 2: a wave per leaf, its targets in registers against the stream
-                        of its sources (2: the default grid is twice as large); 3: symmetric
+     * timing.  0 selects the default for the plan's p and its near-field records (up to 64 targets of
+     * one leaf each). */
+    int near_walk;   /* 0: default; 1, 2: a wave per record, its targets in registers against the stream
+                        of its sources (one kernel; the default near_groups of walk 2 is 4 instead of 2
+                        up to 4,096 records, from 32,768 that of both is 8); 3: symmetric
                         leaf pairs (potential evaluations: each pair of leaves once, its column
                         sums gathered by a second kernel; other passes use walk 1); 4: symmetric
                         leaf pairs with the pairs blocked in registers (each lane holds up to 8
@@ -441,8 +443,9 @@ fmmhp_status fmmhp_reaction_integrals(int64_t m, const double *x, const double *
  *   leaf_sizes   [host] candidate leaf sizes (n_leaf entries), or NULL for {24, 32, 40, 48, 64, 96}
  *   sample       targets in the accuracy sample, 1..n (0 selects min(n, 256))
  *   best         [host] receives the chosen options (p, leaf_size, and the launch shape
- *                near_walk, near_groups timed on the chosen plan, six shapes (walks 1, 2 and 4 on
- *                two to eight workgroups per CU) in turn over three rounds; a shape other than the
+ *                near_walk, near_groups timed on the chosen plan: its default, walk 1 on two, four
+ *                and eight workgroups per CU and walk 4 on four and eight, where their launches
+ *                differ, in turn over three rounds; a shape other than the plan's own
  *                default needs to be more than 2% faster; then the FP64 M2L form:
  *                FMMHP_FLAG_M2L_MFMA instead of the default when more than 2% faster; then
  *                flags gets FMMHP_FLAG_M2L_FP32 when the FP32 matrix-core M2L on that plan and

@@ -314,6 +314,28 @@ fmmhp_status run_direct(int64_t ns, const double *sx, const double *sy, int nvec
 fmmhp_status run_reaction_integrals(int64_t m, const double *x, const double *y, int nmax, cplx Z,
                                     double *out, hipStream_t stream);
 
+// Near-field launch shapes that the tuner times on a plan: its default first, then the record walk on two,
+// four and eight workgroups per CU and the blocked symmetric walk on four and eight, without those that
+// launch the same grid of the same kernel as an earlier one (walks 1 and 2 are one kernel, whose grid is at
+// most a workgroup per four records).
+struct NearShape {
+    int walk, groups;
+};
+inline std::vector<NearShape> tune_shapes(NearShape def, int nrec, int cus) {
+    auto kernel = [](const NearShape &a) { return a.walk <= 2 ? 1 : a.walk; };
+    auto grid = [&](const NearShape &a) {
+        const int64_t g = (int64_t)a.groups * cus, most = ((int64_t)nrec + 3) / 4;
+        return a.walk <= 2 && g > most ? most : g;
+    };
+    std::vector<NearShape> out{def};
+    for (const NearShape c : {NearShape{1, 2}, NearShape{1, 4}, NearShape{1, 8}, NearShape{4, 4}, NearShape{4, 8}}) {
+        bool known = false;
+        for (const NearShape &a : out) known = known || (kernel(a) == kernel(c) && grid(a) == grid(c));
+        if (!known) out.push_back(c);
+    }
+    return out;
+}
+
 inline int pick_bucket(int p) {
     int b = ((p + 4) / 5) * 5;
     return b < 5 ? 5 : b;

@@ -173,32 +173,32 @@ extern "C" fmmhp_status fmmhp_tune(int64_t n, const double *x, const double *y, 
     }
     // launch shape of the near field on the chosen plan: the shapes are timed in turn over three
     // rounds (so that a drift of the clocks favours none), each by the median of its rounds; another
-    // shape replaces the library default only when it is more than 2% faster
+    // shape replaces the plan's default only when it is more than 2% faster
     if (st == FMMHP_OK && best_ms < INFINITY) {
         fmmhp_plan_t plan = nullptr;
         st = fmmhp_plan_create(n, x, y, nullptr, nullptr, lambda_re, lambda_im, &bo, s, &plan);
         if (st == FMMHP_OK) {
-            constexpr int kShapes = 6, kRounds = 3;
-            static const int shapes[kShapes][2] = {{1, 2}, {1, 4}, {2, 4}, {2, 8}, {4, 4}, {4, 8}};
-            const int def_walk = plan->sched.near_walk, def_groups = (int)(plan->sched.near_blocks / plan->sched.cus);
-            double t[kShapes][kRounds];
+            constexpr int kRounds = 3;
+            const Sched &S = plan->sched;
+            const std::vector<NearShape> shapes =
+                tune_shapes(NearShape{S.near_walk, (int)(S.near_blocks / S.cus)}, S.near_nrec, S.cus);
+            std::vector<double> t(shapes.size() * kRounds), med(shapes.size());
             for (int r = 0; r < kRounds && st == FMMHP_OK; ++r)
-                for (int k = 0; k < kShapes && st == FMMHP_OK; ++k) {
-                    st = apply_launch_shape(plan->arena, plan->tree, plan->sched, shapes[k][0], shapes[k][1], s);
-                    if (st == FMMHP_OK) st = mean_ms(plan, n_vec, qv, phi, e0, e1, s, &t[k][r]);
+                for (size_t k = 0; k < shapes.size() && st == FMMHP_OK; ++k) {
+                    st = apply_launch_shape(plan->arena, plan->tree, plan->sched, shapes[k].walk, shapes[k].groups, s);
+                    if (st == FMMHP_OK) st = mean_ms(plan, n_vec, qv, phi, e0, e1, s, &t[k * kRounds + r]);
                 }
             if (st == FMMHP_OK) {
-                double med[kShapes];
-                int kd = 0, kb = 0;
-                for (int k = 0; k < kShapes; ++k) {
-                    std::sort(t[k], t[k] + kRounds);
-                    med[k] = t[k][kRounds / 2];
-                    if (shapes[k][0] == def_walk && shapes[k][1] == def_groups) kd = k;
+                size_t kb = 0;
+                for (size_t k = 0; k < shapes.size(); ++k) {
+                    double *tk = t.data() + k * kRounds;
+                    std::sort(tk, tk + kRounds);
+                    med[k] = tk[kRounds / 2];
                     if (med[k] < med[kb]) kb = k;
                 }
-                const int k = med[kb] < 0.98 * med[kd] ? kb : kd;
-                bo.near_walk = shapes[k][0];
-                bo.near_groups = shapes[k][1];
+                const size_t k = med[kb] < 0.98 * med[0] ? kb : 0;  // 0: the plan's default
+                bo.near_walk = shapes[k].walk;
+                bo.near_groups = shapes[k].groups;
                 best_ms = med[k];
             }
             (void)fmmhp_plan_destroy(plan);
