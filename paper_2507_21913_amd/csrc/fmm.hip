@@ -2888,11 +2888,13 @@ fmmhp_status build_schedule(Arena &A, const Tree &T, Sched &S, int PB, const cpl
         FMMHP_HIP(hipGetLastError());  // (the geometry is filled once the instance table is on the device)
     }
     // deep split: the finest levels holding at least half of the M2L tiles run on a second stream
-    // as soon as their multipoles exist, beside the rest of the upward pass.  Below 32 tiles its
-    // launches, events and waits cost the host more than the overlap gives (2,000 points: 132 us with
-    // it, 115 without; 33,000 points, 24 tiles: 176, 174; 100,000 complex points: 270, 290)
+    // as soon as their multipoles exist, beside the rest of the upward pass.  Below 32 tiles of the
+    // plane-wave form its launches, events and waits cost the host more than the overlap gives (2,000
+    // points: 132 us with it, 115 without; 33,000 points, 24 tiles: 176, 174; 100,000 complex points: 270,
+    // 290).  The Hankel forms' tiles hold half as many targets and take several times as long: they split
+    // whenever there is a tile.
     S.deep_level = 0;
-    if (S.ntiles >= kDeepTiles) {
+    if (S.ntiles >= (hankel ? 1 : kDeepTiles)) {
         for (int l = T.depth; l >= 3; --l)
             if (2 * (S.tile_lev[T.depth + 1] - S.tile_lev[l]) >= S.ntiles) {
                 S.deep_level = l;

@@ -16,7 +16,7 @@ constexpr int kLBits = 30;        // integer cell bits per axis of the root squa
 constexpr int kLBitsForest = 27;  // the same in a forest (instance index in the top key bits)
 constexpr int kMaxInstances = 512;
 constexpr int kVecChunk = 8;        // charge vectors evaluated together
-constexpr int kDeepTiles = 32;      // M2L tiles from which the deep levels get a stream of their own
+constexpr int kDeepTiles = 32;      // plane-wave M2L tiles from which the deep levels get a stream of their own
 constexpr int kNearHeavyGroups = 8; // near-field workgroups per CU at least, for gradient and dipole passes
 constexpr size_t kNoAllocScratchBytes = (size_t)128 << 20;  // device scratch of fmmhp_eval_noalloc
 constexpr int64_t kSurfChunk = 2048;  // points per partial sum of the surface term
