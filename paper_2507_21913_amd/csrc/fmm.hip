@@ -1970,6 +1970,8 @@ __device__ __forceinline__ void m2p_record(const LeafArgs &a, int lane, const WR
     }
 }
 
+constexpr int kM2PRecords = 1 << 25;  // records of a launch at most, a wave each (a launch holds less than 2^32 threads)
+
 template <int PB, int MODE, int NV>
 __global__ __launch_bounds__(256, 2) void k_m2p(LeafArgs a) {
     const int lane = threadIdx.x & 63;
@@ -3445,7 +3447,12 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     if (S.nwrec > 0) {
         FMMHP_HIP(hipEventRecord(S.ev_up, s));
         FMMHP_HIP(hipStreamWaitEvent(side_, S.ev_up, 0));
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2p<PB, LM, NV>), dim3(nblk(S.nwrec, 4)), dim3(256), 0, side_, la);
+        for (int r0 = 0; r0 < S.nwrec; r0 += kM2PRecords) {
+            LeafArgs lw = la;
+            lw.wrec += r0;
+            lw.nwrec = std::min(kM2PRecords, S.nwrec - r0);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2p<PB, LM, NV>), dim3(nblk(lw.nwrec, 4)), dim3(256), 0, side_, lw);
+        }
         if (S.bc == 0 && S.n_wipts > 0)
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_m2p_react<PB, LM, NV>), dim3(nblk(S.n_wipts * kReactLanes, 128)), dim3(128), 0,
                                side_, la);

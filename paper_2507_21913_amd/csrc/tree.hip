@@ -761,8 +761,10 @@ __global__ __launch_bounds__(256) void k_list_counts(TreeView t, int nbox, const
 }
 
 // Image V entries (source << 5 | offset slot), and the near-field records and source streams: a leaf's
-// own points, the other free U entries' in list order, the image ones'.
-__global__ __launch_bounds__(64) void k_list_fill(TreeView t, const int32_t *__restrict__ first,
+// own points, the other free U entries' in list order, the image ones'.  A workgroup takes every
+// gridDim-th box: a box each would ask for more threads than a launch may have from 2^26 boxes on.
+constexpr int kFillBlocks = 1 << 16;
+__global__ __launch_bounds__(64) void k_list_fill(TreeView t, int nbox, const int32_t *__restrict__ first,
                                                   const int32_t *__restrict__ count, const int32_t *__restrict__ uoff,
                                                   const int32_t *__restrict__ uent, const int32_t *__restrict__ voff,
                                                   const int32_t *__restrict__ vent, const int32_t *__restrict__ vimg_off,
@@ -771,34 +773,36 @@ __global__ __launch_bounds__(64) void k_list_fill(TreeView t, const int32_t *__r
                                                   const int32_t *__restrict__ roff, NearRec *__restrict__ rec,
                                                   int32_t *__restrict__ stream, const int32_t *__restrict__ woff,
                                                   const int32_t *__restrict__ wroff, int4 *__restrict__ wrec) {
-    const int b = blockIdx.x, lane = threadIdx.x;
-    if (lane == 0 && vimg_off[b + 1] > vimg_off[b]) {
-        int32_t *out = vimg_ent + vimg_off[b];
-        const int l = t.level[b];
-        for (int e = voff[b]; e < voff[b + 1]; ++e) {
-            if (!(vent[e] & 1)) continue;
-            const int c = vent[e] >> 1;
-            const int dx = t.bx[c] - t.bx[b], dy = (1 << l) - 1 - t.by[c] - t.by[b];
-            *out++ = (c << 5) | ((dy + 3) * 7 + dx + 3);
+    const int lane = threadIdx.x;
+    for (int b = blockIdx.x; b < nbox; b += gridDim.x) {
+        if (lane == 0 && vimg_off[b + 1] > vimg_off[b]) {
+            int32_t *out = vimg_ent + vimg_off[b];
+            const int l = t.level[b];
+            for (int e = voff[b]; e < voff[b + 1]; ++e) {
+                if (!(vent[e] & 1)) continue;
+                const int c = vent[e] >> 1;
+                const int dx = t.bx[c] - t.bx[b], dy = (1 << l) - 1 - t.by[c] - t.by[b];
+                *out++ = (c << 5) | ((dy + 3) * 7 + dx + 3);
+            }
         }
-    }
-    if (!t.leaf[b]) return;
-    const int f = first[b], n = count[b];
-    for (int k = lane; k < (n + 63) / 64; k += 64)
-        rec[roff[b] + k] = NearRec{f + 64 * k, min(64, n - 64 * k), n, (int32_t)nfree[b], (int32_t)nimg[b], 0, soff[b]};
-    if (woff[b + 1] > woff[b])
+        if (!t.leaf[b]) continue;
+        const int f = first[b], n = count[b];
         for (int k = lane; k < (n + 63) / 64; k += 64)
-            wrec[wroff[b] + k] = make_int4(f + 64 * k, min(64, n - 64 * k), woff[b], woff[b + 1]);
-    int32_t *out = stream + soff[b];
-    for (int k = lane; k < n; k += 64) out[k] = f + k;
-    out += n;
-    for (int img = 0; img < 2; ++img)
-        for (int e = uoff[b]; e < uoff[b + 1]; ++e) {
-            const int code = uent[e], c = code >> 1, m = count[c], fc = first[c];
-            if ((code & 1) != img || code == 2 * b) continue;
-            for (int k = lane; k < m; k += 64) out[k] = fc + k;
-            out += m;
-        }
+            rec[roff[b] + k] = NearRec{f + 64 * k, min(64, n - 64 * k), n, (int32_t)nfree[b], (int32_t)nimg[b], 0, soff[b]};
+        if (woff[b + 1] > woff[b])
+            for (int k = lane; k < (n + 63) / 64; k += 64)
+                wrec[wroff[b] + k] = make_int4(f + 64 * k, min(64, n - 64 * k), woff[b], woff[b + 1]);
+        int32_t *out = stream + soff[b];
+        for (int k = lane; k < n; k += 64) out[k] = f + k;
+        out += n;
+        for (int img = 0; img < 2; ++img)
+            for (int e = uoff[b]; e < uoff[b + 1]; ++e) {
+                const int code = uent[e], c = code >> 1, m = count[c], fc = first[c];
+                if ((code & 1) != img || code == 2 * b) continue;
+                for (int k = lane; k < m; k += 64) out[k] = fc + k;
+                out += m;
+            }
+    }
 }
 
 __global__ void k_compact(int64_t n, const int32_t *__restrict__ flag, const int32_t *__restrict__ pos,
@@ -895,7 +899,7 @@ fmmhp_status list_tables(Arena &A, const Tree &T, Sched &S, std::vector<int32_t>
     FMMHP_CHECK(A.alloc_n(&S.wrec, (size_t)h[9], "W records"));
     FMMHP_CHECK(A.alloc_n(&S.wipts, (size_t)h[6], "W image targets"));
     FMMHP_CHECK(A.alloc_n(&S.rpts, (size_t)h[7], "near-axis targets"));
-    hipLaunchKernelGGL(k_list_fill, dim3((unsigned)nb), dim3(64), 0, s, tv, T.first, T.count, T.off[0], T.ent[0],
+    hipLaunchKernelGGL(k_list_fill, dim3((unsigned)std::min(nb, kFillBlocks)), dim3(64), 0, s, tv, nb, T.first, T.count, T.off[0], T.ent[0],
                        T.off[1], T.ent[1], S.vimg_off, S.vimg_ent, nfree, nimg, soff, roff, S.near_rec, S.near_stream,
                        T.off[2], wroff, S.wrec);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, s, S.near_stream + h[8], (int64_t)kNearPad, 0);
