@@ -3402,9 +3402,11 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
         if (y1 > y0) {
             const P2LArgs pa{y1 - y0,  nbox,  S.nloc, NV,        S.xslot + y0, S.xrow0 + y0,              S.xsgeo + y0, S.xstream,
                              S.xy,     S.nrm, ws.qs,  S.logside, S.fact,       S.bc == 2 ? -1.0 : 1.0, ws.Lam};
-            // four lanes a box once that gives each of the 1,024 SIMDs a wave; below, a box's chain of rows is
-            // what a launch takes (100,000 uniform points, p = 15, two vectors: 29 us a launch with four lanes, 12 with sixteen)
-            if (S.nxslot >= kP2LManyBoxes)
+            // four lanes a box where the launch's boxes then give each SIMD a wave; below, a box's chain of
+            // rows is what a launch takes (100,000 uniform points, p = 15, two vectors: 29 us a launch with
+            // four lanes, 12 with sixteen).  The vectors of a pass would multiply the waves, but a vector's
+            // result has to be the same in every pass.
+            if (y1 - y0 >= (64 / 4) * 4 * S.cus)
                 hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2l<PB, DIP, VP, 4>), dim3(nblk(nblk(y1 - y0, 64), 8) * 8, NV / VP),
                                    dim3(256), 0, st, pa);
             else

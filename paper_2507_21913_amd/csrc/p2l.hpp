@@ -52,7 +52,6 @@ __device__ __forceinline__ double lane_group_sum(double s, int IA) {
 }
 
 constexpr int kP2LChunk = 64;  // X boxes sorted by their rows together
-constexpr int kP2LManyBoxes = 16384;  // X boxes of a plan from which four lanes take a box, not sixteen
 
 struct P2LArgs {
     int nslot, nbox, nloc, nv;
