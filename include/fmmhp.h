@@ -110,9 +110,11 @@ typedef struct {
  * duration is then its own, not shared with concurrent kernels); slower. */
 #define FMMHP_FLAG_SERIAL 16u
 /* Form of the FP64 M2L of upper sources (eq. (truncatedM2Lcoef) and the log-kernel M2L).  The default
- * translates plane waves: the same sums through a quadrature whose error stays below 1e-12 of a unit
- * charge's field and below the expansion's own at every p (under 1% of it up to p = 25, 12% at p = 30,
- * of the order of rounding above).  The
+ * translates plane waves: the same sums through a quadrature.  Its root mean square error over points in
+ * the boxes is at most 1.1e-12 of a unit charge's log potential (p = 5; 3.7e-16 at p = 30, 12% of the
+ * expansion's own).  Its largest error, for charges and targets in the corners of their boxes, is at most
+ * 3% of the expansion's there up to p = 30 and 13% at p = 35 (8e-15); at p = 40, where the expansion leaves
+ * 1.3e-15, it is 4e-15, the rounding of the expansion's 41 coefficients.  The
  * flags select the Hankel rows themselves, on the vector ALUs (one lane per target box, operators in
  * scalar registers) or on the FP64 matrix cores (v_mfma_f64_16x16x4f64, complex numbers as 2 x 2 real
  * blocks); at most one of the two.  Ignored with FMMHP_FLAG_M2L_FP32. */
