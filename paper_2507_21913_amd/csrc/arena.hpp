@@ -21,7 +21,7 @@ void set_error(const char *fmt, ...);
 struct Arena {
     std::vector<void *> ptrs;  // slabs and large arrays
     int64_t bytes = 0;         // requested
-    int tries = 0;             // arrays asked for (FMMHP_TEST_FAIL_ALLOC counts them)
+    int tries = 0;             // requests (FMMHP_TEST_FAIL_ALLOC counts them)
     char *cur = nullptr;       // the open slab
     size_t left = 0;
 
@@ -30,65 +30,57 @@ struct Arena {
         size_t bytes;
     };
 
-    // *p is set when the array is there and left alone when it is not.
-    fmmhp_status alloc(void **p, size_t nbytes, const char *what) {
+    // Several arrays at once: all of them, or none and nothing taken (the pointers are left alone then).
+    // Arrays that fit the open slab go there, the others share one new allocation.
+    fmmhp_status alloc_all(std::initializer_list<Part> parts, const char *what) {
+        size_t total = 0, placed = 0, rest = 0;  // placed: in the open slab
+        for (const Part &a : parts) {
+            const size_t need = padded(a.bytes);
+            total += a.bytes;
+            (placed + need <= left ? placed : rest) += need;
+        }
         ++tries;
-        if (const char *e = getenv("FMMHP_TEST_FAIL_ALLOC")) {  // "k": the k-th array fails; "k+": every one from it on
+        if (const char *e = getenv("FMMHP_TEST_FAIL_ALLOC")) {  // "k": the k-th request fails; "k+": every one from it on
             char *end = nullptr;
             const long k = strtol(e, &end, 10);
             if (k > 0 && (tries == k || (*end == '+' && tries > k))) {
-                set_error("allocation of %s (%zu bytes, array %d of the plan) failed (test hook)", what, nbytes, tries);
+                set_error("allocation of %s (%zu bytes, array %d of the plan) failed (test hook)", what, total, tries);
                 return FMMHP_ENOMEM;
             }
         }
-        const size_t need = (nbytes + 255) / 256 * 256;
-        if (need > left) {
-            const size_t slab = std::min<size_t>((size_t)64 << 20, std::max<size_t>((size_t)1 << 20, 2 * (size_t)bytes));
-            bool own = need >= slab;
-            void *m = nullptr;
-            hipError_t e = take(&m, own ? nbytes : slab);
-            if (e != hipSuccess && !own) {  // no room for a slab: the array alone
-                own = true;
-                e = take(&m, nbytes);
-            }
+        char *more = nullptr;
+        size_t got = 0;
+        if (rest > 0) {
+            const size_t slab = std::min<size_t>((size_t)64 << 20, std::max<size_t>((size_t)1 << 20, 2 * ((size_t)bytes + placed)));
+            got = std::max(rest, slab);
+            hipError_t e = take(&more, got);
+            if (e != hipSuccess && got > rest) e = take(&more, got = rest);  // no room for a slab: the arrays alone
             if (e != hipSuccess) {
-                set_error("hipMalloc of %s (%zu bytes) failed: %s", what, nbytes, hipGetErrorString(e));
+                set_error("hipMalloc of %s (%zu bytes) failed: %s", what, total, hipGetErrorString(e));
                 return FMMHP_ENOMEM;
             }
-            ptrs.push_back(m);
-            bytes += (int64_t)nbytes;
-            if (own) {
-                *p = m;
-                return FMMHP_OK;
-            }
-            cur = (char *)m;
-            left = slab;
-        } else {
-            bytes += (int64_t)nbytes;
+            ptrs.push_back(more);
         }
-        *p = cur;
-        cur += need;
-        left -= need;
+        char *m = more;
+        for (const Part &a : parts) {
+            const size_t need = padded(a.bytes);
+            char *&at = need <= left ? cur : m;
+            if (need <= left) left -= need;
+            *a.p = at;
+            at += need;
+        }
+        if (got - rest > left) {  // the new slab is the open one
+            cur = m;
+            left = got - rest;
+        }
+        bytes += (int64_t)total;
         return FMMHP_OK;
     }
 
+    fmmhp_status alloc(void **p, size_t nbytes, const char *what) { return alloc_all({Part{p, nbytes}}, what); }
     template <class T>
     fmmhp_status alloc_n(T **p, size_t n, const char *what) {
         return alloc((void **)p, (n ? n : 1) * sizeof(T), what);
-    }
-
-    // Several arrays at once: all of them, or none and nothing taken.
-    fmmhp_status alloc_all(std::initializer_list<Part> parts, const char *what) {
-        size_t total = 0;
-        for (const Part &a : parts) total += (a.bytes + 255) / 256 * 256;
-        char *base = nullptr;
-        const fmmhp_status st = alloc((void **)&base, total, what);
-        if (st != FMMHP_OK) return st;
-        for (const Part &a : parts) {
-            *a.p = base;
-            base += (a.bytes + 255) / 256 * 256;
-        }
-        return FMMHP_OK;
     }
 
     void release() {
@@ -97,8 +89,9 @@ struct Arena {
     }
 
 private:
-    static hipError_t take(void **m, size_t nbytes) {
-        const hipError_t e = hipMalloc(m, nbytes);
+    static size_t padded(size_t nbytes) { return (nbytes + 255) / 256 * 256; }
+    static hipError_t take(char **m, size_t nbytes) {
+        const hipError_t e = hipMalloc((void **)m, nbytes);
         if (e != hipSuccess) (void)hipGetLastError();
         return e;
     }

@@ -1,5 +1,5 @@
-// Workspaces that a plan's evaluations grow on demand.  Each is one allocation: where it fails, the
-// workspace stays what it was, and what fitted before still runs.
+// Workspaces that a plan's evaluations grow on demand, each as a whole: where that fails, the workspace
+// stays what it was, and what fitted before still runs.
 #pragma once
 #include "internal.hpp"
 
@@ -9,17 +9,28 @@ namespace fmmhp {
 // Im w_0, zero padding to a multiple of 4.
 __host__ __device__ constexpr int m2l32_kp(int PB) { return ((2 * (PB + 1) + 2 + 3) / 4) * 4; }
 
+constexpr int kWsArrays = 8;
+
+// Bytes of the arrays of a pass workspace for nv vectors (W, Lam, qs, near, red, rank1, Wf, part; 0: not in
+// use).
+inline void vec_ws_sizes(const Tree &T, const Sched &S, int nv, size_t (&b)[kWsArrays]) {
+    const size_t nb = (size_t)T.nbox, P1 = (size_t)S.PB + 1;
+    b[0] = nv * P1 * nb * sizeof(cplx);
+    b[1] = nv * (size_t)S.nloc * P1 * nb * sizeof(cplx);
+    b[2] = nv * (size_t)T.n * sizeof(double);
+    b[3] = nv * (size_t)T.n * sizeof(double2);
+    b[4] = nv * (size_t)S.n_rch * sizeof(cplx);
+    b[5] = nv * (size_t)T.n_inst * sizeof(cplx);
+    b[6] = S.m2l_fp32 ? nv * nb * (size_t)m2l32_kp(S.PB) * sizeof(float) : 0;
+    b[7] = S.sym_ok && (S.near_walk == 3 || S.near_walk == 4) ? nv * (size_t)S.sym_npart * sizeof(double) : 0;
+}
+
 // Bytes of a pass workspace for nv vectors (each array aligned to 256 bytes); carves it from base
 // when base is given.
 inline size_t vec_ws_layout(const Tree &T, const Sched &S, int nv, unsigned char *base, VecWs *w) {
-    const size_t nb = (size_t)T.nbox, P1 = (size_t)S.PB + 1;
-    const size_t sizes[8] = {nv * P1 * nb * sizeof(cplx), nv * (size_t)S.nloc * P1 * nb * sizeof(cplx),
-                             nv * (size_t)T.n * sizeof(double), nv * (size_t)T.n * sizeof(double2),
-                             nv * (size_t)S.n_rch * sizeof(cplx), nv * (size_t)T.n_inst * sizeof(cplx),
-                             S.m2l_fp32 ? nv * nb * (size_t)m2l32_kp(S.PB) * sizeof(float) : 0,
-                             S.sym_ok && (S.near_walk == 3 || S.near_walk == 4) ? nv * (size_t)S.sym_npart * sizeof(double) : 0};
-    size_t off[8], at = 0;
-    for (int k = 0; k < 8; ++k) {
+    size_t sizes[kWsArrays], off[kWsArrays], at = 0;
+    vec_ws_sizes(T, S, nv, sizes);
+    for (int k = 0; k < kWsArrays; ++k) {
         off[k] = at;
         at += (sizes[k] + 255) / 256 * 256;
     }
@@ -31,20 +42,29 @@ inline size_t vec_ws_layout(const Tree &T, const Sched &S, int nv, unsigned char
         w->near = (double2 *)(base + off[3]);
         w->red = (cplx *)(base + off[4]);
         w->rank1 = (cplx *)(base + off[5]);
-        w->Wf = S.m2l_fp32 ? (float *)(base + off[6]) : nullptr;
-        w->part = S.sym_ok && (S.near_walk == 3 || S.near_walk == 4) ? (double *)(base + off[7]) : nullptr;
+        w->Wf = sizes[6] ? (float *)(base + off[6]) : nullptr;
+        w->part = sizes[7] ? (double *)(base + off[7]) : nullptr;
     }
     return at;
 }
 
 // Per-vector workspace (multipoles, locals, sorted charges, near-field sums, surface sums) for nv
-// vectors at once; grown on demand, owned by the plan.  One allocation: where it fails, the workspace
+// vectors at once; grown on demand, owned by the plan.  Where one array has no place, the workspace
 // stays what it was.
 inline fmmhp_status ensure_vec_ws(Arena &A, const Tree &T, Sched &S, int nv) {
     if (S.ws.cap >= nv) return FMMHP_OK;
-    unsigned char *base = nullptr;
-    FMMHP_CHECK(A.alloc_n(&base, vec_ws_layout(T, S, nv, nullptr, nullptr), "pass workspace"));
-    vec_ws_layout(T, S, nv, base, &S.ws);
+    size_t b[kWsArrays];
+    vec_ws_sizes(T, S, nv, b);
+    VecWs w;
+    FMMHP_CHECK(A.alloc_all({Arena::Part{(void **)&w.W, b[0]}, Arena::Part{(void **)&w.Lam, b[1]},
+                             Arena::Part{(void **)&w.qs, b[2]}, Arena::Part{(void **)&w.near, b[3]},
+                             Arena::Part{(void **)&w.red, b[4]}, Arena::Part{(void **)&w.rank1, b[5]},
+                             Arena::Part{(void **)&w.Wf, b[6]}, Arena::Part{(void **)&w.part, b[7]}},
+                            "pass workspace"));
+    if (!b[6]) w.Wf = nullptr;
+    if (!b[7]) w.part = nullptr;
+    w.cap = nv;
+    S.ws = w;
     return FMMHP_OK;
 }
 
