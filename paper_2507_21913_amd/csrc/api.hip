@@ -507,7 +507,7 @@ fmmhp_status fmmhp_plan_info(fmmhp_plan_t plan, fmmhp_plan_stats *st) {
     st->lambda_re = plan->lambda_re;
     st->lambda_im = plan->lambda_im;
     st->real_impedance = plan->sched.real_Z ? 1 : 0;
-    st->device_bytes = plan->arena.bytes;
+    st->device_bytes = plan->arena.held;
     st->n_inst = T.n_inst;
     st->n_sources = plan->n_src > 0 ? plan->n_src : T.n;
     st->near_walk = plan->sched.near_walk;

@@ -21,6 +21,7 @@ void set_error(const char *fmt, ...);
 struct Arena {
     std::vector<void *> ptrs;  // slabs and large arrays
     int64_t bytes = 0;         // requested
+    int64_t held = 0;          // taken from the device
     int tries = 0;             // requests (FMMHP_TEST_FAIL_ALLOC counts them)
     char *cur = nullptr;       // the open slab
     size_t left = 0;
@@ -60,6 +61,7 @@ struct Arena {
                 return FMMHP_ENOMEM;
             }
             ptrs.push_back(more);
+            held += (int64_t)got;
         }
         char *m = more;
         for (const Part &a : parts) {

@@ -36,9 +36,6 @@
 
 namespace fmmhp {
 
-// ---------------------------------------------------------------------------------------------
-// Arena
-// ---------------------------------------------------------------------------------------------
 // Build-time temporaries (stream-ordered), carved from slabs of at least `slab` bytes and given back
 // together at the end of the scope.
 struct Scratch {
