@@ -2538,9 +2538,9 @@ __global__ void k_band_tab(int nwave, int nlev, int nroot, const int32_t *__rest
                            const int32_t *__restrict__ leaf, const int32_t *__restrict__ child_first,
                            const int32_t *__restrict__ nchild, const int32_t *__restrict__ bx,
                            const int32_t *__restrict__ by, int32_t *__restrict__ tab) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nwave * 64) return;
-    const int wv = i >> 6, lane = i & 63;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (int64_t)nwave * 64) return;
+    const int wv = (int)(i >> 6), lane = (int)(i & 63);
     const int r = (wv << (2 * (3 - nlev))) + (lane >> (2 * nlev));
     int b = r < nroot ? roots[r] : -1;
     int32_t *t = tab + (int64_t)wv * (nlev + 1) * 64 + lane;
