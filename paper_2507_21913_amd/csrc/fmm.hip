@@ -114,7 +114,6 @@ __global__ void k_pack_xy(const double *__restrict__ xs, const double *__restric
 // ---------------------------------------------------------------------------------------------
 // Charges into sorted order
 // ---------------------------------------------------------------------------------------------
-// ---------------------------------------------------------------------------------------------
 // Workgroup -> chunk of 256 points such that an XCD takes one contiguous eighth of the sorted points (the
 // grid is a multiple of 8 workgroups): the points of an instance then meet in one L2, in which their
 // scattered reads in caller order share lines.
@@ -1065,44 +1064,31 @@ __global__ __launch_bounds__(64) void k_p2l_react(const InstInfo *__restrict__ i
                         continue;
                     }
                     const cplx *Ck = C + (lc * ph + kq) * rs;
-                    cplx acc[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) acc[v] = mk(0.0, 0.0);
+                    cplx acc = mk(0.0, 0.0);
                     // four of the lane's rows loaded together (at a valid row past the end), added
                     // in row order
                     for (int r = r0 + gq; r < r1; r += 4 * G) {
                         cplx t[4];
-                        double qv[4][NV];
+                        double qv[4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int ri = r + i * G < r1 ? r + i * G : r;
                             t[i] = Ck[ri];
-#pragma unroll
-                            for (int v = 0; v < NV; ++v) qv[i][v] = sq[ri][v];
+                            qv[i] = sq[ri][0];
                         }
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if (r + i * G < r1) {
-#pragma unroll
-                                for (int v = 0; v < NV; ++v) acc[v] += qv[i][v] * t[i];
-                            }
-                        }
+                        for (int i = 0; i < 4; ++i)
+                            if (r + i * G < r1) acc += qv[i] * t[i];
                     }
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        acc[v].re = lane_group_sum(acc[v].re, G);
-                        acc[v].im = lane_group_sum(acc[v].im, G);
-                    }
+                    acc.re = lane_group_sum(acc.re, G);
+                    acc.im = lane_group_sum(acc.im, G);
                     // only this wave adds to the box's locals here, one lane per coefficient in
                     // program order, so the sums stay deterministic; the adds return nothing and the
                     // wave does not wait for them
                     if (gq == 0 && m <= PB) {
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            cplx *dst = Lam + (((int64_t)v * nloc + lc) * P1 + m) * nbox + bsl;
-                            unsafeAtomicAdd(&dst->re, acc[v].re);
-                            unsafeAtomicAdd(&dst->im, acc[v].im);
-                        }
+                        cplx *dst = Lam + ((int64_t)lc * P1 + m) * nbox + bsl;
+                        unsafeAtomicAdd(&dst->re, acc.re);
+                        unsafeAtomicAdd(&dst->im, acc.im);
                     }
                 }
             }
@@ -1211,7 +1197,6 @@ struct LeafArgs {
     const InstInfo *ii;      // [n_inst]
     const int32_t *inst;     // box -> instance
     int n_inst;
-    int nv;                  // charge vectors in this pass (interleaved in qs)
     int64_t n;
     int nbox, nloc;
     const double *xs, *ys, *qs;
@@ -1219,7 +1204,7 @@ struct LeafArgs {
     const int32_t *perm, *leaf_of, *level, *bx, *by, *first, *count;
     const int32_t *uoff, *uent, *woff, *went;
     const cplx *W, *Lam;
-    const double *invfact, *fact;
+    const double *invfact;
     const cplx *rank1;       // [nv][n_inst] surface sums (real impedance) or null
     const int4 *wrec;        // [nwrec] targets and entries of the leaves with a W list (see WRec)
     int nwrec;
@@ -1227,10 +1212,8 @@ struct LeafArgs {
     const int32_t *wipts;    // targets whose leaf's W list has image entries
     int64_t n_wipts;
     const int32_t *rpts;     // targets whose leaf has image U entries
-    const double2 *logtab;   // [kLogTable] (1/c_k, -log(1/c_k))
     double2 *near;           // [nv][n] near-field potential per sorted target
     cplx *near_gx, *near_gy; // [n] near-field gradient per sorted target (gradient modes)
-    double *qc;              // [n] sum of the charges coincident with each sorted target, or null
     double *phi;             // [nv][n][2] potential, caller order (potential modes)
     cplx *gx, *gy;           // [n] gradient, caller order (gradient modes)
     double isg;              // sign of the image log term: +1 (Robin, Dirichlet), -1 (Neumann)
@@ -3295,12 +3278,12 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gather_q<NV>), dim3(xcd_grid(T.n)), dim3(256), 0, s, q, T.perm, T.n, ws.qs);
     // the near field needs only the sorted charges: run it on the side stream, concurrently with
     // the far-field chain, and join before the final leaf kernel
-    LeafArgs la{S.inst_info, T.inst,    T.n_inst, NV,       T.n,      nbox,     S.nloc,   T.xs,     T.ys,
-                ws.qs,        S.xy,      T.perm,   T.leaf_of, T.level, T.bx,     T.by,     T.first,  T.count,
-                T.off[0],    T.ent[0],  T.off[2], T.ent[2], ws.W,      ws.Lam,    S.invfact, S.fact,
+    LeafArgs la{S.inst_info, T.inst,  T.n_inst,  T.n,      nbox,     S.nloc,  T.xs,    T.ys,
+                ws.qs,       S.xy,    T.perm,    T.leaf_of, T.level, T.bx,    T.by,    T.first,  T.count,
+                T.off[0],    T.ent[0], T.off[2], T.ent[2], ws.W,     ws.Lam,  S.invfact,
                 S.bc == 0 ? ws.rank1 : nullptr,
-                S.wrec,      S.nwrec,    S.wgeo,  S.wipts,  S.n_wipts, S.rpts,   S.logtab, ws.near,   S.bw.near_gx, S.bw.near_gy, out.qc,
-                out.phi,     out.gx,    out.gy,   S.bc == 2 ? -1.0 : 1.0, S.nrm,
+                S.wrec,      S.nwrec, S.wgeo,    S.wipts,  S.n_wipts, S.rpts, ws.near, S.bw.near_gx, S.bw.near_gy,
+                out.phi,     out.gx,  out.gy,    S.bc == 2 ? -1.0 : 1.0, S.nrm,
                 out.sorted ? 1 : 0};
     FMMHP_HIP(hipEventRecord(S.ev_fork, s));
     FMMHP_HIP(hipStreamWaitEvent(side_, S.ev_fork, 0));
@@ -3342,7 +3325,7 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
                            side_, la);
     FMMHP_HIP(hipGetLastError());
     // the surface sums also need only the sorted charges
-    if (S.nloc == 1 && S.bc == 0 && S.rank1_side) {
+    if (S.nloc == 1 && S.bc == 0) {
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rank1_partial<DIP, NV>), dim3(S.n_rch), dim3(256), 0, side_, T.xs,
                            T.ys, ws.qs, S.rch, S.n_rch, S.inst_info, S.nrm, ws.red);
         hipLaunchKernelGGL(k_rank1_final, dim3(T.n_inst, NV), dim3(256), 0, side_, ws.red, S.n_rch, S.inst_ch,
@@ -3488,13 +3471,6 @@ static fmmhp_status eval_pass(const Tree &T, const Sched &S, const VecWs &ws, co
     }
     FMMHP_HIP(hipGetLastError());
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_SURF, s));
-    if (S.nloc == 1 && S.bc == 0 && !S.rank1_side) {
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rank1_partial<DIP, NV>), dim3(S.n_rch), dim3(256), 0, s, T.xs, T.ys,
-                           ws.qs, S.rch, S.n_rch, S.inst_info, S.nrm, ws.red);
-        hipLaunchKernelGGL(k_rank1_final, dim3(T.n_inst, NV), dim3(256), 0, s, ws.red, S.n_rch, S.inst_ch, T.n_inst,
-                           ws.rank1);
-        FMMHP_HIP(hipGetLastError());
-    }
     FMMHP_HIP(hipStreamWaitEvent(s, S.ev_join, 0));
     FMMHP_CHECK(mk_.mark(FMMHP_PHASE_LEAF, s));
     // dipoles differ from charges only in the source terms: the L2P and M2P kernels are the potential's

@@ -203,7 +203,6 @@ struct Sched {
     int32_t *sym_in_off = nullptr, *sym_in = nullptr;  // per box: its partial slots (gather)
     int64_t near_blocks = 512;      // near-field grid (workgroups)
     bool serial = false;            // every kernel on the eval stream (FMMHP_FLAG_SERIAL)
-    bool rank1_side = true;         // surface sums on the near-field stream
     // bands of the M2M and L2L passes: levels root .. root + nlev, their waves and their part of band_tab
     struct Band {
         int root, nlev, nwave;
