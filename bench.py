@@ -31,13 +31,12 @@ PEAK_FP32_MATRIX_TFLOPS = 157.3  # MI355X fp32 matrix peak
 
 # HBM bytes of k_m2l_pw per evaluation measured with rocprofv3 counter runs (2.00 x FETCH_SIZE + 1.00 x
 # WRITE_SIZE, the factors a plain 256 MiB copy gives), keyed by a hash of the evaluation sources and
-# (p, leaf size): reported (per launch) only while the kernels are the ones that were measured (not
-# measured for the present ones).
-M2L_TRAFFIC = {}
+# (p, leaf size): reported (per launch) only while the kernels are the ones that were measured.
+M2L_TRAFFIC = {("b9cd04d71cecca18", 20, 32): 120.2e6, ("b9cd04d71cecca18", 20, 40): 119.7e6}
 # k_near per launch (rocprofv3 FETCH_SIZE and WRITE_SIZE, scaled as above), same key
-NEAR_TRAFFIC = {}
+NEAR_TRAFFIC = {("b9cd04d71cecca18", 20, 32): 85.2e6, ("b9cd04d71cecca18", 20, 40): 85.1e6}
 # Nodes of the plane-wave quadrature by compiled order
-PW_NODES = {5: 22, 10: 25, 15: 29, 20: 34, 25: 40, 30: 40, 35: 44, 40: 44}
+PW_NODES = {5: 22, 10: 25, 15: 29, 20: 34, 25: 40, 30: 40, 35: 44, 40: 46}
 NEAR_FLOPS = 17.0  # float64 flops of a near pair: 7 FMA (log 5), 1 mul, 2 add
 
 
@@ -64,7 +63,7 @@ def eval_source_hash() -> str:
     import hashlib
     h = hashlib.sha256()
     for f in ("fmm.hip", "tree.hip", "internal.hpp", "special.hpp", "cplx.hpp", "m2l_pw.hpp", "pw_nodes.hpp",
-              "updown.hpp", "p2l.hpp"):
+              "updown.hpp", "p2l.hpp", "arena.hpp", "workspace.hpp"):
         with open(os.path.join(ROOT, "paper_2507_21913_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -539,8 +538,8 @@ def main():
         fl = NEAR_FLOPS * pairs
         achieved = fl / (phase_avg["near"] * 1e-3) / 1e12
         roof = {"kernel": "k_near", "bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
-                "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS, "traffic": None,
-                "flops_per_launch": fl}
+                "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
+                "traffic": NEAR_TRAFFIC.get((eval_source_hash(), info["p"], leaf_use)), "flops_per_launch": fl}
 
     # the same evaluation with every kernel on one stream: each M2L launch's duration is its own
     # (the concurrent schedule above shares the CUs with the near field)

@@ -146,13 +146,15 @@ typedef struct {
 /* Phases of fmmhp_eval whose device time fmmhp_plan_phase_times reports. */
 enum {
     FMMHP_PHASE_P2M = 0,    /* charge gather and leaf multipoles (S2M) */
-    FMMHP_PHASE_M2M = 1,    /* upward pass, one launch per level */
-    FMMHP_PHASE_M2L = 2,    /* multipole-to-local over all levels, one launch */
-    FMMHP_PHASE_P2L = 3,    /* X list */
-    FMMHP_PHASE_L2L = 4,    /* downward pass, one launch per level */
-    FMMHP_PHASE_SURF = 5,   /* surface term sum (real impedance) */
-    FMMHP_PHASE_LEAF = 6,   /* L2P, W list and output (after the near field has joined) */
-    FMMHP_PHASE_NEAR = 7,   /* near field (U list), on the plan's side stream, concurrent with 1-5 */
+    FMMHP_PHASE_M2M = 1,    /* upward pass, one launch per band of up to three levels */
+    FMMHP_PHASE_M2L = 2,    /* multipole-to-local and X list: the coarse levels, and the deep ones on
+                               a stream of their own from 32 tiles on */
+    FMMHP_PHASE_P2L = 3,    /* (empty: the X list runs with the M2L of its levels) */
+    FMMHP_PHASE_L2L = 4,    /* downward pass, one launch per band */
+    FMMHP_PHASE_SURF = 5,   /* (the wait for the near-field stream, which forms the surface sums) */
+    FMMHP_PHASE_LEAF = 6,   /* L2P and output (after the near field and the W list have joined) */
+    FMMHP_PHASE_NEAR = 7,   /* near field (U list) and surface sums, on the plan's side stream, concurrent
+                               with 0-5 */
     FMMHP_NUM_PHASES = 8
 };
 

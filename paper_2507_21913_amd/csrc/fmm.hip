@@ -324,7 +324,7 @@ __global__ __launch_bounds__(64 * m2l_waves(PB)) void k_m2l(M2LArgs a) {
 
 // ---------------------------------------------------------------------------------------------
 // M2L of upper sources on the FP64 matrix cores (FMMHP_FLAG_M2L_MFMA; the tuner times it against the
-// vector form).  On gfx950 an FP64 matrix instruction (16 x 16 x 4, 2048 flops) occupies the SIMD's
+// default plane waves).  On gfx950 an FP64 matrix instruction (16 x 16 x 4, 2048 flops) occupies the SIMD's
 // matrix unit for 64 cycles: the same FP64 rate as the vector ALUs, and the 2x2 embedding padded to
 // 16 output columns and 4 source coefficients keeps 77% of the instructions' work at p = 20 (94% at
 // p = 30): this form has been measured slower than k_m2l at p = 20 and p = 30.
@@ -1253,13 +1253,14 @@ __device__ __forceinline__ XcdChunks xcd_chunks(int64_t nch) {
 // r^2 = 0 in the steps that hold them alone.
 //
 // What bounds it: FP64 issue (19 VALU instructions per evaluated pair, ~77% of them on real pairs:
-// partly filled lanes at the end of a stream and of a leaf) and, at two waves per SIMD, the latency of
-// the loads.  It replaced a thread per target walking the U list entry by entry (38 instructions per
-// pair, lanes of a wave waiting for the longest leaf).  Alone on the GPU at 1M uniform points, leaf 32:
-// one vector 272 -> 190 us; eight vectors on a 2M forest 1,155 -> 1,005 us; potential and gradient of
-// three vectors at 1M 468 -> 360 us; the 4M curve in walk 2's grid 1,980 -> 1,130 us.  Four targets per
-// lane measured better than eight (72 -> 60 M instructions at 1M): the smaller step leaves fewer lanes
-// idle at a stream's end.
+// partly filled lanes at the end of a stream and of a leaf), 68% of the time at 1M and 55% on the 4M curve,
+// and, at two waves per SIMD, the latency of the loads (28% and 37% of the waves' time; a table read costs
+// six bank-conflict cycles).  It replaced a thread per target walking the U list entry by entry (38
+// instructions per pair, lanes of a wave waiting for the longest leaf).  Alone on the GPU at 1M uniform
+// points, leaf 32: one vector 272 -> 190 us on two workgroups per CU, 147 on eight; eight vectors on a 2M
+// forest 1,155 -> 853 us; potential and gradient of three vectors at 1M 468 -> 360 us; the 4M curve
+// 1,980 -> 840 us.  Four targets per lane measured better than eight (72 -> 60 M instructions at 1M): the
+// smaller step leaves fewer lanes idle at a stream's end.
 constexpr int kNearTargets = 4;  // targets per lane at most
 static_assert(kNearPad >= 3 * 64, "a segment reads up to 3 JG entries past its end");
 
@@ -1852,7 +1853,7 @@ __global__ __launch_bounds__(256) void k_leaf(LeafArgs a) {
 // conjugates the target offset instead.  Adds to the near-field sums (before k_leaf reads them).
 //
 // What bounds it: the loads of a wave (record, entry, coefficients, sums) at two waves per SIMD, then FP64
-// issue.  The kernel it replaced took a lane per target, formed complex sums of every vector and both
+// issue; potential and gradient of three vectors spill 8 to 16 of their 256 registers.  The kernel it replaced took a lane per target, formed complex sums of every vector and both
 // locals, and held one wave per SIMD.  Alone on the GPU: 4M points along a curve, p = 30: 314 -> 141 us;
 // 2M points in 64 instances, p = 20, eight vectors: 1,302 -> 308 us (and 51 us in k_m2p_react).
 struct WRec {

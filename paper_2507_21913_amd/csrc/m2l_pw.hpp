@@ -21,9 +21,11 @@
 // box per lane, and writes the four outgoing waves of the step's two nodes to LDS.  Waves 4-7 are the
 // target waves: wave 4 + by + 2 par takes the children in row by of the 32 parents (lane = (parent,
 // bx)) at the nodes of parity par, sums the incoming waves and holds the locals in registers.  The two
-// sides run one step apart on double-buffered LDS with one barrier per step.  What bounds it: FP64
-// issue, ~1,030 cycles per step and SIMD at p = 20, and within a tile the latency of a step (scalar
-// loads, LDS reads, lane swaps, barrier), which the second workgroup on the CU covers.  The lanes bx = 0, 1 of
+// sides run one step apart on double-buffered LDS with one barrier per step.  What bounds it: the
+// latency of a step (scalar loads, LDS reads, lane swaps, barrier), which the second workgroup on the CU
+// covers in part.  By the counters (1M points, p = 20; 4M curve, p = 30; each launch alone) its waves wait
+// 53-61% of their time and the vector instructions take 31% of it, the LDS reads with their bank conflicts
+// (4.6 cycles a read) about as much; 120 MB of HBM traffic at 1M, twice the boxes' expansions.  The lanes bx = 0, 1 of
 // a parent share their sums: each takes the three nearest columns on its own side and the partner's
 // half comes by a lane swap; what differs between the lanes and between the two rows is a sign, so
 // all four child positions run the same code.  A cell without a source box reads a zero column, so a
@@ -32,7 +34,8 @@
 // Measured, all launches of an evaluation alone on the GPU, against the Hankel rows of k_m2l: 1M uniform
 // points, p = 20, leaf 32: 359 -> 80 us; 4M points along a curve, p = 30, leaf 40: 1,407 -> 398 us;
 // 2M points in 64 instances, p = 20, eight vectors: 3,790 -> 855 us; one tile (2,000 points): 90 -> 20 us.
-// Errors against direct sums are those of the Hankel rows to three digits at every p.
+// Potentials of random charges agree with the Hankel rows' to a few times err of pw_nodes.hpp, which also
+// gives the quadrature's largest errors.
 #pragma once
 #include "internal.hpp"
 #include "pw_nodes.hpp"
@@ -213,8 +216,10 @@ __device__ __forceinline__ void pw_targets(const PwArgs &a, cplx *sX, const doub
         }
 }
 
-// p <= 20: 128 registers, two workgroups (16 waves) per CU; above, the locals alone take up to 164 and
-// one workgroup fits.
+// p <= 20: 128 registers, two workgroups (16 waves) per CU.  They do not quite hold p = 20: 14 spills, 52
+// bytes of scratch a lane, before and after the loop over the nodes (one spill at p = 10); two workgroups
+// were still faster than one of 180 registers (1M points: 99 -> 80 us with the scalar table loads).  Above,
+// the locals alone take up to 164 and one workgroup fits: 164, 194, 224 and 254 registers, no spills.
 template <int PB>
 __global__ __launch_bounds__(512, PB <= 20 ? 4 : 2) void k_m2l_pw(PwArgs a) {
     constexpr int P1 = PB + 1, NS = pw_steps(PB), TS = pw_src_row(PB);

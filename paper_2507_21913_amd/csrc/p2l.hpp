@@ -15,8 +15,11 @@
 // d = z_j - c_b (upper box) or in conj(z_j) - c_b (image), so it is nu d/dd with nu = n_x + i n_y, or its
 // conjugate for the image.
 //
-// What bounds it: FP64 issue of 6 (p + 1) operations per row and ~80 for the row's geometry.  Two vectors
-// share the powers up to p = 20; beyond, their sums would not leave two waves per SIMD.
+// What bounds it: the reads of scattered points and the read-modify-write of the locals: 450 MB in 175 us for
+// the deep launch of the 4M curve, whose waves wait 73% of their time; issue (6 (p + 1) FP64 operations per
+// row and ~80 for its geometry) is 27% there, and 48% with eight vectors on the 2M forest.  Two vectors
+// share the powers up to p = 20; beyond, their sums would not leave two waves per SIMD.  At p = 15 with
+// sixteen lanes a box, one vector's sums spill 8 registers (10 for dipoles) of the 128 of four waves.
 // The kernel it replaced formed the terms of 64 rows in LDS and summed them from there, at seven waves per
 // CU.  All launches of an evaluation alone on the GPU: 4M points along a curve, p = 30: 1,035 -> 255 us;
 // 2M points in 64 instances, p = 20, eight vectors: 1,205 -> 367 us (and 33 us for the rows with reaction

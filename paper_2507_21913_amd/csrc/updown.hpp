@@ -15,8 +15,10 @@
 // each box's own local on the way.  Empty positions carry zeros; a level that is empty in the whole
 // wave is skipped.
 //
-// What bounds it: a few thousand cycles of FP64 issue per level and wave, at one or two waves per SIMD,
-// behind one or two memory latencies per band.  The passes it replaced kept subtrees in LDS and were
+// What bounds it: a few thousand cycles of FP64 issue per level and wave, at two waves per SIMD up to p = 20
+// and one from p = 30 (256 registers, and accumulation registers that hold the rest of x by copies: 2 and 56
+// at p = 30, 90 and 160 at p = 40, M2M and L2L; the L2L has 8 at p = 25), behind one or two memory latencies
+// per band.  The passes it replaced kept subtrees in LDS and were
 // bound by LDS reads (two 16-byte reads per four multiply-adds) and one launch per level above.  Alone
 // on the GPU, all launches of an evaluation: 1M uniform points, p = 20: M2M 98 -> 38 us, L2L 62 -> 39 us;
 // 20,000 points along a curve (depth 10, complex impedance), p = 30: M2M 99 -> 49 us, L2L 188 -> 46 us;
