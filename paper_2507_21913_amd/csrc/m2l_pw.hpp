@@ -217,9 +217,10 @@ __device__ __forceinline__ void pw_targets(const PwArgs &a, cplx *sX, const doub
 }
 
 // p <= 20: 128 registers, two workgroups (16 waves) per CU.  They do not quite hold p = 20: 14 spills, 52
-// bytes of scratch a lane, before and after the loop over the nodes (one spill at p = 10); two workgroups
-// were still faster than one of 180 registers (1M points: 99 -> 80 us with the scalar table loads).  Above,
-// the locals alone take up to 164 and one workgroup fits: 164, 194, 224 and 254 registers, no spills.
+// bytes of scratch a lane, two of them LDS addresses that one row's target waves reload in every step, the
+// others before and after the steps (one spill at p = 10); two workgroups were still faster than one of 180
+// registers (1M points: 99 -> 80 us with the scalar table loads).  Above, the locals alone take up to 164
+// and one workgroup fits: 164, 194, 224 and 254 registers, no spills.
 template <int PB>
 __global__ __launch_bounds__(512, PB <= 20 ? 4 : 2) void k_m2l_pw(PwArgs a) {
     constexpr int P1 = PB + 1, NS = pw_steps(PB), TS = pw_src_row(PB);
