@@ -32,9 +32,9 @@ PEAK_FP32_MATRIX_TFLOPS = 157.3  # MI355X fp32 matrix peak
 # HBM bytes of k_m2l_pw per evaluation measured with rocprofv3 counter runs (2.00 x FETCH_SIZE + 1.00 x
 # WRITE_SIZE, the factors a plain 256 MiB copy gives), keyed by a hash of the evaluation sources and
 # (p, leaf size): reported (per launch) only while the kernels are the ones that were measured.
-M2L_TRAFFIC = {("1b0c5e13cd2b5d93", 20, 32): 120.2e6, ("1b0c5e13cd2b5d93", 20, 40): 119.7e6}
+M2L_TRAFFIC = {("16eabef2726de3c9", 20, 32): 120.2e6, ("16eabef2726de3c9", 20, 40): 119.7e6}
 # k_near per launch (rocprofv3 FETCH_SIZE and WRITE_SIZE, scaled as above), same key
-NEAR_TRAFFIC = {("1b0c5e13cd2b5d93", 20, 32): 85.2e6, ("1b0c5e13cd2b5d93", 20, 40): 85.1e6}
+NEAR_TRAFFIC = {("16eabef2726de3c9", 20, 32): 85.2e6, ("16eabef2726de3c9", 20, 40): 85.1e6}
 # Nodes of the plane-wave quadrature by compiled order
 PW_NODES = {5: 22, 10: 25, 15: 29, 20: 34, 25: 40, 30: 40, 35: 44, 40: 46}
 NEAR_FLOPS = 17.0  # float64 flops of a near pair: 7 FMA (log 5), 1 mul, 2 add

@@ -122,8 +122,8 @@ inline fmmhp_status ensure_split(Arena &A, const Tree &T, Sched &S, int g) {
 // where the memory is short, fewer, and within a recording those that there are.
 inline fmmhp_status grow_split(Arena &A, const Tree &T, Sched &S, int nvec, hipStream_t s) {
     auto grow = [&](int g) { return ensure_split(A, T, S, g); };
-    if (S.ccap == 0) return widen(std::min(nvec, kVecChunk / 2), 0, S.ccap_limit, grow);
-    if (S.ccap >= std::min(nvec, S.ccap_limit) || recording(s)) return FMMHP_OK;
+    if (S.ccap >= std::min(nvec, S.ccap_limit)) return FMMHP_OK;
+    if (recording(s)) return grow(1);  // (a refusal there says nothing about the memory)
     RelaxedCapture relaxed;
     return widen(std::min(nvec, kVecChunk / 2), S.ccap, S.ccap_limit, grow);
 }
