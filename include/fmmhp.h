@@ -230,7 +230,7 @@ fmmhp_status fmmhp_batch_plan_create(int n_inst, const int64_t *offsets, const d
  * widest pass the first time; the plan keeps the narrower workspace as well, which a recorded graph may
  * hold.  Where the memory is short, and while stream records a graph of the caller's, the call takes the
  * widest passes that the present workspace serves instead (warm up with the same n_vec before recording
- * for the wide ones).  Complex charges: see fmmhp_eval_complex.  No host synchronisation.
+ * for the wide ones); a width whose memory was not there is not tried again on that plan.  Complex charges: see fmmhp_eval_complex.  No host synchronisation.
  */
 fmmhp_status fmmhp_eval(fmmhp_plan_t plan, int n_vec, const double *q, double *phi,
                         hipStream_t stream);
